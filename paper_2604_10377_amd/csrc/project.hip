@@ -17,6 +17,8 @@
 // Backward: rows of dF are vertices; a wave owns 32 vertices x NT*32 feature
 // columns and contracts over k.  The two lane halves take the two halves of
 // the k range, so a lane walks along its own basis row.
+#include <algorithm>
+
 #include "fmap_device.h"
 #include "fmap_launch.h"
 #include "fmap_lds.h"
@@ -694,22 +696,34 @@ static bool lds_fwd_shape_ok(int64_t n, int64_t k, int64_t d, int32_t dtype)
 
 static bool aligned16(const void *p) { return ((uintptr_t)p & 15) == 0; }
 
+// The chunk budget that workspaces are sized for: the chunks of the general, LDS, bf16 and emulated kernels and,
+// for k > 64, two workgroups per CU over 64-row slices and 256-column blocks (the tall kernel needs no more).  The
+// sizes it gives decide which calls the built-in scratch array takes, so they stay as they are.
+static int64_t other_nsplit(int64_t batch, int64_t n, int64_t k, int64_t d, int32_t dtype)
+{
+    int64_t ns = plan_project(batch, n, k, d, dtype).nsplit;
+    if (lds_fwd_shape_ok(n, k, d, dtype)) ns = std::max<int64_t>(ns, lds_fwd_nsplit(batch, n, d));
+    if (dtype == 1 && bf16_fwd_shape_ok(n, k, d)) ns = std::max<int64_t>(ns, bf16_fwd_nsplit(batch, n, k, d));
+    if (dtype == 0 && f32_split_fwd_shape_ok(n, k, d)) ns = std::max<int64_t>(ns, f32_split_fwd_nsplit(batch, n, k, d));
+    if (dtype == 0 && k > 64 && k <= kMaxK && k % 4 == 0 && d % 4 == 0 && n % 4 == 0 && n >= 128) {
+        const int64_t blocks = (d + 255) / 256 * ((k + 63) / 64), quarter = (n + 31) / 32 / 4;
+        ns = std::max<int64_t>(ns, std::min<int64_t>(2 * device_cu_count() / (batch * blocks), quarter));
+    }
+    return ns;
+}
+
+// Chunks of the tall kernel: within that budget, or more while the partial sums fit the built-in scratch array (a
+// few shapes of any n then still spread over the chip, and no call outgrows the array).
+static int tall_chunks(int64_t batch, int64_t n, int64_t k, int64_t d)
+{
+    const int64_t fit = (int64_t)(32u << 20) / (batch * k * d * (int64_t)sizeof(float));
+    return tall_nsplit(batch, n, k, d, std::max(fit, other_nsplit(batch, n, k, d, 0)));
+}
+
 size_t project_workspace_bytes(int64_t batch, int64_t n, int64_t k, int64_t d, int32_t dtype)
 {
-    ProjPlan p = plan_project(batch, n, k, d, dtype);
-    int64_t ns = p.nsplit;
-    if (lds_fwd_shape_ok(n, k, d, dtype)) {
-        const int64_t nl = lds_fwd_nsplit(batch, n, d);
-        if (nl > ns) ns = nl;
-    }
-    if (dtype == 1 && bf16_fwd_shape_ok(n, k, d)) {
-        const int64_t nb = bf16_fwd_nsplit(batch, n, k, d);
-        if (nb > ns) ns = nb;
-    }
-    if (dtype == 0 && f32_split_fwd_shape_ok(n, k, d)) {
-        const int64_t nx = f32_split_fwd_nsplit(batch, n, k, d);
-        if (nx > ns) ns = nx;
-    }
+    int64_t ns = other_nsplit(batch, n, k, d, dtype);
+    if (dtype == 0 && tall_shape_ok(n, k, d)) ns = std::max<int64_t>(ns, tall_chunks(batch, n, k, d));
     if (ns <= 1) return 0;
     return (size_t)batch * ns * k * d * sizeof(float);
 }
@@ -854,6 +868,9 @@ hipError_t launch_reduce(const float *part, int nsplit, int64_t batch, int64_t k
 hipError_t launch_project(const void *phi, const float *mass, const void *feat, int32_t dtype, int64_t batch, int64_t n,
                           int64_t k, int64_t d, float *A, void *ws, hipStream_t st)
 {
+    if (dtype == 0 && tall_shape_ok(n, k, d) && aligned16(feat) && aligned16(A) && aligned16(ws))
+        return launch_project_tall((const float *)phi, mass, (const float *)feat, batch, n, k, d,
+                                   tall_chunks(batch, n, k, d), A, ws, st);
     if (dtype == 0 && f32_split_fwd_shape_ok(n, k, d) && aligned16(phi) && aligned16(mass) && aligned16(feat))
         return launch_project_f32_split((const float *)phi, mass, (const float *)feat, batch, n, k, d, A, ws, st);
     if (lds_fwd_shape_ok(n, k, d, dtype) && aligned16(phi) && aligned16(mass) && aligned16(feat)) {

@@ -839,13 +839,10 @@ __host__ __device__ constexpr int x3_np(int k) { return (k + 7) / 8; }  // 1 KB 
 // as in the backward above).  Features through registers, basis x mass split
 // once per workgroup.
 //
-// Workgroup = 4 waves over a 256-column block and 64 (padded) basis rows: all
-// of them for k <= 64 (k even), or, SLICED (k > 64, k % 4 == 0), the slice
-// [64 kb, 64 kb + 64), each stage then holding that 64-float slice of every
-// vertex row (8 windows of 4 vertices).  The row blocks and column blocks of
-// one vertex chunk take consecutive ids on one XCD, so the feature tile they
-// all read comes from HBM once and from that XCD's L2 afterwards.  Within a block:
-// wave w owns block columns 64w .. 64w + 63 (column 4m + t of the wave is
+// Workgroup = 4 waves over a 256-column block and 64 (padded) basis rows (k <= 64,
+// k even; larger k runs on the tall kernel).  The column blocks of one vertex
+// chunk take consecutive ids on one XCD, so the basis tile they all read comes
+// from HBM once and from that XCD's L2 afterwards.  Within a block: wave w owns block columns 64w .. 64w + 63 (column 4m + t of the wave is
 // column m of tile t).  Stages of 32 vertices.  Each lane loads its 4 feature
 // columns of 8 vertices straight into registers (eight 16-byte loads), two
 // stages ahead, so the feature stream -- nearly all of the bytes -- needs no
@@ -864,34 +861,27 @@ constexpr int RSTAGE = 8 * 1024 + 256;  // basis windows + mass window
 constexpr int RPARTS = 3 * 4 * 64 * 16;  // split basis tile: [part][row tile][lane] of u32x4
 __host__ __device__ constexpr size_t x3r_lds() { return (size_t)RNST * RSTAGE + RPARTS; }
 
-// One workgroup's block: vertices [vbeg, vend) of one shape (P, Mv, F), basis rows [64 kb, 64 kb + 64)
-// (all rows unless SLICED), columns [dbase, dbase + 256); the k x d partial slot O receives its part.
-// vbeg is a multiple of 32, and every stage but the last is full.
-template <bool SLICED>
+// One workgroup's block: vertices [vbeg, vend) of one shape (P, Mv, F), columns [dbase, dbase + 256); the
+// k x d partial slot O receives its part.  vbeg is a multiple of 32, and every stage but the last is full.
 __device__ __forceinline__ void x3r_block(const float *__restrict__ P, const float *__restrict__ Mv,
-                                          const float *__restrict__ F, int n, int k, int d, int vbeg, int vend,
-                                          int kb, int dbase, float *__restrict__ O)
+                                          const float *__restrict__ F, int k, int d, int vbeg, int vend, int dbase,
+                                          float *__restrict__ O)
 {
     extern __shared__ __align__(16) float smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int m16 = lane & 15, g4 = lane >> 4;
-    const int kbase = SLICED ? 64 * kb : 0;
-    const int kvalid = SLICED ? min(64, k - kbase) : k;  // basis rows of this block
-    const int pstride = SLICED ? 64 : k;                 // LDS floats per vertex row of the basis tile
     const int nst = (vend - vbeg + XS - 1) / XS;
 
-    const int np = SLICED ? 8 : x3_np(k);
+    const int np = x3_np(k);
     char *ring = reinterpret_cast<char *>(smem);
     u32x4_t *parts = reinterpret_cast<u32x4_t *>(ring + RNST * RSTAGE);
     for (int e = tid * 16; e < RNST * RSTAGE; e += 256 * 16) *reinterpret_cast<f32x4 *>(ring + e) = f32x4{0, 0, 0, 0};
     __syncthreads();
 
     // basis roles: windows wave and wave + 4 (clamped to the last), the mass window.  A window is
-    // 256 contiguous floats of the 32 x k tile or, sliced, vertices 4w .. 4w + 3 of the slice with
-    // lane l taking the 4 floats at column 64 kb + 4 (l % 16) (clamped to k - 4) of vertex 4w + l/16
+    // 256 contiguous floats of the 32 x k tile
     const int pw0 = min(wave, np - 1), pw1 = min(wave + 4, np - 1);
-    const int scol = min(kbase + 4 * (lane & 15), k - 4);
     const int poff0 = min(pw0 * 256 + 4 * lane, XS * k - 4), poff1 = min(pw1 * 256 + 4 * lane, XS * k - 4);
     // feature role: columns fc .. fc + 3 (clamped into d; d % 4 == 0) of vertices 8 g4 .. + 7
     const int cw = wave * 64 + 4 * m16;
@@ -901,22 +891,15 @@ __device__ __forceinline__ void x3r_block(const float *__restrict__ P, const flo
         const int v = vbeg + t * XS;
         const int rows = min(XS, vend - v);  // a multiple of 4 (n % 4 == 0)
         const float *Pv = P + (size_t)v * k;
-        if (SLICED) {  // vertices past the stage's rows read the last row
-            const int r0 = min(4 * pw0 + (lane >> 4), rows - 1), r1 = min(4 * pw1 + (lane >> 4), rows - 1);
-            dma16(Pv + (size_t)r0 * k + scol, reinterpret_cast<float *>(S + pw0 * 1024));
-            dma16(Pv + (size_t)r1 * k + scol, reinterpret_cast<float *>(S + pw1 * 1024));
-        } else {
-            const int pv = rows * k - 4;
-            dma16(Pv + min(poff0, pv), reinterpret_cast<float *>(S + pw0 * 1024));
-            dma16(Pv + min(poff1, pv), reinterpret_cast<float *>(S + pw1 * 1024));
-        }
+        const int pv = rows * k - 4;
+        dma16(Pv + min(poff0, pv), reinterpret_cast<float *>(S + pw0 * 1024));
+        dma16(Pv + min(poff1, pv), reinterpret_cast<float *>(S + pw1 * 1024));
         __builtin_amdgcn_global_load_lds((glb_void_t *)(Mv + v + min(lane & 31, rows - 1)),
                                          (lds_void_t *)(S + 8 * 1024), 4, 0, 0);
-        // (sliced, the row blocks of a chunk re-read the same features from L2: ordinary loads there)
 #pragma unroll
         for (int i = 0; i < RFF; ++i) {
             const f32x4 *fp = reinterpret_cast<const f32x4 *>(F + (size_t)(v + min(8 * g4 + i, rows - 1)) * d + fc);
-            fr[i] = SLICED ? *fp : stream_load(fp);
+            fr[i] = stream_load(fp);
         }
     };
 
@@ -927,8 +910,8 @@ __device__ __forceinline__ void x3r_block(const float *__restrict__ P, const flo
         for (int t = 0; t < 4; ++t) acc[a][t] = f32x4{0, 0, 0, 0};
     // split role: row tile a = wave, operand lane = lane: basis row 4 m16 + wave, vertices 8 g4 .. + 7
     const int srow = 4 * m16 + wave;
-    const bool srow_ok = srow < kvalid;
-    const int srow_c = min(srow, kvalid - 1);
+    const bool srow_ok = srow < k;
+    const int srow_c = min(srow, k - 1);
 
     auto stage = [&](int t, const f32x4 (&fr)[RFF]) {
         const char *S = ring + (t % RNST) * RSTAGE;
@@ -943,7 +926,7 @@ __device__ __forceinline__ void x3r_block(const float *__restrict__ P, const flo
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 // the mass is masked, not the product, so the LDS reads are unconditional and issued together
-                const float pv = Ps[(8 * g4 + i) * pstride + srow_c];
+                const float pv = Ps[(8 * g4 + i) * k + srow_c];
                 x[i] = pv * ((srow_ok && 8 * g4 + i < vrem) ? mv[i] : 0.f);
             }
             uint32_t w[4][3];
@@ -1029,54 +1012,47 @@ __device__ __forceinline__ void x3r_block(const float *__restrict__ P, const flo
     for (int r = 0; r < 4; ++r)
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
-            const int row = kbase + 16 * g4 + 4 * r + a;
+            const int row = 16 * g4 + 4 * r + a;
             if (row >= k || col >= d) continue;
             const f32x4 v = f32x4{acc[a][0][r], acc[a][1][r], acc[a][2][r], acc[a][3][r]};
             *reinterpret_cast<f32x4 *>(O + (size_t)row * d + col) = v;  // d % 4 == 0: all 4 columns exist
         }
 }
 
-template <bool SLICED>
 __global__ __launch_bounds__(256, 2) void proj_fwd_x3r_kernel(const float *__restrict__ phi,
                                                              const float *__restrict__ mass,
                                                              const float *__restrict__ feat, int n, int k, int d,
-                                                             int nsplit, int dblocks, int kblocks, int ntiles,
-                                                             float *__restrict__ out)
+                                                             int nsplit, int dblocks, int ntiles, float *__restrict__ out)
 {
     const int bid = blockIdx.x;
     const int xs = bid & 7, q = bid >> 3;
-    const int dk = dblocks * kblocks;
-    const int db = (q % dk) % dblocks, kb = (q % dk) / dblocks;
-    const int j = (q / dk) * 8 + xs;
+    const int db = q % dblocks;
+    const int j = (q / dblocks) * 8 + xs;
     if (j >= ntiles) return;  // whole workgroup, before any barrier
     const int split = j % nsplit, s = j / nsplit;
     const int nst_all = (n + XS - 1) / XS;
     const int st0 = (int)(((long)split * nst_all) / nsplit), st1 = (int)(((long)(split + 1) * nst_all) / nsplit);
-    x3r_block<SLICED>(phi + (size_t)s * n * k, mass + (size_t)s * n, feat + (size_t)s * n * d, n, k, d, st0 * XS,
-                      min(n, st1 * XS), kb, db * 256, out + (size_t)j * k * d);
+    x3r_block(phi + (size_t)s * n * k, mass + (size_t)s * n, feat + (size_t)s * n * d, k, d, st0 * XS,
+              min(n, st1 * XS), db * 256, out + (size_t)j * k * d);
 }
 
 // Uneven batches: one workgroup per work item (items of whole 32-vertex stages only).
-template <bool SLICED>
 __global__ __launch_bounds__(256, 2) void proj_fwd_x3r_items_kernel(const FwdItem *__restrict__ items)
 {
     const FwdItem w = items[blockIdx.x];
     if (w.v0 >= w.v1) return;  // empty slot of the table (whole workgroup, before any barrier)
-    x3r_block<SLICED>(global_ptr(w.phi), global_ptr(w.mass), global_ptr(w.feat), w.n, w.k, w.d, w.v0, w.v1, w.kbase / 64,
-                      w.dbase, global_ptr(w.out));
+    x3r_block(global_ptr(w.phi), global_ptr(w.mass), global_ptr(w.feat), w.k, w.d, w.v0, w.v1, w.dbase,
+              global_ptr(w.out));
 }
 
 bool f32_split_fwd_shape_ok(int64_t n, int64_t k, int64_t d)
 {
-    const bool kok = (k >= 4 && k <= 64 && k % 2 == 0) || (k > 64 && k <= kMaxK && k % 4 == 0);
-    return kok && d % 4 == 0 && n % 4 == 0 && n >= 4 * XS;
+    return k >= 4 && k <= 64 && k % 2 == 0 && d % 4 == 0 && n % 4 == 0 && n >= 4 * XS;
 }
-
-static int x3_kblocks(int64_t k) { return k <= 64 ? 1 : (int)((k + 63) / 64); }
 
 int f32_split_fwd_nsplit(int64_t batch, int64_t n, int64_t k, int64_t d)
 {
-    const int64_t blocks = (d + 255) / 256 * x3_kblocks(k);
+    const int64_t blocks = (d + 255) / 256;
     const int64_t stages = (n + XS - 1) / XS;
     int64_t ns = (2 * device_cus()) / (batch * blocks);  // two workgroups per CU
     if (ns > stages / 4) ns = stages / 4;               // keep >= 4 stages per chunk
@@ -1084,16 +1060,14 @@ int f32_split_fwd_nsplit(int64_t batch, int64_t n, int64_t k, int64_t d)
     return (int)ns;
 }
 
-template <bool SLICED>
 static hipError_t dispatch_x3r(const float *phi, const float *mass, const float *feat, int64_t batch, int64_t n,
                                int64_t k, int64_t d, int ns, float *out, hipStream_t st)
 {
     const int dblocks = (int)((d + 255) / 256);
-    const int kblocks = x3_kblocks(k);
     const int ntiles = (int)(batch * ns);
-    const unsigned grid = (unsigned)(8 * dblocks * kblocks * ((ntiles + 7) / 8));
-    hipLaunchKernelGGL((proj_fwd_x3r_kernel<SLICED>), dim3(grid), dim3(256), x3r_lds(), st, phi, mass, feat, (int)n,
-                       (int)k, (int)d, ns, dblocks, kblocks, ntiles, out);
+    const unsigned grid = (unsigned)(8 * dblocks * ((ntiles + 7) / 8));
+    hipLaunchKernelGGL(proj_fwd_x3r_kernel, dim3(grid), dim3(256), x3r_lds(), st, phi, mass, feat, (int)n,
+                       (int)k, (int)d, ns, dblocks, ntiles, out);
     return hipGetLastError();
 }
 
@@ -1102,8 +1076,7 @@ hipError_t launch_project_f32_split(const float *phi, const float *mass, const f
 {
     const int ns = f32_split_fwd_nsplit(batch, n, k, d);
     float *out = ns > 1 ? (float *)ws : A;
-    hipError_t e = k <= 64 ? dispatch_x3r<false>(phi, mass, feat, batch, n, k, d, ns, out, st)
-                           : dispatch_x3r<true>(phi, mass, feat, batch, n, k, d, ns, out, st);
+    hipError_t e = dispatch_x3r(phi, mass, feat, batch, n, k, d, ns, out, st);
     if (e != hipSuccess || ns <= 1) return e;
     return launch_reduce(out, ns, batch, k, d, A, st);
 }
@@ -1241,16 +1214,13 @@ hipError_t launch_project_backward_f32k(const float *phi, const float *mass, con
 // ---------------------------------------------------------------------------
 bool x3r_item_shape_ok(int64_t k, int64_t d)
 {
-    return ((k >= 4 && k <= 64 && k % 2 == 0) || (k > 64 && k <= kMaxK && k % 4 == 0)) && d % 4 == 0;
+    return k >= 4 && k <= 64 && k % 2 == 0 && d % 4 == 0;
 }
 
-hipError_t launch_fwd_x3r_items(const FwdItem *items, int nitems, bool sliced, hipStream_t st)
+hipError_t launch_fwd_x3r_items(const FwdItem *items, int nitems, hipStream_t st)
 {
     if (nitems <= 0) return hipSuccess;
-    if (sliced)
-        hipLaunchKernelGGL((proj_fwd_x3r_items_kernel<true>), dim3((unsigned)nitems), dim3(256), x3r_lds(), st, items);
-    else
-        hipLaunchKernelGGL((proj_fwd_x3r_items_kernel<false>), dim3((unsigned)nitems), dim3(256), x3r_lds(), st, items);
+    hipLaunchKernelGGL(proj_fwd_x3r_items_kernel, dim3((unsigned)nitems), dim3(256), x3r_lds(), st, items);
     return hipGetLastError();
 }
 

@@ -11,119 +11,241 @@
 // (A_re[c][0], -A_im[c][0], A_re[c][1], -A_im[c][1], ...) and row c of W_im is
 // (A_im[c][j], A_re[c][j]) pairs (variant A) or (A_re[c][j], A_im[c][j]) pairs
 // (variant B).  That is a dense contraction of 8 D^2 flops per vertex against
-// 12 D bytes of traffic (85 flop/B at D = 128): it runs on the float32 matrix
-// cores (v_mfma_f32_32x32x2_f32), with the elementwise combination fused into
-// the epilogue.
+// 12 D bytes of traffic (85 flop/B at D = 128), with the elementwise combination
+// fused into the epilogue.  On the float32 matrix cores it was bound by them
+// (160000 vertices, D = 128: 224 us, 94 TFLOP/s); it runs on the float16 ones with
+// both operands split in two (fmap_split.h), three products per float32 one.
 //
-// A workgroup owns a block of 32 output channels: it builds the 64 rows of W
-// for them (32 of W_re, 32 of W_im) in LDS once and then walks vertex tiles of
-// 32, one tile per wave at a time.  Lane (m, h) (m = lane % 32, h = lane / 32)
-// reads 16-byte pieces of the z row of vertex m straight from global memory;
-// the matrix-core K order is permuted so that each lane uses its own four
-// consecutive values in four steps, and the W operand is read the same way
-// from LDS.  The workgroups of one vertex range and different channel blocks
-// get consecutive ids in one residue class mod 8 (one XCD), so the z rows they
-// all read come from HBM once and then from that XCD's L2.
+// The weights stay in registers: a wave holds the parts of W for 16 channels (D = 256: 8), both rows of each, as
+// matrix-core operands with one scale per channel, at most 128 registers, and the 8 waves of a workgroup cover all D
+// channels (D = 256: 64), so z is read and split once (four times).  A tile of z rows goes through LDS: its loading
+// waves take whole rows, 8 consecutive values per lane, scale each row by its largest value, and write the parts as
+// operand slots, permuted so that the lanes of a row hit different bank groups.  Two tiles are in LDS (one barrier
+// per tile) and a third one's loads are in flight.  The result tile has channels along registers: a lane ends up
+// with 4 consecutive channels of one vertex and stores 16 bytes.  With W in LDS instead and the split z rows in
+// registers, every wave loaded, split and multiplied in turn, all at the same time: 87 us at 160000 vertices, D = 128.
+// Measured (160000 vertices; before: float32 matrix cores): D = 32 32.4 -> 17.1 us, D = 64 64 -> 29 us, D = 128
+// 208 -> 69 us (3.6 TB/s of its bytes), 200000 vertices of D = 256 1160 -> 365 us; 5000 of D = 128 42 -> 11.5 us.  The
+// error against float64 falls: 2.9e-7 -> 1.9e-7 at D = 128, 4.1e-7 -> 2.5e-7 at D = 256.  Up to D = 128 it is bound by
+// memory and its latency (one tile in flight per workgroup); at D = 256 by LDS: a wave's 128 weight registers hold
+// one row tile, so every operand read from LDS feeds three products.
 #include "../../include/fmap.h"
 
 #include <algorithm>
 
-#include "fmap_device.h"
 #include "fmap_launch.h"
+#include "fmap_lds.h"
+#include "fmap_split.h"
 
 namespace fmap {
 
 namespace {
 
-constexpr int GF_WAVES = 4;
-constexpr int GF_CB = 32;  // output channels per workgroup
+constexpr int GF_WAVES = 8;
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // g need not be 16-byte aligned
 
 __device__ __forceinline__ f32x4 ld4(const float *p) { return *reinterpret_cast<const f32x4 *>(p); }
 
+template <int D>
+struct Gf {
+    static constexpr int K = 2 * D, KS = K / 32;      // row length, K steps
+    static constexpr int CH = D <= 128 ? 16 : 8;      // channels per wave
+    static constexpr int NR = D <= 128 ? 2 : 1;       // its W row tiles: re and im, or 8 re + 8 im rows in one
+    static constexpr int CW = D <= 128 ? D / CH : 8;  // waves along the channels
+    static constexpr int NB = D / (CW * CH);          // channel blocks (workgroups per vertex range)
+    static constexpr int VT = 2, VW = GF_WAVES / CW;  // vertex tiles of 16 per wave, waves along the vertices
+    static constexpr int VERTS = 16 * VT * VW;        // vertices per tile of the workgroup
+    static constexpr int RPW = VERTS / GF_WAVES;      // rows a wave loads
+    static constexpr int LR = 64 / RPW;               // lanes per row
+    static constexpr int PASS = K / (8 * LR);         // 8-value pieces per lane
+    static constexpr int BUF = VERTS * K / 4;         // 16-byte slots per tile (two float16 parts per value)
+    static constexpr size_t LDS = (size_t)2 * BUF * 16 + 2 * VERTS * sizeof(int);
+    static constexpr int PER_CU = D <= 32 ? 2 : 1;    // resident workgroups (registers, LDS)
+};
+
 }  // namespace
 
-// z [V][2D], A_re, A_im [D][D], g [V][D]; D % 32 == 0, D <= 512.  grid = vgroups * (D / 32), XCD-ordered.
+// z [V][2D], A_re, A_im [D][D], g [V][D].  grid = vgroups * NB, XCD-ordered.
 template <int D>
-__global__ __launch_bounds__(256) void gradfeat_mfma_kernel(const float *__restrict__ z, const float *__restrict__ Are,
-                                                            const float *__restrict__ Aim, int variant, int V,
-                                                            int vgroups, float *__restrict__ g)
+__global__ __launch_bounds__(64 * GF_WAVES, D <= 32 ? 4 : 2) void gradfeat_mfma_kernel(
+    const float *__restrict__ z, const float *__restrict__ Are, const float *__restrict__ Aim, int variant, int V,
+    int vgroups, float *__restrict__ g)
 {
-    constexpr int K = 2 * D;
-    constexpr int WP = K + 4;  // LDS row pitch of W (floats): 16-byte aligned, rows 4 banks apart
-    constexpr int Q = K / 8;   // 8 k values per lane pair and step group
-    extern __shared__ __align__(16) float sW[];  // [64][WP]: rows 0..31 W_re, 32..63 W_im of this block
-    const int nb = D / GF_CB;
-    // XCD-aware decode: ids b, b + 8, b + 16, ... share an XCD; the nb channel blocks of one vertex group are
+    using C = Gf<D>;
+    constexpr int K = C::K, KS = C::KS;
+    extern __shared__ __align__(16) float smem[];
+    u32x4_t *buf = reinterpret_cast<u32x4_t *>(smem);       // two tiles [vertex tile][K step][part][64 slots]
+    int *s_zs = reinterpret_cast<int *>(buf + 2 * C::BUF);  // [2][VERTS] row shifts
+    // XCD-aware decode: ids b, b + 8, b + 16, ... share an XCD; the NB channel blocks of one vertex group are
     // consecutive in that sequence
     const int id = blockIdx.x;
     const int per_xcd = (int)((gridDim.x + 7) / 8);
     const int seq = (id % 8) * per_xcd + id / 8;  // position in the XCD-major order
-    if (seq >= vgroups * nb) return;
-    const int vg = seq / nb, cb = seq % nb;
-    const int c0 = cb * GF_CB;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int m = lane & 31, h = lane >> 5;
+    if (seq >= vgroups * C::NB) return;
+    const int vg = seq / C::NB;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int m16 = lane & 15, g4 = lane >> 4;
+    const int vw = wave / C::CW;
+    const int c0 = (seq % C::NB) * C::CW * C::CH + (wave % C::CW) * C::CH;
 
-    // W rows of this channel block
-    for (int e = tid; e < 64 * D; e += 256) {
-        const int r = e / D, j = e % D;  // r < 32: W_re row c0 + r; r >= 32: W_im row c0 + r - 32
-        const int c = c0 + (r & 31);
-        const float ar = Are[(size_t)c * D + j], ai = Aim[(size_t)c * D + j];
-        float w0, w1;
-        if (r < 32) {
-            w0 = ar;
-            w1 = -ai;
-        } else if (variant == 0) {
-            w0 = ai;
-            w1 = ar;
-        } else {
-            w0 = ar;
-            w1 = ai;
+    const int tiles = (V + C::VERTS - 1) / C::VERTS;
+    const int t0 = (int)((long)vg * tiles / vgroups), t1 = (int)((long)(vg + 1) * tiles / vgroups);
+    if (t0 >= t1) return;
+
+    // loading role: 8-value pieces lr, lr + LR, ... of row `row` of the tile
+    const int row = wave * C::RPW + lane / C::LR, lr = lane % C::LR;
+    f32x4 x[C::PASS][2];
+    auto issue = [&](int t) {
+        const float *zr = z + (size_t)min(t * C::VERTS + row, V - 1) * K + 8 * lr;
+#pragma unroll
+        for (int q = 0; q < C::PASS; ++q) {
+            x[q][0] = ld4(zr + 8 * C::LR * q);
+            x[q][1] = ld4(zr + 8 * C::LR * q + 4);
         }
-        sW[r * WP + 2 * j] = w0;
-        sW[r * WP + 2 * j + 1] = w1;
-    }
-    __syncthreads();
+    };
+    // slot of operand lane (m, g) at K step s: the vertex index permuted by the piece number
+    auto slot = [](int m, int g, int s) { return (m ^ (4 * (s & 3) + g)) + 16 * g; };
+    auto split = [&](int b) {
+        float mx = 0.f;
+#pragma unroll
+        for (int q = 0; q < C::PASS; ++q)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) mx = fmaxf(mx, fmaxf(fabsf(x[q][0][e]), fabsf(x[q][1][e])));
+#pragma unroll
+        for (int o = 1; o < C::LR; o *= 2) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+        const int sh = split_shift(__float_as_uint(mx));
+        const float sc = split_scale(sh);
+        if (lr == 0) s_zs[b * C::VERTS + row] = sh;
+        u32x4_t *B = buf + b * C::BUF + (row >> 4) * KS * 128;
+#pragma unroll
+        for (int q = 0; q < C::PASS; ++q) {
+            u32x4_t h, l;
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) {
+                uint32_t hh, ll;
+                split_pair(x[q][jj >> 1][2 * (jj & 1)], x[q][jj >> 1][2 * (jj & 1) + 1], sc, hh, ll);
+                h[jj] = hh;
+                l[jj] = ll;
+            }
+            const int piece = q * C::LR + lr, s = piece >> 2;
+            u32x4_t *o = B + s * 128 + slot(row & 15, piece & 3, s);
+            o[0] = h;
+            o[64] = l;
+        }
+    };
 
-    const int tiles = (V + 31) / 32;
-    const int t_per = (tiles + vgroups - 1) / vgroups;
-    const int t0 = vg * t_per, t1 = min(tiles, t0 + t_per);
-    const float *wre = sW + m * WP + 4 * h;
-    const float *wim = sW + (32 + m) * WP + 4 * h;
-    for (int t = t0 + wave; t < t1; t += GF_WAVES) {
-        const int v0 = 32 * t;
-        const float *zr = z + (size_t)min(v0 + m, V - 1) * K + 4 * h;
-        f32x16 are = zero16(), aim = zero16();
-        // z pieces of 8 step groups in flight at a time
-        constexpr int G = 8;
-#pragma unroll 1
-        for (int q0 = 0; q0 < Q; q0 += G) {
-            f32x4 a[G];
+    issue(t0);
+    // this wave's weights: lane (m16, g4) holds W row m16, values 32 s + 8 g4 .. + 7 of K step s
+    u32x4_t wh[C::NR][KS], wl[C::NR][KS];
+    int wshift[4];  // shifts of the rows 4 g4 + r (a channel's two rows hold the same magnitudes)
+    {
+        const int c = c0 + (C::NR == 2 ? m16 : (m16 & 7));
+        f32x4 ar[KS], ai[KS];
 #pragma unroll
-            for (int u = 0; u < G; ++u) a[u] = ld4(zr + 8 * (q0 + u));
+        for (int s = 0; s < KS; ++s) {
+            ar[s] = *reinterpret_cast<const f32x4u *>(Are + (size_t)c * D + 16 * s + 4 * g4);
+            ai[s] = *reinterpret_cast<const f32x4u *>(Aim + (size_t)c * D + 16 * s + 4 * g4);
+        }
+        float mx = 0.f;
 #pragma unroll
-            for (int u = 0; u < G; ++u) {
-                const f32x4 br = ld4(wre + 8 * (q0 + u)), bi = ld4(wim + 8 * (q0 + u));
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) mx = fmaxf(mx, fmaxf(fabsf(ar[s][e]), fabsf(ai[s][e])));
+        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        const int sh = split_shift(__float_as_uint(mx));
+        const float sc = split_scale(sh);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) wshift[r] = __shfl(sh, 4 * g4 + r, 64);
+#pragma unroll
+        for (int n = 0; n < C::NR; ++n) {
+            const bool im = C::NR == 2 ? n == 1 : m16 >= 8;
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    are = mfma32x32x2(a[u][e], br[e], are);
-                    aim = mfma32x32x2(a[u][e], bi[e], aim);
+                    const float a = ar[s][e], b = ai[s][e];
+                    uint32_t h, l;
+                    split_pair(im && variant == 0 ? b : a, im ? (variant == 0 ? a : b) : -b, sc, h, l);
+                    wh[n][s][e] = h;
+                    wl[n][s][e] = l;
                 }
+        }
+    }
+    split(0);
+    issue(min(t0 + 1, t1 - 1));
+    lds_barrier();
+
+    for (int t = t0; t < t1; ++t) {
+        const int b = (t - t0) & 1;
+        const int v0 = t * C::VERTS + vw * 16 * C::VT;  // this wave's vertices
+        // the lane's output: 4 channels of one vertex per tile (D = 256: the lanes of the upper half take the second
+        // vertex tile, those of the lower half the first); its x and y in flight while the products run
+        const int co = c0 + 4 * (C::NR == 2 ? g4 : (g4 & 1));
+        constexpr int NO = C::NR == 2 ? C::VT : 1;
+        f32x4 xy[NO][2];
+        int vo[NO];
+#pragma unroll
+        for (int n = 0; n < NO; ++n) {
+            vo[n] = v0 + 16 * (C::NR == 2 ? n : g4 >> 1) + m16;
+            const float *zr = z + (size_t)min(vo[n], V - 1) * K + 2 * co;
+            xy[n][0] = ld4(zr);
+            xy[n][1] = ld4(zr + 4);
+        }
+        const u32x4_t *B = buf + b * C::BUF + vw * C::VT * KS * 128;
+        f32x4 acc[C::NR][C::VT];
+#pragma unroll
+        for (int n = 0; n < C::NR; ++n)
+#pragma unroll
+            for (int v = 0; v < C::VT; ++v) acc[n][v] = f32x4{0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            u32x4_t zh[C::VT], zl[C::VT];
+#pragma unroll
+            for (int v = 0; v < C::VT; ++v) {
+                zh[v] = B[v * KS * 128 + s * 128 + slot(m16, g4, s)];
+                zl[v] = B[v * KS * 128 + s * 128 + 64 + slot(m16, g4, s)];
             }
-        }
-        // epilogue: g[v][c] = x_c (A z)_re + y_c (A z)_im for the 16 vertex rows of this lane, channel c0 + m
-        const int c = c0 + m;
-        float2 xy[16];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int v = min(v0 + acc32_row(r, lane), V - 1);
-            xy[r] = *reinterpret_cast<const float2 *>(z + (size_t)v * K + 2 * c);
-        }
+            for (int n = 0; n < C::NR; ++n)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int v = v0 + acc32_row(r, lane);
-            if (v < V) g[(size_t)v * D + c] = xy[r].x * are[r] + xy[r].y * aim[r];
+                for (int v = 0; v < C::VT; ++v) acc[n][v] = mfma16x16x32f16(wl[n][s], zh[v], acc[n][v]);
+#pragma unroll
+            for (int n = 0; n < C::NR; ++n)
+#pragma unroll
+                for (int v = 0; v < C::VT; ++v) acc[n][v] = mfma16x16x32f16(wh[n][s], zl[v], acc[n][v]);
+#pragma unroll
+            for (int n = 0; n < C::NR; ++n)
+#pragma unroll
+                for (int v = 0; v < C::VT; ++v) acc[n][v] = mfma16x16x32f16(wh[n][s], zh[v], acc[n][v]);
         }
+        split(b ^ 1);  // tile t + 1 (past the last one: the last one again, never read)
+        issue(min(t + 2, t1 - 1));
+        // g[v][c] = x_c (A z)_re + y_c (A z)_im; register r of lane (m16, g4): W row 4 g4 + r, vertex m16
+#pragma unroll
+        for (int n = 0; n < NO; ++n) {
+            const f32x4 p = xy[n][0], q = xy[n][1];
+            const float xs[4] = {p[0], p[2], q[0], q[2]}, ys[4] = {p[1], p[3], q[1], q[3]};
+            const int zs = s_zs[b * C::VERTS + vo[n] - t * C::VERTS];
+            f32x4 o;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                float re, im;
+                if constexpr (C::NR == 2) {
+                    re = acc[0][n][r];
+                    im = acc[1][n][r];
+                } else {
+                    const bool up = g4 >= 2;  // holds im rows: keeps those of the second tile, gives the first's away
+                    const float got = __shfl_xor(up ? acc[0][0][r] : acc[0][1][r], 32, 64);
+                    re = up ? got : acc[0][0][r];
+                    im = up ? acc[0][1][r] : got;
+                }
+                const int sh = -(wshift[r] + zs);
+                o[r] = xs[r] * __builtin_amdgcn_ldexpf(re, sh) + ys[r] * __builtin_amdgcn_ldexpf(im, sh);
+            }
+            if (vo[n] < V) *reinterpret_cast<f32x4u *>(g + (size_t)vo[n] * D + co) = o;
+        }
+        lds_barrier();
     }
 }
 
@@ -151,22 +273,21 @@ template <int D>
 static void launch_gf(const float *z, const float *Are, const float *Aim, int variant, int64_t V, float *g,
                       hipStream_t st)
 {
-    const size_t lds = (size_t)64 * (2 * D + 4) * sizeof(float);
+    using C = Gf<D>;
     static bool attr = false;
     if (!attr) {
         (void)hipFuncSetAttribute((const void *)gradfeat_mfma_kernel<D>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)lds);
+                                  (int)C::LDS);
         attr = true;
     }
-    const int nb = D / GF_CB;
-    const int64_t tiles = (V + 31) / 32;
-    // about two workgroups per CU over all channel blocks, at least 4 tiles per wave
-    const int64_t want = std::max<int64_t>(1, 2 * (int64_t)device_cus() / nb);
-    const int64_t vgroups = std::max<int64_t>(1, std::min<int64_t>(want, (tiles + 15) / 16));
-    const int64_t n = vgroups * nb;
+    const int64_t tiles = (V + C::VERTS - 1) / C::VERTS;
+    // one round of resident workgroups over all channel blocks, at least one tile each
+    const int64_t want = std::max<int64_t>(1, (int64_t)C::PER_CU * device_cus() / C::NB);
+    const int64_t vgroups = std::min<int64_t>(want, tiles);
+    const int64_t n = vgroups * C::NB;
     const int64_t grid = ((n + 7) / 8) * 8;  // whole rounds of the 8 XCDs; surplus ids exit
-    hipLaunchKernelGGL((gradfeat_mfma_kernel<D>), dim3((unsigned)grid), dim3(256), lds, st, z, Are, Aim, variant,
-                       (int)V, (int)vgroups, g);
+    hipLaunchKernelGGL((gradfeat_mfma_kernel<D>), dim3((unsigned)grid), dim3(64 * GF_WAVES), C::LDS, st, z, Are, Aim,
+                       variant, (int)V, (int)vgroups, g);
 }
 
 hipError_t launch_gradient_features(const float *z, const float *Are, const float *Aim, int variant, int64_t V,

@@ -37,10 +37,7 @@ struct RedItem {                  // A = sum of `nchunks` partial k x d slots
 hipError_t launch_fwd_items(const FwdItem *items, int nitems, int kmax, int grid, hipStream_t st);
 hipError_t launch_bwd_items(const BwdItem *items, int nitems, int kmax, int grid, hipStream_t st);
 hipError_t launch_reduce_items(const RedItem *items, int nitems, hipStream_t st);
-// Uneven batches on the emulated float32 kernels, one workgroup per item.  Forward items cover whole
-// 32-vertex stages (v0, v1 multiples of 32) of shapes with x3r_item_shape_ok (k <= 64).
-bool x3r_item_shape_ok(int64_t k, int64_t d);
-hipError_t launch_fwd_x3r_items(const FwdItem *items, int nitems, hipStream_t st);
+// Uneven batches on the emulated float32 kernels, one workgroup per item.
 // Backward items of one k (k even, <= kMaxK): mc_item_cols(k) columns per item.
 bool mc_item_shape_ok(int64_t k);
 int mc_item_cols(int64_t k);
@@ -54,12 +51,6 @@ int bf16_fwd_nsplit(int64_t batch, int64_t n, int64_t k, int64_t d);
 bool bf16_bwd_shape_ok(int64_t n, int64_t k, int64_t d);
 hipError_t launch_project_backward_bf16(const uint16_t *phi, const float *mass, const float *dA, int64_t batch,
                                         int64_t n, int64_t k, int64_t d, float *dF, hipStream_t st);
-// float32 forward projection on the bf16 matrix cores, operands split into three bf16 parts
-// (k even <= 64, d % 4 == 0, n % 4 == 0).
-bool f32_split_fwd_shape_ok(int64_t n, int64_t k, int64_t d);
-int f32_split_fwd_nsplit(int64_t batch, int64_t n, int64_t k, int64_t d);
-hipError_t launch_project_f32_split(const float *phi, const float *mass, const float *feat, int64_t batch, int64_t n,
-                                    int64_t k, int64_t d, float *A, void *ws, hipStream_t st);
 // float32 forward projection for 64 < k <= kMaxK on the float16 matrix cores, operands split into two parts
 // (d % 4 == 0, 16-byte aligned features, any n and k).
 bool tall_shape_ok(int64_t n, int64_t k, int64_t d);
@@ -67,7 +58,13 @@ bool tall_shape_ok(int64_t n, int64_t k, int64_t d);
 int tall_nsplit(int64_t batch, int64_t n, int64_t k, int64_t d, int64_t cap);
 hipError_t launch_project_tall(const float *phi, const float *mass, const float *feat, int64_t batch, int64_t n,
                                int64_t k, int64_t d, int ns, float *A, void *ws, hipStream_t st);
-// Its work-item form: instances by class of k, tall_cols(k) columns per item.
+// The same for k <= 64.
+bool short_shape_ok(int64_t n, int64_t k, int64_t d);
+int short_nsplit(int64_t batch, int64_t n, int64_t k, int64_t d);
+hipError_t launch_project_short(const float *phi, const float *mass, const float *feat, int64_t batch, int64_t n,
+                                int64_t k, int64_t d, int ns, float *A, void *ws, hipStream_t st);
+hipError_t launch_fwd_short_items(const FwdItem *items, int nitems, hipStream_t st);
+// The tall kernel's work-item form: instances by class of k, tall_cols(k) columns per item.
 constexpr int kTallClasses = 4;
 int tall_class(int64_t k);
 int tall_cols(int64_t k);

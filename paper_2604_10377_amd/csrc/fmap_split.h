@@ -25,13 +25,15 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 // Scaled values of this magnitude or more do not fit (the largest float16 is 65504).
 constexpr float kSplitLimit = 65000.f;
 
-// Power-of-two shift that brings values of magnitude <= |m| (given as float bits, sign clear) below 2^14:
-// [2^13, 2^14) for normal m, so values up to 4 |m| fit before the scale has to be lowered.  Clamped so that
-// both 2^shift and 2^-shift are normal numbers; zero gives the largest shift.
+// Power-of-two shift that brings values of magnitude <= |m| (given as float bits, sign clear) below 2^(TOP + 1):
+// [2^TOP, 2^(TOP + 1)) for normal m.  With TOP = 13 values up to 4 |m| fit, with TOP = 9 up to 64 |m| (values below
+// 2^-11 |m| then keep fewer than 22 bits, to 2^-34 |m|).  Clamped so that both 2^shift and 2^-shift are normal numbers;
+// zero gives the largest shift.
+template <int TOP = 13>
 __device__ __forceinline__ int split_shift(uint32_t mbits)
 {
     const int e = (int)(mbits >> 23) - 127;
-    return max(-126, min(126, 13 - e));
+    return max(-126, min(126, TOP - e));
 }
 __device__ __forceinline__ float split_scale(int shift) { return __uint_as_float((uint32_t)(shift + 127) << 23); }
 

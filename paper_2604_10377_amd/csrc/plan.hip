@@ -4,11 +4,10 @@
 // one batch dimension, Eq. (8)), allocates the group buffers, and builds device
 // tables of work items:
 //   - forward projection items: (shape, vertex chunk, 64-row k block, 256-column
-//     d block).  Shapes of k <= 64 that the emulated float32 kernel takes (k even,
-//     d % 4 == 0, 16-byte aligned rows) run their whole 32-vertex stages on it,
-//     one workgroup per item; those of k > 64 run on the tall kernel (d % 4 == 0,
-//     one launch per class of k); the last n % 32 vertices of the former, and all
-//     other shapes, are items of ONE persistent launch of the general kernel;
+//     d block).  With d % 4 == 0 and 16-byte aligned features, shapes of k <= 64 run
+//     on the short split kernel and those of k > 64 on the tall one (one launch per
+//     class of k), one workgroup per item; all other shapes are items of ONE
+//     persistent launch of the general kernel;
 //   - reduction items: the fixed-order sum of each shape's chunk partials;
 //   - backward projection items: (shape, 256-vertex tiles, column block) on the
 //     emulated kernels, one launch per k group; (shape, rows, d block) items of
@@ -84,8 +83,8 @@ struct fmap_plan {
     std::vector<Bucket> buckets;
     std::vector<void *> allocs;
     float *partials = nullptr;
-    FwdItem *d_fwd = nullptr, *d_x3 = nullptr, *d_tall[kTallClasses] = {};
-    int nfwd = 0, nx3 = 0, ntall[kTallClasses] = {};
+    FwdItem *d_fwd = nullptr, *d_small = nullptr, *d_tall[kTallClasses] = {};
+    int nfwd = 0, nsmall = 0, ntall[kTallClasses] = {};
     McItem *d_mc = nullptr;
     int nmc = 0;
     RedItem *d_red = nullptr;
@@ -144,11 +143,8 @@ struct Shape {
 
 bool aligned(const void *p, uintptr_t a) { return ((uintptr_t)p & (a - 1)) == 0; }
 
-// the forward of this shape runs its whole stages on the emulated float32 kernel (k <= 64)
-bool x3r_shape(const Shape &s, int64_t d)
-{
-    return x3r_item_shape_ok(s.k, d) && aligned(s.phi, 16) && aligned(s.feat, 16) && s.n >= 32;
-}
+// the forward of this shape runs on the split kernel of k <= 64
+bool short_shape(const Shape &s, int64_t d) { return s.k <= kSmallK && d >= 4 && d % 4 == 0 && aligned(s.feat, 16); }
 
 // the forward of this shape runs on the tall kernel (k > 64)
 bool tall_shape(const Shape &s, int64_t d) { return tall_shape_ok(s.n, s.k, d) && aligned(s.feat, 16); }
@@ -237,10 +233,10 @@ void tall_chunks(const fmap_plan *pl, const std::vector<Shape> &shapes, int (&ch
 }
 
 // Forward and reduction items for a given chunk size (a multiple of 32); partial slots are laid out shape
-// after shape.  it.x3: emulated-kernel items (k <= 64), it.tall: tall-kernel items (k > 64) by class of k,
+// after shape.  it.small: split-kernel items of k <= 64, it.tall: tall-kernel items (k > 64) by class of k,
 // it.general: general-kernel items.
 struct FwdTables {
-    std::vector<FwdItem> general, x3, tall[kTallClasses];
+    std::vector<FwdItem> general, small, tall[kTallClasses];
     std::vector<RedItem> red;
 };
 
@@ -255,8 +251,7 @@ void build_fwd_items(const fmap_plan *pl, int chunk, FwdTables &it, size_t *part
     for (const Shape &s : shapes) {
         const Bucket &B = pl->buckets[s.bucket];
         const bool tall = tall_shape(s, d);
-        // vertices on the tall kernel (all of them) or in whole stages on the emulated kernel
-        const int64_t nfast = tall ? s.n : (x3r_shape(s, d) ? s.n - s.n % 32 : 0);
+        const int64_t nfast = tall || short_shape(s, d) ? s.n : 0;  // vertices on the split kernels: all or none
         const int fchunk = tall ? tchunk[tall_class(s.k)] : chunk;
         const int nchf = (int)((nfast + fchunk - 1) / fchunk);
         const int nchg = (int)((s.n - nfast + chunk - 1) / chunk);
@@ -287,7 +282,7 @@ void build_fwd_items(const fmap_plan *pl, int chunk, FwdTables &it, size_t *part
                     w.v1 = (int)v1;
                     w.kbase = kk * 64;
                     w.dbase = dd * cols;
-                    (cf ? (tall ? it.tall[tall_class(s.k)] : it.x3) : it.general).push_back(w);
+                    (cf ? (tall ? it.tall[tall_class(s.k)] : it.small) : it.general).push_back(w);
                 }
         }
         RedItem r;
@@ -303,8 +298,8 @@ void build_fwd_items(const fmap_plan *pl, int chunk, FwdTables &it, size_t *part
     // balances the tails
     auto longer = [](const FwdItem &a, const FwdItem &b) { return a.v1 - a.v0 > b.v1 - b.v0; };
     std::stable_sort(it.general.begin(), it.general.end(), longer);
-    std::stable_sort(it.x3.begin(), it.x3.end(), longer);
-    deal_to_xcds(it.x3);
+    std::stable_sort(it.small.begin(), it.small.end(), longer);
+    deal_to_xcds(it.small);
     for (auto &t : it.tall) {
         std::stable_sort(t.begin(), t.end(), longer);
         deal_to_xcds(t);
@@ -387,7 +382,7 @@ void build_bwd_items(fmap_plan *pl, int rb, std::vector<BwdItem> &bi, std::vecto
 // The forward projection items of all shapes, then the fixed-order chunk sums.
 hipError_t launch_projections_fwd(fmap_plan *pl, int grid, hipStream_t st)
 {
-    hipError_t e = launch_fwd_x3r_items(pl->d_x3, pl->nx3, st);
+    hipError_t e = launch_fwd_short_items(pl->d_small, pl->nsmall, st);
     for (int c = 0; c < kTallClasses && e == hipSuccess; ++c)
         e = launch_fwd_tall_items(pl->d_tall[c], pl->ntall[c], c, st);
     if (e == hipSuccess && pl->nfwd > 0) e = launch_fwd_items(pl->d_fwd, pl->nfwd, (int)pl->kmax, grid, st);
@@ -686,10 +681,10 @@ fmap_status fmap_plan_create(const fmap_pair *pairs, int32_t npairs, int64_t d, 
         size_t pf = 0;
         build_fwd_items(pl, chunk, it, &pf);
         pl->nfwd = (int)it.general.size();
-        pl->nx3 = (int)it.x3.size();
+        pl->nsmall = (int)it.small.size();
         pl->nred = (int)it.red.size();
         hipError_t e = upload(pl, &pl->d_fwd, it.general, st);
-        if (e == hipSuccess) e = upload(pl, &pl->d_x3, it.x3, st);
+        if (e == hipSuccess) e = upload(pl, &pl->d_small, it.small, st);
         for (int c = 0; c < kTallClasses && e == hipSuccess; ++c) {
             pl->ntall[c] = (int)it.tall[c].size();
             e = upload(pl, &pl->d_tall[c], it.tall[c], st);
@@ -722,6 +717,7 @@ fmap_status fmap_plan_create(const fmap_pair *pairs, int32_t npairs, int64_t d, 
                     bc = c;
                     bg = g;
                 }
+                if (pl->nfwd == 0) break;  // the grid is the general kernel's
             }
         }
         pl->chunk = bc;

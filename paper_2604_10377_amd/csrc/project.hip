@@ -22,109 +22,9 @@
 #include "fmap_device.h"
 #include "fmap_launch.h"
 #include "fmap_lds.h"
+#include "proj_general.h"
 
 namespace fmap {
-
-template <typename T>
-__device__ __forceinline__ float load_elem(const T *p, size_t i);
-template <>
-__device__ __forceinline__ float load_elem<float>(const float *p, size_t i) { return p[i]; }
-template <>
-__device__ __forceinline__ float load_elem<uint16_t>(const uint16_t *p, size_t i) { return bf16_to_f32(p[i]); }
-
-// One (shape, vertex range, k-block, column block) of the forward projection:
-// partial A rows [kbase, kbase + MT*32) x columns [dbase4 + wave*NT*32, ...)
-// over vertices [v0, v1), written to O (row-major k x d).
-template <typename T, int MT, int NT, int U>
-__device__ __forceinline__ void proj_fwd_tile(const T *__restrict__ P, const float *__restrict__ Mv,
-                                              const T *__restrict__ F, int k, int d, int v0, int v1, int kbase,
-                                              int dbase4, float *__restrict__ O)
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int half = lane >> 5, l32 = lane & 31;
-    const int dbase = dbase4 + wave * (NT * 32);
-    if (dbase >= d) return;  // whole wave idle (narrow d)
-
-    int rows[MT], cols[NT];
-    bool rok[MT], cok[NT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        rows[mt] = kbase + mt * 32 + l32;
-        rok[mt] = rows[mt] < k;
-    }
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-        cols[nt] = dbase + nt * 32 + l32;
-        cok[nt] = cols[nt] < d;
-    }
-
-    f32x16 acc[MT][NT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = zero16();
-
-    // Two register stages of U matrix-core steps (2U vertices): the loads of one
-    // stage are in flight while the other stage's multiplies run.
-    float pa0[U][MT], pb0[U][NT], m0[U], pa1[U][MT], pb1[U][NT], m1[U];
-    auto load = [&](float (&pa)[U][MT], float (&pb)[U][NT], float (&mv)[U], int v) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const unsigned vv = (unsigned)(v + 2 * u + half);
-            mv[u] = Mv[vv];
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) pa[u][mt] = rok[mt] ? load_elem(P, vv * (unsigned)k + rows[mt]) : 0.f;
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) pb[u][nt] = cok[nt] ? load_elem(F, vv * (unsigned)d + cols[nt]) : 0.f;
-        }
-    };
-    auto mma = [&](float (&pa)[U][MT], float (&pb)[U][NT], float (&mv)[U]) {
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const float a = pa[u][mt] * mv[u];
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = mfma32x32x2(a, pb[u][nt], acc[mt][nt]);
-            }
-    };
-    const int S = 2 * U;
-    const int nst = (v1 - v0) / S;
-    int v = v0;
-    if (nst > 0) load(pa0, pb0, m0, v);
-    for (int st = 0; st < nst; st += 2) {
-        if (st + 1 < nst) load(pa1, pb1, m1, v + S);
-        mma(pa0, pb0, m0);
-        if (st + 2 < nst) load(pa0, pb0, m0, v + 2 * S);
-        if (st + 1 < nst) mma(pa1, pb1, m1);
-        v += 2 * S;
-    }
-    // Tail: guarded single steps.
-    for (v = v0 + nst * S; v < v1; v += 2) {
-        const int vv = v + half;
-        const bool ok = vv < v1;
-        const float m = ok ? Mv[vv] : 0.f;
-        float a[MT], b[NT];
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) a[mt] = (ok && rok[mt]) ? load_elem(P, (size_t)vv * k + rows[mt]) * m : 0.f;
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) b[nt] = (ok && cok[nt]) ? load_elem(F, (size_t)vv * d + cols[nt]) : 0.f;
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = mfma32x32x2(a[mt], b[nt], acc[mt][nt]);
-    }
-
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int row = kbase + mt * 32 + acc32_row(r, lane);
-                if (row < k && cok[nt]) O[(size_t)row * d + cols[nt]] = acc[mt][nt][r];
-            }
-}
 
 template <typename T, int MT, int NT, int U>
 __global__ __launch_bounds__(256) void proj_fwd_kernel(const T *__restrict__ phi, const float *__restrict__ mass,
@@ -155,200 +55,6 @@ __global__ __launch_bounds__(256) void proj_fwd_items_kernel(const FwdItem *__re
         const FwdItem w = items[it];
         proj_fwd_tile<float, MT, NT, U>(global_ptr(w.phi), global_ptr(w.mass), global_ptr(w.feat), w.k, w.d, w.v0, w.v1,
                                         w.kbase, w.dbase, global_ptr(w.out));
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Forward, LDS-pipelined variant (float32, k <= 64, one 256-column block of d
-// per workgroup).  Vertices are consumed in stages of FS = 32: the feature rows
-// (1 KB each), the contiguous basis tile and the masses of a stage arrive by
-// direct global->LDS loads (global_load_lds_dwordx4) into a ring of FNST stage
-// buffers, two stages ahead of the multiplies, so ~80 KB per CU are in flight
-// without occupying registers and the basis is read once per workgroup.
-// Every wave issues exactly FL loads per stage (addresses clamped into the
-// valid range, never exec-masked), which makes the vmcnt accounting exact.
-//
-// 8 waves: wave = (column group cg of 64 columns) x (vertex parity vg).  A
-// wave runs the 16x16x4 float32 matrix cores on MT16 row tiles of 16 and
-// NT16 = 4 column tiles; REM (<= 4) trailing rows of k are accumulated with
-// plain FMAs instead of padding a whole 16-row tile (k = 50 = 3*16 + 2).
-// The two parity groups are summed through LDS at the end.
-// ---------------------------------------------------------------------------
-constexpr int FS = 32;            // vertices per stage
-constexpr int FNST = 3;           // stage buffers in the ring
-constexpr int FLDF = 256 + 16;    // LDS row stride of the feature tile (floats)
-constexpr int FL = 6;             // direct loads per wave per stage
-constexpr int F_TILE = FS * FLDF;             // floats
-constexpr int P_TILE = 8 * 256;               // basis tile: up to 8 KB (k <= 64)
-constexpr int M_TILE = 256;                   // masses: one 1 KB load window
-constexpr int STAGE_FLOATS = F_TILE + P_TILE + M_TILE;
-constexpr size_t FWD_LDS_BYTES = (size_t)FNST * STAGE_FLOATS * sizeof(float);
-
-__device__ __forceinline__ f32x4 mfma16x16x4(float a, float b, f32x4 c)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
-template <int MT16, int REM>
-__global__ __launch_bounds__(512) void proj_fwd_lds_kernel(const float *__restrict__ phi,
-                                                           const float *__restrict__ mass,
-                                                           const float *__restrict__ feat, int n, int k, int d,
-                                                           int nsplit, int dblocks, float *__restrict__ out)
-{
-    extern __shared__ __align__(16) float smem[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int cg = wave & 3, vg = wave >> 2;
-    const int r16 = lane & 15, g4 = lane >> 4;
-    int bid = blockIdx.x;
-    const int db = bid % dblocks;
-    bid /= dblocks;
-    const int split = bid % nsplit;
-    const int s = bid / nsplit;
-    const int dbase = db * 256;
-
-    // balanced split of the stages of this shape
-    const int nst_all = (n + FS - 1) / FS;
-    const int st0 = (int)(((long)split * nst_all) / nsplit), st1 = (int)(((long)(split + 1) * nst_all) / nsplit);
-    const int vbeg = st0 * FS, vend = min(n, st1 * FS);
-    const int nst = st1 - st0;
-
-    const float *P = phi + (size_t)s * n * k;
-    const float *F = feat + (size_t)s * n * d;
-    const float *Mv = mass + (size_t)s * n;
-
-    // zero the ring once so that slots never hold non-finite garbage
-    for (int e = tid * 4; e < FNST * STAGE_FLOATS; e += 512 * 4) *reinterpret_cast<f32x4 *>(&smem[e]) = f32x4{0, 0, 0, 0};
-    __syncthreads();
-
-    const int np = (k + 7) / 8;  // 1 KB basis windows per stage (32 rows x k floats)
-    // Load list of a stage: 32 feature rows, np basis windows, then mass windows up to 8*FL.
-    auto issue = [&](int t) {
-        float *S = smem + (t % FNST) * STAGE_FLOATS;
-        const int v = vbeg + t * FS;
-        const int rows = min(FS, vend - v);
-        const int pvalid = rows * k;  // floats of the basis tile that exist
-#pragma unroll
-        for (int q = 0; q < FL; ++q) {
-            const int item = q * 8 + wave;
-            if (item < FS) {
-                const int r = min(item, rows - 1);
-                const int col = min(dbase + 4 * lane, d - 4);
-                dma16(F + (size_t)(v + r) * d + col, S + item * FLDF);
-            } else if (item < FS + np) {
-                const int wdw = item - FS;
-                const int off = min(wdw * 256 + 4 * lane, ((pvalid + 3) & ~3) - 4);
-                dma16(P + (size_t)v * k + off, S + F_TILE + wdw * 256);
-            } else {
-                const int off = min(4 * lane, ((rows + 3) & ~3) - 4);
-                dma16(Mv + v + off, S + F_TILE + P_TILE);
-            }
-        }
-    };
-
-    f32x4 acc[MT16][4];
-#pragma unroll
-    for (int mt = 0; mt < MT16; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) acc[mt][nt] = f32x4{0, 0, 0, 0};
-    float rem[REM > 0 ? REM : 1][4];
-#pragma unroll
-    for (int e = 0; e < (REM > 0 ? REM : 1); ++e)
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) rem[e][nt] = 0.f;
-
-    for (int t = 0; t < FNST - 1 && t < nst; ++t) issue(t);
-    for (int t = 0; t < nst; ++t) {
-        if (t + FNST - 1 < nst) issue(t + FNST - 1);
-        // loads issued after stage t's: those of the next FNST-1 stages that exist
-        if (t + 2 < nst) wait_vmcnt<2 * FL>();
-        else if (t + 1 < nst) wait_vmcnt<FL>();
-        else wait_vmcnt<0>();
-        lds_barrier();
-        const float *S = smem + (t % FNST) * STAGE_FLOATS;
-        const float *Fs = S, *Ps = S + F_TILE, *Ms = S + F_TILE + P_TILE;
-        const int vs = vbeg + t * FS;
-#pragma unroll
-        for (int qq = 0; qq < FS / 8; ++qq) {
-            const int vloc = 4 * (2 * qq + vg) + g4;
-            const float m = (vs + vloc < vend) ? Ms[vloc] : 0.f;
-            float a[MT16], b[4];
-#pragma unroll
-            for (int mt = 0; mt < MT16; ++mt) {
-                const int row = 16 * mt + r16;
-                a[mt] = (REM > 0 || mt < MT16 - 1 || row < k) ? Ps[vloc * k + row] * m : 0.f;
-            }
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) b[nt] = Fs[vloc * FLDF + cg * 64 + 16 * nt + r16];
-#pragma unroll
-            for (int mt = 0; mt < MT16; ++mt)
-#pragma unroll
-                for (int nt = 0; nt < 4; ++nt) acc[mt][nt] = mfma16x16x4(a[mt], b[nt], acc[mt][nt]);
-            if (REM > 0) {
-#pragma unroll
-                for (int e = 0; e < REM; ++e) {
-                    const float wv = Ps[vloc * k + 16 * MT16 + e] * m;
-#pragma unroll
-                    for (int nt = 0; nt < 4; ++nt) rem[e][nt] += wv * b[nt];
-                }
-            }
-        }
-        lds_barrier();  // the slot is refilled by the next iteration's issue
-    }
-
-    // remainder rows: sum the four vertex lane groups
-    if (REM > 0) {
-#pragma unroll
-        for (int e = 0; e < REM; ++e)
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) {
-                float v = rem[e][nt];
-                v += __shfl_xor(v, 16, 64);
-                v += __shfl_xor(v, 32, 64);
-                rem[e][nt] = v;
-            }
-    }
-    // parity group 1 hands its sums to group 0 through LDS
-    constexpr int PER_LANE = MT16 * 16 + (REM > 0 ? REM : 1) * 4;
-    float *X = smem + (size_t)(cg * 64 + lane) * PER_LANE;
-    if (vg == 1) {
-#pragma unroll
-        for (int mt = 0; mt < MT16; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) X[(mt * 4 + nt) * 4 + r] = acc[mt][nt][r];
-        if (REM > 0) {
-#pragma unroll
-            for (int e = 0; e < REM; ++e)
-#pragma unroll
-                for (int nt = 0; nt < 4; ++nt) X[MT16 * 16 + e * 4 + nt] = rem[e][nt];
-        }
-    }
-    __syncthreads();
-    if (vg == 0) {
-        float *O = out + ((size_t)s * nsplit + split) * (size_t)k * d;
-#pragma unroll
-        for (int mt = 0; mt < MT16; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) {
-                const int col = dbase + cg * 64 + 16 * nt + r16;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int row = 16 * mt + 4 * g4 + r;
-                    const float v = acc[mt][nt][r] + X[(mt * 4 + nt) * 4 + r];
-                    if (row < k && col < d) O[(size_t)row * d + col] = v;
-                }
-            }
-        if (REM > 0 && g4 == 0) {
-#pragma unroll
-            for (int e = 0; e < REM; ++e)
-#pragma unroll
-                for (int nt = 0; nt < 4; ++nt) {
-                    const int col = dbase + cg * 64 + 16 * nt + r16;
-                    const int row = 16 * MT16 + e;
-                    if (col < d) O[(size_t)row * d + col] = rem[e][nt] + X[MT16 * 16 + e * 4 + nt];
-                }
-        }
     }
 }
 
@@ -655,17 +361,6 @@ static int device_cu_count()
     return cus[dev];
 }
 
-// Chunks of the LDS-pipelined forward: about one workgroup per CU overall.
-static int lds_fwd_nsplit(int64_t batch, int64_t n, int64_t d)
-{
-    const int64_t dblocks = (d + 255) / 256;
-    const int64_t stages = (n + FS - 1) / FS;
-    int64_t ns = (device_cu_count() + batch * dblocks - 1) / (batch * dblocks);
-    if (ns > stages / 4) ns = stages / 4;  // keep >= 4 stages per chunk
-    if (ns < 1) ns = 1;
-    return (int)ns;
-}
-
 ProjPlan plan_project(int64_t batch, int64_t n, int64_t k, int64_t d, int32_t dtype)
 {
     ProjPlan p;
@@ -689,80 +384,47 @@ ProjPlan plan_project(int64_t batch, int64_t n, int64_t k, int64_t d, int32_t dt
     return p;
 }
 
-static bool lds_fwd_shape_ok(int64_t n, int64_t k, int64_t d, int32_t dtype)
-{
-    return dtype == 0 && k <= 64 && n % 4 == 0 && d % 4 == 0 && (n * k) % 4 == 0 && n >= 4 * FS;
-}
-
 static bool aligned16(const void *p) { return ((uintptr_t)p & 15) == 0; }
 
-// The chunk budget that workspaces are sized for: the chunks of the general, LDS, bf16 and emulated kernels and,
-// for k > 64, two workgroups per CU over 64-row slices and 256-column blocks (the tall kernel needs no more).  The
-// sizes it gives decide which calls the built-in scratch array takes, so they stay as they are.
-static int64_t other_nsplit(int64_t batch, int64_t n, int64_t k, int64_t d, int32_t dtype)
+// The chunk budget that workspaces are sized for: the chunks of the general and bf16 kernels and, for d % 4 == 0 and
+// n % 4 == 0, two workgroups per CU over 64-row slices and 256-column blocks (one for odd k <= 64).  The sizes it gives
+// decide which calls the built-in scratch array takes, so they stay as they are.
+static int64_t budget_nsplit(int64_t batch, int64_t n, int64_t k, int64_t d, int32_t dtype)
 {
     int64_t ns = plan_project(batch, n, k, d, dtype).nsplit;
-    if (lds_fwd_shape_ok(n, k, d, dtype)) ns = std::max<int64_t>(ns, lds_fwd_nsplit(batch, n, d));
     if (dtype == 1 && bf16_fwd_shape_ok(n, k, d)) ns = std::max<int64_t>(ns, bf16_fwd_nsplit(batch, n, k, d));
-    if (dtype == 0 && f32_split_fwd_shape_ok(n, k, d)) ns = std::max<int64_t>(ns, f32_split_fwd_nsplit(batch, n, k, d));
-    if (dtype == 0 && k > 64 && k <= kMaxK && k % 4 == 0 && d % 4 == 0 && n % 4 == 0 && n >= 128) {
-        const int64_t blocks = (d + 255) / 256 * ((k + 63) / 64), quarter = (n + 31) / 32 / 4;
-        ns = std::max<int64_t>(ns, std::min<int64_t>(2 * device_cu_count() / (batch * blocks), quarter));
+    if (dtype == 0 && k <= kMaxK && d % 4 == 0 && n % 4 == 0 && n >= 128) {
+        const int64_t blocks = batch * ((d + 255) / 256), quarter = (n + 31) / 32 / 4, cus = device_cu_count();
+        if (k <= 64) ns = std::max(ns, std::min((cus + blocks - 1) / blocks, quarter));
+        if (k > 64 ? k % 4 == 0 : k >= 4 && k % 2 == 0)
+            ns = std::max(ns, std::min(2 * cus / (blocks * ((k + 63) / 64)), quarter));
     }
     return ns;
 }
 
-// Chunks of the tall kernel: within that budget, or more while the partial sums fit the built-in scratch array (a
-// few shapes of any n then still spread over the chip, and no call outgrows the array).
-static int tall_chunks(int64_t batch, int64_t n, int64_t k, int64_t d)
+// Chunks of the split kernels: within that budget, or more while the partial sums fit the built-in scratch array (a few
+// shapes of any n then still spread over the chip, and no call outgrows the array).
+static int64_t split_cap(int64_t batch, int64_t n, int64_t k, int64_t d)
 {
     const int64_t fit = (int64_t)(32u << 20) / (batch * k * d * (int64_t)sizeof(float));
-    return tall_nsplit(batch, n, k, d, std::max(fit, other_nsplit(batch, n, k, d, 0)));
+    return std::max(fit, budget_nsplit(batch, n, k, d, 0));
+}
+static int tall_chunks(int64_t batch, int64_t n, int64_t k, int64_t d)
+{
+    return tall_nsplit(batch, n, k, d, split_cap(batch, n, k, d));
+}
+static int short_chunks(int64_t batch, int64_t n, int64_t k, int64_t d)
+{
+    return (int)std::min<int64_t>(short_nsplit(batch, n, k, d), split_cap(batch, n, k, d));
 }
 
 size_t project_workspace_bytes(int64_t batch, int64_t n, int64_t k, int64_t d, int32_t dtype)
 {
-    int64_t ns = other_nsplit(batch, n, k, d, dtype);
+    int64_t ns = budget_nsplit(batch, n, k, d, dtype);
     if (dtype == 0 && tall_shape_ok(n, k, d)) ns = std::max<int64_t>(ns, tall_chunks(batch, n, k, d));
+    if (dtype == 0 && short_shape_ok(n, k, d)) ns = std::max<int64_t>(ns, short_chunks(batch, n, k, d));
     if (ns <= 1) return 0;
     return (size_t)batch * ns * k * d * sizeof(float);
-}
-
-template <int MT16, int REM>
-static void launch_fwd_lds(const float *phi, const float *mass, const float *feat, int64_t batch, int64_t n,
-                           int64_t k, int64_t d, int nsplit, float *out, hipStream_t st)
-{
-    static bool attr_set = false;
-    if (!attr_set) {
-        (void)hipFuncSetAttribute((const void *)proj_fwd_lds_kernel<MT16, REM>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)FWD_LDS_BYTES);
-        attr_set = true;
-    }
-    const int dblocks = (int)((d + 255) / 256);
-    const unsigned grid = (unsigned)(batch * nsplit * dblocks);
-    hipLaunchKernelGGL((proj_fwd_lds_kernel<MT16, REM>), dim3(grid), dim3(512), FWD_LDS_BYTES, st, phi, mass, feat,
-                       (int)n, (int)k, (int)d, nsplit, dblocks, out);
-}
-
-static void dispatch_fwd_lds(const float *phi, const float *mass, const float *feat, int64_t batch, int64_t n,
-                             int64_t k, int64_t d, int nsplit, float *out, hipStream_t st)
-{
-    const int r = (int)(k % 16);
-    if (k > 16 && r >= 1 && r <= 4) {
-        const int mt = (int)(k / 16);
-#define FMAP_FL(M, R) \
-    if (mt == M && r == R) return launch_fwd_lds<M, R>(phi, mass, feat, batch, n, k, d, nsplit, out, st)
-        FMAP_FL(1, 1); FMAP_FL(1, 2); FMAP_FL(1, 3); FMAP_FL(1, 4);
-        FMAP_FL(2, 1); FMAP_FL(2, 2); FMAP_FL(2, 3); FMAP_FL(2, 4);
-        FMAP_FL(3, 1); FMAP_FL(3, 2); FMAP_FL(3, 3); FMAP_FL(3, 4);
-#undef FMAP_FL
-    }
-    switch ((k + 15) / 16) {
-    case 1: return launch_fwd_lds<1, 0>(phi, mass, feat, batch, n, k, d, nsplit, out, st);
-    case 2: return launch_fwd_lds<2, 0>(phi, mass, feat, batch, n, k, d, nsplit, out, st);
-    case 3: return launch_fwd_lds<3, 0>(phi, mass, feat, batch, n, k, d, nsplit, out, st);
-    default: return launch_fwd_lds<4, 0>(phi, mass, feat, batch, n, k, d, nsplit, out, st);
-    }
 }
 
 template <typename T, int MT, int NT>
@@ -871,16 +533,9 @@ hipError_t launch_project(const void *phi, const float *mass, const void *feat, 
     if (dtype == 0 && tall_shape_ok(n, k, d) && aligned16(feat) && aligned16(A) && aligned16(ws))
         return launch_project_tall((const float *)phi, mass, (const float *)feat, batch, n, k, d,
                                    tall_chunks(batch, n, k, d), A, ws, st);
-    if (dtype == 0 && f32_split_fwd_shape_ok(n, k, d) && aligned16(phi) && aligned16(mass) && aligned16(feat))
-        return launch_project_f32_split((const float *)phi, mass, (const float *)feat, batch, n, k, d, A, ws, st);
-    if (lds_fwd_shape_ok(n, k, d, dtype) && aligned16(phi) && aligned16(mass) && aligned16(feat)) {
-        const int ns = lds_fwd_nsplit(batch, n, d);
-        float *out = ns > 1 ? (float *)ws : A;
-        dispatch_fwd_lds((const float *)phi, mass, (const float *)feat, batch, n, k, d, ns, out, st);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess || ns <= 1) return e;
-        return launch_reduce((const float *)ws, ns, batch, k, d, A, st);
-    }
+    if (dtype == 0 && short_shape_ok(n, k, d) && aligned16(feat) && aligned16(A) && aligned16(ws))
+        return launch_project_short((const float *)phi, mass, (const float *)feat, batch, n, k, d,
+                                    short_chunks(batch, n, k, d), A, ws, st);
     if (dtype == 1 && bf16_fwd_shape_ok(n, k, d) && aligned16(phi) && aligned16(mass) && aligned16(feat))
         return launch_project_bf16((const uint16_t *)phi, mass, (const uint16_t *)feat, batch, n, k, d, A, ws, st);
     ProjPlan p = plan_project(batch, n, k, d, dtype);

@@ -23,7 +23,7 @@ struct BwdItem {                  // dF rows [r0, r0 + 128*rb) x columns [dbase,
     float *dF;
     int n, k, d, r0, rb, dbase;
 };
-struct McItem {                   // dF tiles [t0, t1) of 256 vertices x columns [dbase, dbase + block)
+struct McItem {                   // dF tiles [t0, t1) of back_verts vertices x columns [dbase, dbase + back_cols)
     const float *phi, *mass, *dA;
     float *dF;
     int n, k, d, t0, t1, dbase;
@@ -37,11 +37,16 @@ struct RedItem {                  // A = sum of `nchunks` partial k x d slots
 hipError_t launch_fwd_items(const FwdItem *items, int nitems, int kmax, int grid, hipStream_t st);
 hipError_t launch_bwd_items(const BwdItem *items, int nitems, int kmax, int grid, hipStream_t st);
 hipError_t launch_reduce_items(const RedItem *items, int nitems, hipStream_t st);
-// Uneven batches on the emulated float32 kernels, one workgroup per item.
-// Backward items of one k (k even, <= kMaxK): mc_item_cols(k) columns per item.
-bool mc_item_shape_ok(int64_t k);
-int mc_item_cols(int64_t k);
-hipError_t launch_bwd_mc_items(const McItem *items, int nitems, int64_t k, hipStream_t st);
+// float32 backward projection for 4 <= k <= kMaxK on the float16 matrix cores, operands split into two parts (any n and
+// d, any alignment), and its work-item form for one k: back_cols columns per item, tiles of back_verts vertices,
+// back_slots resident workgroups.
+bool back_shape_ok(int64_t k, int64_t d);
+int back_cols(int64_t k, int64_t d);
+int back_verts(int64_t k, int64_t d);
+int back_slots(int64_t k);
+hipError_t launch_project_back(const float *phi, const float *mass, const float *dA, int64_t batch, int64_t n, int64_t k,
+                               int64_t d, float *dF, hipStream_t st);
+hipError_t launch_bwd_split_items(const McItem *items, int nitems, int64_t k, int64_t d, hipStream_t st);
 // Fixed-order sum of split-K partials [batch][nsplit][k][d] into A [batch][k][d].
 hipError_t launch_reduce(const float *part, int nsplit, int64_t batch, int64_t k, int64_t d, float *A, hipStream_t st);
 // bf16 forward projection on the bf16 matrix cores (k % 8 == 0, k <= 256, d % 8 == 0, n % 4 == 0).
@@ -51,7 +56,15 @@ int bf16_fwd_nsplit(int64_t batch, int64_t n, int64_t k, int64_t d);
 bool bf16_bwd_shape_ok(int64_t n, int64_t k, int64_t d);
 hipError_t launch_project_backward_bf16(const uint16_t *phi, const float *mass, const float *dA, int64_t batch,
                                         int64_t n, int64_t k, int64_t d, float *dF, hipStream_t st);
-// float32 forward projection for 64 < k <= kMaxK on the float16 matrix cores, operands split into two parts
+// float32 forward projection for 64 < k <= kMaxK with d < 5 k / 4, operands split into three bf16 parts (k % 4 == 0,
+// d % 4 == 0, n % 4 == 0; items of whole 32-vertex stages): the shapes whose results hang on the last bits of A.
+bool near_square(int64_t k, int64_t d);
+bool sliced_fwd_shape_ok(int64_t n, int64_t k, int64_t d);
+hipError_t launch_project_sliced(const float *phi, const float *mass, const float *feat, int64_t batch, int64_t n,
+                                 int64_t k, int64_t d, float *A, void *ws, hipStream_t st);
+bool sliced_item_shape_ok(int64_t k, int64_t d);
+hipError_t launch_fwd_sliced_items(const FwdItem *items, int nitems, hipStream_t st);
+// float32 forward projection for 64 < k <= kMaxK and d >= 5 k / 4 on the float16 matrix cores, operands split into two parts
 // (d % 4 == 0, 16-byte aligned features, any n and k).
 bool tall_shape_ok(int64_t n, int64_t k, int64_t d);
 // Chunks of the vertex sum, at most `cap`.
@@ -64,19 +77,11 @@ int short_nsplit(int64_t batch, int64_t n, int64_t k, int64_t d);
 hipError_t launch_project_short(const float *phi, const float *mass, const float *feat, int64_t batch, int64_t n,
                                 int64_t k, int64_t d, int ns, float *A, void *ws, hipStream_t st);
 hipError_t launch_fwd_short_items(const FwdItem *items, int nitems, hipStream_t st);
-// The tall kernel's work-item form: instances by class of k, tall_cols(k) columns per item.
-constexpr int kTallClasses = 4;
-int tall_class(int64_t k);
-int tall_cols(int64_t k);
+// The tall kernel's work-item form: instances by class of (k, d), tall_cols(k, d) columns per item.
+constexpr int kTallClasses = 5;
+int tall_class(int64_t k, int64_t d);
+int tall_cols(int64_t k, int64_t d);
 hipError_t launch_fwd_tall_items(const FwdItem *items, int nitems, int cls, hipStream_t st);
-// float32 backward projection on the bf16 matrix cores, operands split into three bf16 parts (k even, k <= 64).
-bool f32_split_bwd_shape_ok(int64_t n, int64_t k, int64_t d);
-// float32 backward for 64 < k <= kMaxK (k even), 64-column blocks with every k slot's dA^T parts in LDS
-bool f32k_bwd_shape_ok(int64_t n, int64_t k, int64_t d);
-hipError_t launch_project_backward_f32k(const float *phi, const float *mass, const float *dA, int64_t batch,
-                                        int64_t n, int64_t k, int64_t d, float *dF, hipStream_t st);
-hipError_t launch_project_backward_f32_split(const float *phi, const float *mass, const float *dA, int64_t batch,
-                                             int64_t n, int64_t k, int64_t d, float *dF, hipStream_t st);
 hipError_t launch_project_bf16(const uint16_t *phi, const float *mass, const uint16_t *feat, int64_t batch, int64_t n,
                                int64_t k, int64_t d, float *A, void *ws, hipStream_t st);
 int device_cus();

@@ -6,12 +6,13 @@
 //   - forward projection items: (shape, vertex chunk, 64-row k block, 256-column
 //     d block).  With d % 4 == 0 and 16-byte aligned features, shapes of k <= 64 run
 //     on the short split kernel and those of k > 64 on the tall one (one launch per
-//     class of k), one workgroup per item; all other shapes are items of ONE
-//     persistent launch of the general kernel;
+//     class of k; d close to k: whole 32-vertex stages on the sliced one), one
+//     workgroup per item; the rest are items of ONE persistent launch of the general
+//     kernel;
 //   - reduction items: the fixed-order sum of each shape's chunk partials;
-//   - backward projection items: (shape, 256-vertex tiles, column block) on the
-//     emulated kernels, one launch per k group; (shape, rows, d block) items of
-//     one persistent launch of the general kernel for the rest;
+//   - backward projection items: (shape, vertex tiles, column block) on the split
+//     kernel, one launch per k group; (shape, rows, d block) items of one
+//     persistent launch of the general kernel for the rest;
 //   - copy items: gather eigenvalues / lambda / dC into the group buffers and
 //     scatter C / info back to the pairs.
 // It then autotunes (vertices per item, persistent grid size, row systems per
@@ -66,7 +67,7 @@ struct Bucket {
     int64_t k = 0;
     std::vector<int> pairs;
     int waves = 4;             // row systems per workgroup of the register row solve (k <= kSmallK)
-    int mc_off = 0, mc_n = 0;  // this group's backward items in the emulated-kernel table
+    int mc_off = 0, mc_n = 0;  // this group's backward items in the split-kernel table
     float *AB = nullptr, *dAB = nullptr, *C = nullptr, *factors = nullptr, *evx = nullptr, *evy = nullptr,
           *lam = nullptr, *dC = nullptr;
     int32_t *info = nullptr;
@@ -83,12 +84,12 @@ struct fmap_plan {
     std::vector<Bucket> buckets;
     std::vector<void *> allocs;
     float *partials = nullptr;
-    FwdItem *d_fwd = nullptr, *d_small = nullptr, *d_tall[kTallClasses] = {};
-    int nfwd = 0, nsmall = 0, ntall[kTallClasses] = {};
+    FwdItem *d_fwd = nullptr, *d_small = nullptr, *d_sliced = nullptr, *d_tall[kTallClasses] = {};
+    int nfwd = 0, nsmall = 0, nsliced = 0, ntall[kTallClasses] = {};
     McItem *d_mc = nullptr;
     int nmc = 0;
-    RedItem *d_red = nullptr;
-    int nred = 0;
+    RedItem *d_red[2] = {};  // chunk sums of the shapes with k <= kSmallK / k > kSmallK
+    int nred[2] = {};
     BwdItem *d_bwd = nullptr;
     int nbwd = 0;
     CopyItem *d_gf = nullptr, *d_sf = nullptr, *d_gb = nullptr;
@@ -97,7 +98,7 @@ struct fmap_plan {
     hipStream_t cap = nullptr;
     // k groups solve on up to kLanes graph branches: lane 0 is the capturing stream, lanes 1.. these streams
     std::vector<hipStream_t> side;
-    hipEvent_t fork = nullptr;
+    hipEvent_t fork = nullptr, fork2 = nullptr;
     std::vector<hipEvent_t> join;
     hipGraph_t gf = nullptr, gb = nullptr;
     hipGraphExec_t ef = nullptr, eb = nullptr;
@@ -146,22 +147,17 @@ bool aligned(const void *p, uintptr_t a) { return ((uintptr_t)p & (a - 1)) == 0;
 // the forward of this shape runs on the split kernel of k <= 64
 bool short_shape(const Shape &s, int64_t d) { return s.k <= kSmallK && d >= 4 && d % 4 == 0 && aligned(s.feat, 16); }
 
+// the forward of this shape runs its whole stages on the sliced kernel (k > 64, d close to k)
+bool sliced_shape(const Shape &s, int64_t d)
+{
+    return sliced_item_shape_ok(s.k, d) && aligned(s.phi, 16) && aligned(s.feat, 16) && s.n >= 32;
+}
+
 // the forward of this shape runs on the tall kernel (k > 64)
 bool tall_shape(const Shape &s, int64_t d) { return tall_shape_ok(s.n, s.k, d) && aligned(s.feat, 16); }
 
-// the backward of every shape of this group runs on the emulated float32 kernels
-bool mc_bucket(const fmap_plan *pl, int b)
-{
-    const Bucket &B = pl->buckets[b];
-    if (!mc_item_shape_ok(B.k)) return false;
-    for (int q : B.pairs) {
-        const fmap_pair &p = pl->pairs[q];
-        if (!aligned(p.phi_x, 8) || !aligned(p.phi_y, 8) ||
-            (pl->d % 4 == 0 && (!aligned(p.dF_x, 16) || !aligned(p.dF_y, 16))))
-            return false;
-    }
-    return true;
-}
+// the backward of this group runs on the split kernel
+bool mc_bucket(const fmap_plan *pl, int b) { return back_shape_ok(pl->buckets[b].k, pl->d); }
 
 std::vector<Shape> shapes_of(const fmap_plan *pl)
 {
@@ -178,7 +174,7 @@ std::vector<Shape> shapes_of(const fmap_plan *pl)
     return sh;
 }
 
-// One workgroup per item, workgroup ids dealt round-robin to the 8 XCDs: reorder an emulated-kernel
+// One workgroup per item, workgroup ids dealt round-robin to the 8 XCDs: reorder a split-kernel
 // item list so that the items of one vertex chunk (its k and d blocks, which read the same feature
 // rows) share an XCD and that XCD's L2.  Chunks, longest first, go to the least loaded XCD queue;
 // table slot r * 8 + x is item r of queue x, or an empty item (v0 == v1) that returns at once.
@@ -216,16 +212,16 @@ void tall_chunks(const fmap_plan *pl, const std::vector<Shape> &shapes, int (&ch
     for (int c = 0; c < kTallClasses; ++c) {
         int64_t work = 0, longest = 32;
         for (const Shape &s : shapes)
-            if (tall_shape(s, pl->d) && tall_class(s.k) == c) {
-                work += s.n * ((pl->d + tall_cols(s.k) - 1) / tall_cols(s.k));
+            if (tall_shape(s, pl->d) && tall_class(s.k, pl->d) == c) {
+                work += s.n * ((pl->d + tall_cols(s.k, pl->d) - 1) / tall_cols(s.k, pl->d));
                 longest = std::max(longest, s.n);
             }
         int64_t t = std::max<int64_t>(256, (work / device_cus() + 31) / 32 * 32);
         for (; t < longest; t += 32) {
             int64_t items = 0;
             for (const Shape &s : shapes)
-                if (tall_shape(s, pl->d) && tall_class(s.k) == c)
-                    items += (s.n + t - 1) / t * ((pl->d + tall_cols(s.k) - 1) / tall_cols(s.k));
+                if (tall_shape(s, pl->d) && tall_class(s.k, pl->d) == c)
+                    items += (s.n + t - 1) / t * ((pl->d + tall_cols(s.k, pl->d) - 1) / tall_cols(s.k, pl->d));
             if (items <= device_cus()) break;
         }
         chunk[c] = (int)t;
@@ -233,11 +229,12 @@ void tall_chunks(const fmap_plan *pl, const std::vector<Shape> &shapes, int (&ch
 }
 
 // Forward and reduction items for a given chunk size (a multiple of 32); partial slots are laid out shape
-// after shape.  it.small: split-kernel items of k <= 64, it.tall: tall-kernel items (k > 64) by class of k,
+// after shape.  it.small: split-kernel items of k <= 64; it.tall: tall-kernel items (k > 64) by class of k; it.sliced:
+// sliced-kernel items (d close to k);
 // it.general: general-kernel items.
 struct FwdTables {
-    std::vector<FwdItem> general, small, tall[kTallClasses];
-    std::vector<RedItem> red;
+    std::vector<FwdItem> general, small, sliced, tall[kTallClasses];
+    std::vector<RedItem> red[2];
 };
 
 void build_fwd_items(const fmap_plan *pl, int chunk, FwdTables &it, size_t *partial_floats)
@@ -251,12 +248,14 @@ void build_fwd_items(const fmap_plan *pl, int chunk, FwdTables &it, size_t *part
     for (const Shape &s : shapes) {
         const Bucket &B = pl->buckets[s.bucket];
         const bool tall = tall_shape(s, d);
-        const int64_t nfast = tall || short_shape(s, d) ? s.n : 0;  // vertices on the split kernels: all or none
-        const int fchunk = tall ? tchunk[tall_class(s.k)] : chunk;
+        const bool sliced = sliced_shape(s, d);
+        // vertices on the split kernels: all (the sliced one: those in whole stages) or none
+        const int64_t nfast = tall || short_shape(s, d) ? s.n : (sliced ? s.n - s.n % 32 : 0);
+        const int fchunk = tall ? tchunk[tall_class(s.k, pl->d)] : chunk;
         const int nchf = (int)((nfast + fchunk - 1) / fchunk);
         const int nchg = (int)((s.n - nfast + chunk - 1) / chunk);
         const int nch = nchf + nchg;
-        const int cols = tall ? tall_cols(s.k) : 256;
+        const int cols = tall ? tall_cols(s.k, pl->d) : 256;
         const int kb = tall ? 1 : (int)((s.k + 63) / 64), db = (int)((d + cols - 1) / cols);
         float *part = pl->partials ? pl->partials + off : nullptr;
         for (int c = 0; c < nch; ++c) {
@@ -282,7 +281,7 @@ void build_fwd_items(const fmap_plan *pl, int chunk, FwdTables &it, size_t *part
                     w.v1 = (int)v1;
                     w.kbase = kk * 64;
                     w.dbase = dd * cols;
-                    (cf ? (tall ? it.tall[tall_class(s.k)] : it.small) : it.general).push_back(w);
+                    (!cf ? it.general : (tall ? it.tall[tall_class(s.k, pl->d)] : (sliced ? it.sliced : it.small))).push_back(w);
                 }
         }
         RedItem r;
@@ -291,7 +290,7 @@ void build_fwd_items(const fmap_plan *pl, int chunk, FwdTables &it, size_t *part
         r.A_user = s.A_user;
         r.nchunks = nch;
         r.kd = (int)(s.k * d);
-        it.red.push_back(r);
+        it.red[s.k > kSmallK].push_back(r);
         off += (size_t)nch * s.k * d;
     }
     // longest items first: the workgroup scheduler (or the persistent grid's static round-robin) then
@@ -300,6 +299,8 @@ void build_fwd_items(const fmap_plan *pl, int chunk, FwdTables &it, size_t *part
     std::stable_sort(it.general.begin(), it.general.end(), longer);
     std::stable_sort(it.small.begin(), it.small.end(), longer);
     deal_to_xcds(it.small);
+    std::stable_sort(it.sliced.begin(), it.sliced.end(), longer);
+    deal_to_xcds(it.sliced);
     for (auto &t : it.tall) {
         std::stable_sort(t.begin(), t.end(), longer);
         deal_to_xcds(t);
@@ -307,24 +308,39 @@ void build_fwd_items(const fmap_plan *pl, int chunk, FwdTables &it, size_t *part
     *partial_floats = off;
 }
 
-// Backward items: groups on the emulated kernels get McItems of 2 rb 256-vertex tiles (bucket by bucket,
-// with each bucket's offset and count recorded), the rest general-kernel items of 128 rb rows.
+// Backward items: groups on the split kernel get McItems (bucket by bucket, with each bucket's offset and count recorded), the rest general-kernel items of 128 rb rows.
 void build_bwd_items(fmap_plan *pl, int rb, std::vector<BwdItem> &bi, std::vector<McItem> &mi)
 {
     bi.clear();
     mi.clear();
     const int64_t d = pl->d;
+    const std::vector<Shape> shapes = shapes_of(pl);
     for (int b = 0; b < (int)pl->buckets.size(); ++b) {
         Bucket &B = pl->buckets[b];
         B.mc_off = (int)mi.size();
         B.mc_n = 0;
         if (!mc_bucket(pl, b)) continue;
-        const int cols = mc_item_cols(B.k);
-        const int tpi = 2 * rb;
+        const int cols = back_cols(B.k, d), verts = back_verts(B.k, d);
+        // tiles per item: the fewest whose items fit one round of resident workgroups (an item loads its columns of dA
+        // first, 3 to 5 us, so a second round costs that again)
+        const int64_t resident = back_slots(B.k), blocks = (d + cols - 1) / cols;
+        int64_t tiles = 0, most = 1;
+        for (const Shape &s : shapes)
+            if (s.bucket == b) {
+                tiles += (s.n + verts - 1) / verts;
+                most = std::max<int64_t>(most, (s.n + verts - 1) / verts);
+            }
+        int tpi = (int)std::max<int64_t>(1, tiles * blocks / resident);
+        for (; tpi < most; ++tpi) {
+            int64_t items = 0;
+            for (const Shape &s : shapes)
+                if (s.bucket == b) items += ((s.n + verts - 1) / verts + tpi - 1) / tpi * blocks;
+            if (items <= resident) break;
+        }
         std::vector<McItem> ranges;  // (shape, tile range) tasks, column block still open
-        for (const Shape &s : shapes_of(pl)) {
+        for (const Shape &s : shapes) {
             if (s.bucket != b) continue;
-            const int ntile = (int)((s.n + 255) / 256);
+            const int ntile = (int)((s.n + verts - 1) / verts);
             for (int t0 = 0; t0 < ntile; t0 += tpi) {
                 McItem w;
                 w.phi = s.phi;
@@ -357,7 +373,7 @@ void build_bwd_items(fmap_plan *pl, int rb, std::vector<BwdItem> &bi, std::vecto
         }
         B.mc_n = (int)mi.size() - B.mc_off;
     }
-    for (const Shape &s : shapes_of(pl)) {
+    for (const Shape &s : shapes) {
         const Bucket &B = pl->buckets[s.bucket];
         if (B.mc_n > 0) continue;
         const int db = (int)((d + 255) / 256);
@@ -379,57 +395,94 @@ void build_bwd_items(fmap_plan *pl, int rb, std::vector<BwdItem> &bi, std::vecto
     }
 }
 
-// The forward projection items of all shapes, then the fixed-order chunk sums.
+// The split kernels' forward items of the shapes with k <= kSmallK (large = 0) or k > kSmallK (1), then the fixed-order
+// chunk sums of those shapes (whose general items have run before).
+hipError_t launch_fwd_part(fmap_plan *pl, int large, hipStream_t st)
+{
+    hipError_t e = hipSuccess;
+    if (!large) {
+        e = launch_fwd_short_items(pl->d_small, pl->nsmall, st);
+    } else {
+        e = launch_fwd_sliced_items(pl->d_sliced, pl->nsliced, st);
+        for (int c = 0; c < kTallClasses && e == hipSuccess; ++c)
+            e = launch_fwd_tall_items(pl->d_tall[c], pl->ntall[c], c, st);
+    }
+    if (e == hipSuccess && pl->nred[large] > 0) e = launch_reduce_items(pl->d_red[large], pl->nred[large], st);
+    return e;
+}
+
+// The forward projection of all shapes.
 hipError_t launch_projections_fwd(fmap_plan *pl, int grid, hipStream_t st)
 {
-    hipError_t e = launch_fwd_short_items(pl->d_small, pl->nsmall, st);
-    for (int c = 0; c < kTallClasses && e == hipSuccess; ++c)
-        e = launch_fwd_tall_items(pl->d_tall[c], pl->ntall[c], c, st);
-    if (e == hipSuccess && pl->nfwd > 0) e = launch_fwd_items(pl->d_fwd, pl->nfwd, (int)pl->kmax, grid, st);
-    if (e == hipSuccess) e = launch_reduce_items(pl->d_red, pl->nred, st);
+    hipError_t e = pl->nfwd > 0 ? launch_fwd_items(pl->d_fwd, pl->nfwd, (int)pl->kmax, grid, st) : hipSuccess;
+    if (e == hipSuccess) e = launch_fwd_part(pl, 1, st);
+    if (e == hipSuccess) e = launch_fwd_part(pl, 0, st);
     return e;
+}
+
+hipError_t launch_group_bwd(fmap_plan *pl, const Bucket &B, hipStream_t st)
+{
+    return B.mc_n > 0 ? launch_bwd_split_items(pl->d_mc + B.mc_off, B.mc_n, B.k, pl->d, st) : hipSuccess;
 }
 
 hipError_t launch_projections_bwd(fmap_plan *pl, int grid, hipStream_t st)
 {
     hipError_t e = hipSuccess;
     for (const Bucket &B : pl->buckets)
-        if (e == hipSuccess && B.mc_n > 0) e = launch_bwd_mc_items(pl->d_mc + B.mc_off, B.mc_n, B.k, st);
+        if (e == hipSuccess) e = launch_group_bwd(pl, B, st);
     if (e == hipSuccess && pl->nbwd > 0) e = launch_bwd_items(pl->d_bwd, pl->nbwd, (int)pl->kmax, grid, st);
     return e;
 }
 
-// The per-group solves of one pass.  Groups share no buffer (each has its own blocks of A, B, C, factors,
-// info and workspace) and the solve kernels have no inter-workgroup waits, so with `branch` the groups run on
-// separate streams forked from st and joined back into it: under capture, parallel branches of the graph, so
-// that one group's latency-bound kernels run beside another group's.  With `tiled_in_line` the groups of the
-// tiled row solve (k > kSmallK) stay in sequence on st: each is a persistent grid sized to the whole chip, and
-// two side by side contend for it; only the other groups branch off beside them.
-template <typename Fn>
-hipError_t record_groups(fmap_plan *pl, hipStream_t st, bool branch, bool tiled_in_line, Fn fn)
+// One pass's per-group work as branches.  Groups share no buffer (each has its own blocks of A, B, C, factors, info and
+// workspace) and no kernel waits on another workgroup, so groups may run on streams forked from st and joined back into
+// it: under capture, parallel branches of the graph.  With `tiled_in_line` the groups of the tiled row solve
+// (k > kSmallK) stay in sequence on st: each of its solves is a persistent grid sized to the whole chip, and two side by
+// side contend for it.  The others run on the side streams.  `part(large, stream)` is the work that precedes the groups
+// of either kind: the latency-bound solves of the large k then run beside the memory-bound projections of the small ones.
+template <typename Part, typename Fn>
+hipError_t record_groups(fmap_plan *pl, hipStream_t st, bool branch, bool tiled_in_line, Part part, Fn fn)
 {
-    const int nb = (int)pl->buckets.size();
-    const int nside = branch ? std::min<int>((int)pl->side.size(), nb - 1) : 0;
-    std::vector<int> lane(nb, 0);
-    int next = 0, used = 0;  // lanes 1..used receive work
-    for (int i = 0; i < nb && nside > 0; ++i) {
-        if (tiled_in_line && pl->buckets[i].k > kSmallK) continue;
-        // round robin over all lanes, or over the side lanes when st carries the tiled groups
-        const int span = tiled_in_line ? nside : nside + 1;
-        const int l = (tiled_in_line ? 1 : 0) + (next++ % span);
-        lane[i] = l;
-        used = std::max(used, l);
-    }
+    auto in_line = [&](const Bucket &B) { return tiled_in_line && B.k > kSmallK; };
+    int nsmall = 0, nlarge = 0;
+    for (const Bucket &B : pl->buckets) (in_line(B) ? nlarge : nsmall) += 1;
+    const bool forked = branch && nsmall > 0 && !pl->side.empty() && nsmall + nlarge > 1;
     hipError_t e = hipSuccess;
-    if (used > 0) {
-        e = hipEventRecord(pl->fork, st);
-        for (int l = 1; l <= used && e == hipSuccess; ++l) e = hipStreamWaitEvent(pl->side[l - 1], pl->fork, 0);
+    if (!forked) {
+        for (int large = 1; large >= 0 && e == hipSuccess; --large) {
+            if ((large ? nlarge : nsmall) == 0) continue;
+            e = part(large, st);
+            for (Bucket &B : pl->buckets)
+                if (e == hipSuccess && in_line(B) == (large != 0)) e = fn(B, st);
+        }
+        return e;
     }
-    for (int i = 0; i < nb && e == hipSuccess; ++i) e = fn(pl->buckets[i], lane[i] == 0 ? st : pl->side[lane[i] - 1]);
+    // the small groups' lanes: the side streams, or st and the side streams when st has no large group
+    std::vector<hipStream_t> lanes;
+    if (nlarge == 0) lanes.push_back(st);
+    for (hipStream_t q : pl->side)
+        if ((int)lanes.size() < nsmall) lanes.push_back(q);
+    const hipStream_t first = lanes[0];
+    if (first != st) {
+        e = hipEventRecord(pl->fork, st);
+        if (e == hipSuccess) e = hipStreamWaitEvent(first, pl->fork, 0);
+    }
+    if (e == hipSuccess) e = part(0, first);
+    if (e == hipSuccess && lanes.size() > 1) e = hipEventRecord(pl->fork2, first);
+    size_t used = 1;  // lanes that received work
+    for (size_t l = 1; l < lanes.size() && e == hipSuccess; ++l) {
+        e = hipStreamWaitEvent(lanes[l], pl->fork2, 0);
+        used = l + 1;
+    }
+    if (e == hipSuccess && nlarge > 0) e = part(1, st);
+    int next = 0;
+    for (Bucket &B : pl->buckets)
+        if (e == hipSuccess) e = fn(B, in_line(B) ? st : lanes[next++ % lanes.size()]);
     // join every forked lane, also after an error, so that the capture ends with no unjoined work
-    for (int l = 1; l <= used; ++l) {
-        hipError_t j = hipEventRecord(pl->join[l - 1], pl->side[l - 1]);
-        if (j == hipSuccess) j = hipStreamWaitEvent(st, pl->join[l - 1], 0);
+    for (size_t l = 0; l < used; ++l) {
+        if (lanes[l] == st) continue;
+        hipError_t j = hipEventRecord(pl->join[l - (nlarge == 0 ? 1 : 0)], lanes[l]);
+        if (j == hipSuccess) j = hipStreamWaitEvent(st, pl->join[l - (nlarge == 0 ? 1 : 0)], 0);
         if (e == hipSuccess) e = j;
     }
     return e;
@@ -438,14 +491,16 @@ hipError_t record_groups(fmap_plan *pl, hipStream_t st, bool branch, bool tiled_
 hipError_t record_forward(fmap_plan *pl, hipStream_t st, bool branch = false)
 {
     hipError_t e = launch_copies(pl->d_gf, pl->ngf, st);
-    if (e == hipSuccess) e = launch_projections_fwd(pl, pl->grid_fwd, st);
+    if (e == hipSuccess && pl->nfwd > 0) e = launch_fwd_items(pl->d_fwd, pl->nfwd, (int)pl->kmax, pl->grid_fwd, st);
     if (e == hipSuccess)
-        e = record_groups(pl, st, branch, true, [&](Bucket &B, hipStream_t s) {
-            const int64_t P = (int64_t)B.pairs.size();
-            return launch_solve(B.AB, B.AB + (size_t)P * B.k * pl->d, B.evx, B.evy, B.lam, pl->mask_kind, pl->gamma,
-                                P, B.k, B.k, pl->d, 0, 0.f, B.C, pl->recompute ? nullptr : B.factors, B.info, nullptr,
-                                B.ws, s, B.waves);
-        });
+        e = record_groups(
+            pl, st, branch, true, [&](int large, hipStream_t s) { return launch_fwd_part(pl, large, s); },
+            [&](Bucket &B, hipStream_t s) {
+                const int64_t P = (int64_t)B.pairs.size();
+                return launch_solve(B.AB, B.AB + (size_t)P * B.k * pl->d, B.evx, B.evy, B.lam, pl->mask_kind, pl->gamma,
+                                    P, B.k, B.k, pl->d, 0, 0.f, B.C, pl->recompute ? nullptr : B.factors, B.info,
+                                    nullptr, B.ws, s, B.waves);
+            });
     if (e == hipSuccess) e = launch_copies(pl->d_sf, pl->nsf, st);
     return e;
 }
@@ -454,14 +509,18 @@ hipError_t record_backward(fmap_plan *pl, hipStream_t st, bool branch = false)
 {
     hipError_t e = launch_copies(pl->d_gb, pl->ngb, st);
     if (e == hipSuccess)
-        e = record_groups(pl, st, branch, false, [&](Bucket &B, hipStream_t s) {
-            const int64_t P = (int64_t)B.pairs.size();
-            const size_t half = (size_t)P * B.k * pl->d;
-            return launch_solve_backward(B.dC, B.AB, B.AB + half, B.C, B.evx, B.evy, B.lam, pl->mask_kind, pl->gamma,
-                                         P, B.k, B.k, pl->d, pl->recompute ? nullptr : B.factors, B.dAB, B.dAB + half,
-                                         nullptr, nullptr, B.ws, s, B.waves);
-        });
-    if (e == hipSuccess) e = launch_projections_bwd(pl, pl->grid_bwd, st);
+        e = record_groups(
+            pl, st, branch, false, [](int, hipStream_t) { return hipSuccess; },
+            [&](Bucket &B, hipStream_t s) {
+                const int64_t P = (int64_t)B.pairs.size();
+                const size_t half = (size_t)P * B.k * pl->d;
+                const hipError_t r = launch_solve_backward(B.dC, B.AB, B.AB + half, B.C, B.evx, B.evy, B.lam,
+                                                           pl->mask_kind, pl->gamma, P, B.k, B.k, pl->d,
+                                                           pl->recompute ? nullptr : B.factors, B.dAB, B.dAB + half,
+                                                           nullptr, nullptr, B.ws, s, B.waves);
+                return r == hipSuccess ? launch_group_bwd(pl, B, s) : r;
+            });
+    if (e == hipSuccess && pl->nbwd > 0) e = launch_bwd_items(pl->d_bwd, pl->nbwd, (int)pl->kmax, pl->grid_bwd, st);
     return e;
 }
 
@@ -578,6 +637,7 @@ void plan_free(fmap_plan *pl)
     for (hipStream_t q : pl->side) (void)hipStreamDestroy(q);
     for (hipEvent_t ev : pl->join) (void)hipEventDestroy(ev);
     if (pl->fork) (void)hipEventDestroy(pl->fork);
+    if (pl->fork2) (void)hipEventDestroy(pl->fork2);
     for (void *p : pl->allocs) (void)hipFree(p);
     delete pl;
 }
@@ -682,14 +742,18 @@ fmap_status fmap_plan_create(const fmap_pair *pairs, int32_t npairs, int64_t d, 
         build_fwd_items(pl, chunk, it, &pf);
         pl->nfwd = (int)it.general.size();
         pl->nsmall = (int)it.small.size();
-        pl->nred = (int)it.red.size();
         hipError_t e = upload(pl, &pl->d_fwd, it.general, st);
         if (e == hipSuccess) e = upload(pl, &pl->d_small, it.small, st);
+        pl->nsliced = (int)it.sliced.size();
+        if (e == hipSuccess) e = upload(pl, &pl->d_sliced, it.sliced, st);
         for (int c = 0; c < kTallClasses && e == hipSuccess; ++c) {
             pl->ntall[c] = (int)it.tall[c].size();
             e = upload(pl, &pl->d_tall[c], it.tall[c], st);
         }
-        if (e == hipSuccess) e = upload(pl, &pl->d_red, it.red, st);
+        for (int c = 0; c < 2 && e == hipSuccess; ++c) {
+            pl->nred[c] = (int)it.red[c].size();
+            e = upload(pl, &pl->d_red[c], it.red[c], st);
+        }
         return e;
     };
     auto set_bwd = [&](int rb) -> hipError_t {
@@ -748,7 +812,9 @@ fmap_status fmap_plan_create(const fmap_pair *pairs, int32_t npairs, int64_t d, 
         if (bwd) {
             best = 1e30f;
             int brb = 2, bgb = 2 * cus;
+            FMAP_TRY(set_bwd(brb));
             for (int rb : {1, 2, 4, 8}) {
+                if (pl->nbwd == 0) break;  // rows per item and grid are the general kernel's
                 FMAP_TRY(set_bwd(rb));
                 for (int gm : {1, 2, 4}) {
                     const int g = std::max(1, std::min(gm * cus, std::max(pl->nbwd, 1)));
@@ -775,6 +841,7 @@ fmap_status fmap_plan_create(const fmap_pair *pairs, int32_t npairs, int64_t d, 
     FMAP_TRY(hipStreamCreateWithFlags(&pl->cap, hipStreamNonBlocking));
     if (pl->buckets.size() > 1) {
         FMAP_TRY(hipEventCreateWithFlags(&pl->fork, hipEventDisableTiming));
+        FMAP_TRY(hipEventCreateWithFlags(&pl->fork2, hipEventDisableTiming));
         const int nside = std::min<int>((int)pl->buckets.size(), kLanes) - 1;
         for (int l = 0; l < nside; ++l) {
             hipStream_t q = nullptr;

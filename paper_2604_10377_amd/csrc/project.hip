@@ -58,137 +58,6 @@ __global__ __launch_bounds__(256) void proj_fwd_items_kernel(const FwdItem *__re
     }
 }
 
-// ---------------------------------------------------------------------------
-// Backward, LDS-pipelined variant (float32, k <= 64, 256-column block of d per
-// workgroup).  The dA block (k x 256) is staged in LDS once per workgroup; the
-// basis rows and masses of 64-vertex stages arrive by direct global->LDS loads
-// into a 3-deep ring, two stages ahead.  8 waves = 2 row halves x 4 column
-// groups; a wave owns 32 vertices x 64 columns (two 32x32 tiles) per stage and
-// contracts over k with the 32x32x2 matrix cores (k = 50: 25 steps, no
-// padding).  Output rows are written with buffer stores whose out-of-range
-// lanes are dropped by the hardware, so every wave issues the same number of
-// memory operations per stage and the vmcnt waits stay exact (stores count
-// in vmcnt on this architecture).
-// ---------------------------------------------------------------------------
-constexpr int BS = 64;                 // vertices per stage
-constexpr int BNST = 3;                // ring depth
-constexpr int BLD = 256 + 32;          // LDS row stride of the dA block (floats)
-constexpr int BFL = 3;                 // direct loads per wave per stage
-constexpr int BNS = 32;                // stores per wave per stage
-constexpr int BP_TILE = 4096;          // basis tile: 64 rows x k <= 64 floats (16 KB)
-constexpr int BM_TILE = 256;           // masses: one 1 KB load window
-constexpr int BSTAGE = BP_TILE + BM_TILE;
-constexpr int BG_FLOATS = 64 * BLD;    // dA block, k <= 64 rows
-constexpr size_t BWD_LDS_BYTES = (size_t)(BNST * BSTAGE + BG_FLOATS) * sizeof(float);
-
-__global__ __launch_bounds__(512) void proj_bwd_lds_kernel(const float *__restrict__ phi,
-                                                           const float *__restrict__ mass,
-                                                           const float *__restrict__ dA, int n, int k, int d,
-                                                           int nsplit, int dblocks, float *__restrict__ dF)
-{
-    extern __shared__ __align__(16) float smem[];
-    float *sG = smem + BNST * BSTAGE;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int cg = wave & 3, rh = wave >> 2;
-    const int half = lane >> 5, l32 = lane & 31;
-    int bid = blockIdx.x;
-    const int db = bid % dblocks;
-    bid /= dblocks;
-    const int split = bid % nsplit;
-    const int s = bid / nsplit;
-    const int dbase = db * 256;
-
-    const int nst_all = (n + BS - 1) / BS;
-    const int st0 = (int)(((long)split * nst_all) / nsplit), st1 = (int)(((long)(split + 1) * nst_all) / nsplit);
-    const int vbeg = st0 * BS, vend = min(n, st1 * BS);
-    const int nst = st1 - st0;
-
-    const float *P = phi + (size_t)s * n * k;
-    const float *Mv = mass + (size_t)s * n;
-    const float *G = dA + (size_t)s * k * d;
-    const __amdgpu_buffer_rsrc_t out =
-        __builtin_amdgcn_make_buffer_rsrc(dF + (size_t)s * n * d, 0, (int)((size_t)n * d * sizeof(float)), 0x00020000);
-
-    // ring to zero (finite stale values), dA block to LDS (zero beyond k and d)
-    for (int e = tid * 4; e < BNST * BSTAGE; e += 512 * 4) *reinterpret_cast<f32x4 *>(&smem[e]) = f32x4{0, 0, 0, 0};
-    const int kp = (k + 1) & ~1;
-    batched_for<8>(
-        tid, kp * 256, 512, [&](int e) { return G[(size_t)min(e >> 8, k - 1) * d + min(dbase + (e & 255), d - 1)]; },
-        [&](int e, float g) {
-            const int j = e >> 8, c = e & 255;
-            sG[j * BLD + c] = (j < k && dbase + c < d) ? g : 0.f;
-        });
-    __syncthreads();
-
-    const int npw = (BS * k + 255) / 256;  // 1 KB basis windows per stage
-    auto issue = [&](int t) {
-        float *S = smem + (t % BNST) * BSTAGE;
-        const int v = vbeg + t * BS;
-        const int rows = min(BS, vend - v);
-        const int pvalid = rows * k;
-#pragma unroll
-        for (int q = 0; q < BFL; ++q) {
-            const int item = q * 8 + wave;
-            if (item < npw) {
-                const int off = min(item * 256 + 4 * lane, ((pvalid + 3) & ~3) - 4);
-                dma16(P + (size_t)v * k + off, S + item * 256);
-            } else {
-                const int off = min(4 * lane, ((rows + 3) & ~3) - 4);
-                dma16(Mv + v + off, S + BP_TILE);
-            }
-        }
-    };
-
-    for (int t = 0; t < BNST - 1 && t < nst; ++t) issue(t);
-    const int kh = (k + 1) >> 1;
-    for (int t = 0; t < nst; ++t) {
-        if (t + BNST - 1 < nst) issue(t + BNST - 1);
-        // Memory operations issued after stage t's loads: the stores of stages t-2 and t-1 and the
-        // loads of stages t+1 and t+2 (those that exist).  Waiting until at most that many are
-        // outstanding retires stage t's loads (vmcnt is in issue order); counts above the 6-bit
-        // counter range are clamped, which only waits longer.
-        const int nl = min(2, nst - 1 - t), ns = min(2, t);
-        switch (nl * 3 + ns) {
-        case 0: wait_vmcnt<0>(); break;
-        case 1: wait_vmcnt<BNS>(); break;
-        case 2: wait_vmcnt<(2 * BNS < 63 ? 2 * BNS : 63)>(); break;
-        case 3: wait_vmcnt<BFL>(); break;
-        case 4: wait_vmcnt<BFL + BNS>(); break;
-        case 5: wait_vmcnt<(BFL + 2 * BNS < 63 ? BFL + 2 * BNS : 63)>(); break;
-        case 6: wait_vmcnt<2 * BFL>(); break;
-        case 7: wait_vmcnt<2 * BFL + BNS>(); break;
-        default: wait_vmcnt<(2 * BFL + 2 * BNS < 63 ? 2 * BFL + 2 * BNS : 63)>(); break;
-        }
-        lds_barrier();
-        const float *S = smem + (t % BNST) * BSTAGE;
-        const float *Ps = S, *Ms = S + BP_TILE;
-        const int vs = vbeg + t * BS;
-        const int vloc = 32 * rh + l32;
-        const float m = (vs + vloc < vend) ? Ms[vloc] : 0.f;
-        const float *prow = Ps + vloc * k + half;
-        const float *g0 = sG + half * BLD + cg * 64 + l32;
-        f32x16 acc0 = zero16(), acc1 = zero16();
-        for (int tt = 0; tt < kh; ++tt) {
-            const float a = (2 * tt + half < k) ? prow[2 * tt] * m : 0.f;
-            const float *g = g0 + 2 * tt * BLD;
-            acc0 = mfma32x32x2(a, g[0], acc0);
-            acc1 = mfma32x32x2(a, g[32], acc1);
-        }
-        lds_barrier();  // slot t is refilled by the next iteration's issue
-        // 32 unconditional stores per wave; rows past the end are dropped by the buffer range check
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int vr = vs + 32 * rh + acc32_row(r, lane);
-            const int c0 = dbase + cg * 64 + l32;
-            const bool rv = vr < vend;
-            const unsigned o0 = (rv && c0 < d) ? (unsigned)((vr * d + c0) * 4) : 0x80000000u;
-            const unsigned o1 = (rv && c0 + 32 < d) ? (unsigned)((vr * d + c0 + 32) * 4) : 0x80000000u;
-            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc0[r]), out, o0, 0, 0);
-            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc1[r]), out, o1, 0, 0);
-        }
-    }
-}
-
 // A[s] = sum over chunks (in chunk order) of part[s][chunk].  Four consecutive
 // elements per thread (k*d % 4 == 0, 16-byte aligned buffers); the chunks are
 // read in groups of RG, all loads of a group in flight before the adds.
@@ -533,6 +402,8 @@ hipError_t launch_project(const void *phi, const float *mass, const void *feat, 
     if (dtype == 0 && tall_shape_ok(n, k, d) && aligned16(feat) && aligned16(A) && aligned16(ws))
         return launch_project_tall((const float *)phi, mass, (const float *)feat, batch, n, k, d,
                                    tall_chunks(batch, n, k, d), A, ws, st);
+    if (dtype == 0 && sliced_fwd_shape_ok(n, k, d) && aligned16(phi) && aligned16(mass) && aligned16(feat))
+        return launch_project_sliced((const float *)phi, mass, (const float *)feat, batch, n, k, d, A, ws, st);
     if (dtype == 0 && short_shape_ok(n, k, d) && aligned16(feat) && aligned16(A) && aligned16(ws))
         return launch_project_short((const float *)phi, mass, (const float *)feat, batch, n, k, d,
                                     short_chunks(batch, n, k, d), A, ws, st);
@@ -570,42 +441,11 @@ static void launch_bwd_t(const void *phi, const float *mass, const float *dA, in
                        (int)k, (int)d, rgroups, RB, dblocks, dF);
 }
 
-static bool lds_bwd_shape_ok(int64_t n, int64_t k, int64_t d, int32_t dtype)
-{
-    return dtype == 0 && k <= 64 && n % 4 == 0 && d % 4 == 0 && (n * k) % 4 == 0 && n >= 4 * BS &&
-           (double)n * d * 4.0 < 2147483647.0;
-}
-
-static int lds_bwd_nsplit(int64_t batch, int64_t n, int64_t d)
-{
-    const int64_t dblocks = (d + 255) / 256;
-    const int64_t stages = (n + BS - 1) / BS;
-    int64_t ns = (device_cu_count() + batch * dblocks - 1) / (batch * dblocks);
-    if (ns > stages / 3) ns = stages / 3;
-    if (ns < 1) ns = 1;
-    return (int)ns;
-}
-
 hipError_t launch_project_backward(const void *phi, const float *mass, int32_t dtype, const float *dA, int64_t batch,
                                    int64_t n, int64_t k, int64_t d, float *dF, hipStream_t st)
 {
-    if (dtype == 0 && f32_split_bwd_shape_ok(n, k, d) && ((uintptr_t)phi & 7) == 0 && ((uintptr_t)dF & 15) == 0)
-        return launch_project_backward_f32_split((const float *)phi, mass, dA, batch, n, k, d, dF, st);
-    if (dtype == 0 && f32k_bwd_shape_ok(n, k, d) && ((uintptr_t)phi & 7) == 0 && ((uintptr_t)dF & 15) == 0)
-        return launch_project_backward_f32k((const float *)phi, mass, dA, batch, n, k, d, dF, st);
-    if (lds_bwd_shape_ok(n, k, d, dtype) && aligned16(phi) && aligned16(mass)) {
-        static bool attr_set = false;
-        if (!attr_set) {
-            (void)hipFuncSetAttribute((const void *)proj_bwd_lds_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      (int)BWD_LDS_BYTES);
-            attr_set = true;
-        }
-        const int ns = lds_bwd_nsplit(batch, n, d);
-        const int dblocks = (int)((d + 255) / 256);
-        hipLaunchKernelGGL(proj_bwd_lds_kernel, dim3((unsigned)(batch * ns * dblocks)), dim3(512), BWD_LDS_BYTES, st,
-                           (const float *)phi, mass, dA, (int)n, (int)k, (int)d, ns, dblocks, dF);
-        return hipGetLastError();
-    }
+    if (dtype == 0 && back_shape_ok(k, d))
+        return launch_project_back((const float *)phi, mass, dA, batch, n, k, d, dF, st);
     if (dtype == 1 && bf16_bwd_shape_ok(n, k, d) && aligned16(phi) && aligned16(dF))
         return launch_project_backward_bf16((const uint16_t *)phi, mass, dA, batch, n, k, d, dF, st);
     if (dtype == 0) {

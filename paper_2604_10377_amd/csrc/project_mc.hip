@@ -605,227 +605,269 @@ __global__ __launch_bounds__(512, 2) void proj_bwd_mc_kernel(const T *__restrict
                                dF + (size_t)s * n * d, n, k, d, t0, t1, db * BB_COLS);
 }
 
-// Uneven batches: one workgroup per work item (float32 basis).
-template <int KS>
-__global__ __launch_bounds__(512, 2) void proj_bwd_mc_items_kernel(const McItem *__restrict__ items)
-{
-    const McItem w = items[blockIdx.x];
-    if (w.t0 >= w.t1) return;  // empty slot of the table (whole workgroup, before any barrier)
-    bwdmc_block<float, 3, 3, KS>(global_ptr(w.phi), global_ptr(w.mass), global_ptr(w.dA), global_ptr(w.dF), w.n, w.k, w.d, w.t0, w.t1, w.dbase);
-}
+constexpr int XS = 32;  // vertices per stage (one matrix-core K step)
 
 // ---------------------------------------------------------------------------
-// Backward projection for float32 inputs with 64 < k <= kMaxK (k even), on the
-// bf16 matrix cores with both operands split into three parts (six products).
+// Forward projection with float32 basis and features on the bf16 matrix cores for 64 < k and d < 5 k / 4 (k % 4 == 0):
+// both operands split into three bf16 parts, six products kept (float32 level).
 //
-// The dA^T parts of every k slot would not fit in LDS for 128 columns, so a
-// workgroup owns a 64-column block: 3 parts x 64 columns x (32 KS + 8) bf16
-// pairs, up to 126 KB, staged once.  8 waves x 32 vertices form a 256-vertex
-// tile.  A wave's work is a flat sequence of steps (tile, K step); the basis
-// row segments of step s + 3 are loaded while step s is multiplied (four
-// register buffers rotated by unrolling, loads unconditional from clamped
-// addresses), so the basis stream never waits for a tile boundary.  The 4 x 2
-// accumulators of a tile are stored, scaled by the masses, after its last K
-// step, exchanged across lanes first so that each store writes whole 128-byte
-// lines.  The column blocks of one vertex range share an XCD (their basis rows
-// are read from HBM once and from L2 afterwards).
+// With d so close to k, A A^T is nearly singular (condition about 4000 at k = 120, d = 128) and the last bits of A
+// decide C to 2e-5: any other order or rounding of these sums, the tall kernel's more exact ones included, moves results
+// by more than two float32 builds of the same sums should differ.  These shapes therefore keep the rounding they had;
+// all others run on the tall kernel (k = 120, d = 256: 139 against 115 us).
+//
+// Workgroup = 4 waves over a 256-column block and the 64-row slice [64 kb, 64 kb + 64) of the basis, each stage of 32
+// vertices holding that 64-float slice of every vertex row (8 windows of 4 vertices).  The row blocks and column blocks
+// of one vertex chunk take consecutive ids on one XCD, so the feature tile they all read comes from HBM once and from
+// that XCD's L2 afterwards.  Within a block: wave w owns block columns 64w .. 64w + 63 (column 4m + t of the wave is
+// column m of tile t).  Each lane loads its 4 feature columns of 8 vertices straight into registers (eight 16-byte
+// loads), two stages ahead.  The basis slice and the masses arrive by direct global->LDS loads in a ring of 3.  Per stage
+// wave w splits the basis x mass values of row tile w (rows 4R + w) into their three bf16 parts and stores them in LDS in
+// the matrix-core operand layout; after a barrier every wave reads all four tiles.
 // ---------------------------------------------------------------------------
-constexpr int BK_COLS = 64;  // columns per workgroup
-__host__ __device__ constexpr size_t bwdk_lds(int ks) { return (size_t)3 * BK_COLS * bwdmc_stride(ks); }
+constexpr int RNST = 3;  // basis stages in the LDS ring
+constexpr int RFL = 3;   // direct loads per wave per stage: 2 basis windows, 1 mass window
+constexpr int RFF = 8;   // feature loads per lane per stage
+constexpr int RSTAGE = 8 * 1024 + 256;  // basis windows + mass window
+constexpr int RPARTS = 3 * 4 * 64 * 16;  // split basis tile: [part][row tile][lane] of u32x4
+__host__ __device__ constexpr size_t x3r_lds() { return (size_t)RNST * RSTAGE + RPARTS; }
 
-struct BkStep {
-    RowSeg<float> seg[2];  // vertex tiles nt = 0, 1
-    float m[2];            // their masses
-};
-
-// One workgroup's block: 256-vertex tiles [t0, t1) of one shape for the columns [dbase, dbase + 64).
-// SHALLOW: loads one step ahead instead of three (two step buffers), for instances that run two
-// workgroups per CU, where the other workgroup covers the load latency.
-template <int KS, bool SHALLOW = false>
-__device__ __forceinline__ void bwdk_block(const float *__restrict__ P, const float *__restrict__ Mv,
-                                           const float *__restrict__ G, float *__restrict__ O, int n, int k, int d,
-                                           int t0, int t1, int dbase)
+// One workgroup's block: vertices [vbeg, vend) of one shape (P, Mv, F), basis rows [64 kb, 64 kb + 64)
+// columns [dbase, dbase + 256); the k x d partial slot O receives its part.
+// vbeg is a multiple of 32, and every stage but the last is full.
+__device__ __forceinline__ void x3r_block(const float *__restrict__ P, const float *__restrict__ Mv,
+                                          const float *__restrict__ F, int n, int k, int d, int vbeg, int vend,
+                                          int kb, int dbase, float *__restrict__ O)
 {
-    constexpr int STRIDE = bwdmc_stride(KS);
     extern __shared__ __align__(16) float smem[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int m16 = lane & 15, g4 = lane >> 4;
+    const int kbase = 64 * kb;
+    const int kvalid = min(64, k - kbase);  // basis rows of this block
+    constexpr int pstride = 64;             // LDS floats per vertex row of the basis tile
+    const int nst = (vend - vbeg + XS - 1) / XS;
 
-    // dA^T parts for columns [dbase, dbase + 64), slots < 32 KS (zero past k and d)
-    char *parts = reinterpret_cast<char *>(smem);
-    batched_for<8>(
-        tid, KS * 32 * BK_COLS, 512,
-        [&](int e) {
-            const int jj = e / BK_COLS, c = e - jj * BK_COLS;
-            return G[(size_t)min(jj, k - 1) * d + min(dbase + c, d - 1)];
-        },
-        [&](int e, float g) {
-            const int jj = e / BK_COLS, c = e - jj * BK_COLS;
-            const float v = (jj < k && dbase + c < d) ? g : 0.f;
-            uint32_t w[3];
-            split_pack<3>(v, 0.f, w);
-#pragma unroll
-            for (int p = 0; p < 3; ++p)
-                *reinterpret_cast<uint16_t *>(parts + (size_t)p * BK_COLS * STRIDE + c * STRIDE + 2 * jj) =
-                    (uint16_t)w[p];
-        });
+    char *ring = reinterpret_cast<char *>(smem);
+    u32x4_t *parts = reinterpret_cast<u32x4_t *>(ring + RNST * RSTAGE);
+    for (int e = tid * 16; e < RNST * RSTAGE; e += 256 * 16) *reinterpret_cast<f32x4 *>(ring + e) = f32x4{0, 0, 0, 0};
     __syncthreads();
 
-    if (t0 >= t1) return;
-    const int nsteps = (t1 - t0) * KS;
-    const bool vec = (d & 3) == 0;
-
-    auto load_step = [&](int st, BkStep &b) {
-        const int vt = t0 + st / KS, ks = st % KS;
+    // basis roles: windows wave and wave + 4, the mass window.  A window is vertices 4w .. 4w + 3 of the slice with
+    // lane l taking the 4 floats at column 64 kb + 4 (l % 16) (clamped to k - 4) of vertex 4w + l/16
+    const int pw0 = wave, pw1 = wave + 4;
+    const int scol = min(kbase + 4 * (lane & 15), k - 4);
+    // feature role: columns fc .. fc + 3 (clamped into d; d % 4 == 0) of vertices 8 g4 .. + 7
+    const int cw = wave * 64 + 4 * m16;
+    const int fc = min(dbase + cw, d - 4);
+    auto issue = [&](int t, f32x4 (&fr)[RFF]) {
+        char *S = ring + (t % RNST) * RSTAGE;
+        const int v = vbeg + t * XS;
+        const int rows = min(XS, vend - v);  // a multiple of 4 (n % 4 == 0)
+        const float *Pv = P + (size_t)v * k;
+        // vertices past the stage's rows read the last row
+        const int r0 = min(4 * pw0 + (lane >> 4), rows - 1), r1 = min(4 * pw1 + (lane >> 4), rows - 1);
+        dma16(Pv + (size_t)r0 * k + scol, reinterpret_cast<float *>(S + pw0 * 1024));
+        dma16(Pv + (size_t)r1 * k + scol, reinterpret_cast<float *>(S + pw1 * 1024));
+        __builtin_amdgcn_global_load_lds((glb_void_t *)(Mv + v + min(lane & 31, rows - 1)),
+                                         (lds_void_t *)(S + 8 * 1024), 4, 0, 0);
+        // (the row blocks of a chunk re-read the same features from L2: ordinary loads)
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
-            const int v = min(vt * BB_VT + wave * 32 + nt * 16 + m16, n - 1);
-            b.m[nt] = Mv[v];
-            b.seg[nt] = load_seg_f32(P + (size_t)v * k, ks * 32 + 8 * g4, k);
+        for (int i = 0; i < RFF; ++i) {
+            fr[i] = *reinterpret_cast<const f32x4 *>(F + (size_t)(v + min(8 * g4 + i, rows - 1)) * d + fc);
         }
     };
-    f32x4 acc[4][2];
+
+    f32x4 acc[4][4];
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
+    for (int a = 0; a < 4; ++a)
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) acc[mt][nt] = f32x4{0, 0, 0, 0};
-    auto step = [&](int st, const BkStep &b) {
-        const int vt = t0 + st / KS, ks = st % KS;
-        u32x4_t B[2][3];
+        for (int t = 0; t < 4; ++t) acc[a][t] = f32x4{0, 0, 0, 0};
+    // split role: row tile a = wave, operand lane = lane: basis row 4 m16 + wave, vertices 8 g4 .. + 7
+    const int srow = 4 * m16 + wave;
+    const bool srow_ok = srow < kvalid;
+    const int srow_c = min(srow, kvalid - 1);
+
+    auto stage = [&](int t, const f32x4 (&fr)[RFF]) {
+        const char *S = ring + (t % RNST) * RSTAGE;
+        const float *Ps = reinterpret_cast<const float *>(S);
+        const float *Ms = reinterpret_cast<const float *>(S + 8 * 1024);
+        const int vrem = vend - (vbeg + t * XS);
+        {
+            const f32x4 m0 = *reinterpret_cast<const f32x4 *>(Ms + 8 * g4);
+            const f32x4 m1 = *reinterpret_cast<const f32x4 *>(Ms + 8 * g4 + 4);
+            const float mv[8] = {m0[0], m0[1], m0[2], m0[3], m1[0], m1[1], m1[2], m1[3]};
+            float x[8];
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) seg_parts<3>(b.seg[nt], ks * 32 + 8 * g4, k, B[nt]);
+            for (int i = 0; i < 8; ++i) {
+                // the mass is masked, not the product, so the LDS reads are unconditional and issued together
+                const float pv = Ps[(8 * g4 + i) * pstride + srow_c];
+                x[i] = pv * ((srow_ok && 8 * g4 + i < vrem) ? mv[i] : 0.f);
+            }
+            uint32_t w[4][3];
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) {
-            u32x4_t A[3];
+            for (int jj = 0; jj < 4; ++jj) split_pack<3>(x[2 * jj], x[2 * jj + 1], w[jj]);
 #pragma unroll
-            for (int p = 0; p < 3; ++p)
-                A[p] = *reinterpret_cast<const u32x4_t *>(parts + (size_t)p * BK_COLS * STRIDE + (mt * 16 + m16) * STRIDE +
-                                                         2 * (ks * 32 + 8 * g4));
+            for (int p = 0; p < 3; ++p) parts[(p * 4 + wave) * 64 + lane] = u32x4_t{w[0][p], w[1][p], w[2][p], w[3][p]};
+        }
+        lds_barrier();
+        u32x4_t A[4][3];
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int p = 0; p < 3; ++p) A[a][p] = parts[(p * 4 + a) * 64 + lane];
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) {
+            u32x4_t B[3];
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) {
+                uint32_t w[3];
+                split_pack<3>(fr[2 * jj][tt], fr[2 * jj + 1][tt], w);
+#pragma unroll
+                for (int p = 0; p < 3; ++p) B[p][jj] = w[p];
+            }
 #pragma unroll
             for (int i = 0; i < 3; ++i)
 #pragma unroll
                 for (int jp = 0; jp < 3; ++jp)
                     if (i + jp <= 2) {
 #pragma unroll
-                        for (int nt = 0; nt < 2; ++nt) acc[mt][nt] = mfma16x16x32bf16(A[jp], B[nt][i], acc[mt][nt]);
+                        for (int a = 0; a < 4; ++a) acc[a][tt] = mfma16x16x32bf16(A[a][i], B[jp], acc[a][tt]);
                     }
-        }
-        if (ks == KS - 1) {  // the tile is complete: register r of lane (m16, g4) is column 4 g4 + r of tile mt
-            if (vec) {
-                // whole 128-byte lines: the accumulators are exchanged across lanes (ds_bpermute, no LDS
-                // allocation) so that one store covers 8 vertices x 32 columns, lane L taking vertex L / 8
-                // (+ 8 i) and columns 4 (L % 8) .. + 3 of the half block hh; the values and the mass product
-                // are those of the lane that computed them
-                const int c4 = lane & 7;
-                const bool upper = (c4 >> 2) != 0;  // tile 2 hh + 1
-#pragma unroll
-                for (int nt = 0; nt < 2; ++nt) {
-#pragma unroll
-                    for (int i = 0; i < 2; ++i) {
-                        const int vr = 8 * i + (lane >> 3);  // vertex within the 16 of nt
-                        const int src = 4 * (vr + 16 * (c4 & 3));
-                        const int v = vt * BB_VT + wave * 32 + nt * 16 + vr;
-                        const float m = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(b.m[nt])));
-                        float *row = O + (size_t)min(v, n - 1) * d;
-#pragma unroll
-                        for (int hh = 0; hh < 2; ++hh) {
-                            f32x4 val;
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) {
-                                const float lo = __int_as_float(
-                                    __builtin_amdgcn_ds_bpermute(src, __float_as_int(acc[2 * hh][nt][r])));
-                                const float hi = __int_as_float(
-                                    __builtin_amdgcn_ds_bpermute(src, __float_as_int(acc[2 * hh + 1][nt][r])));
-                                val[r] = (upper ? hi : lo) * m;
-                            }
-                            const int col = dbase + 32 * hh + 4 * c4;
-                            if (v < n && col < d) stream_store(reinterpret_cast<f32x4 *>(row + col), val);
-                        }
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int nt = 0; nt < 2; ++nt) {
-                    const int v = vt * BB_VT + wave * 32 + nt * 16 + m16;
-                    float *row = O + (size_t)min(v, n - 1) * d;
-#pragma unroll
-                    for (int mt = 0; mt < 4; ++mt) {
-                        const int col = dbase + mt * 16 + 4 * g4;
-                        const f32x4 val = acc[mt][nt] * b.m[nt];
-#pragma unroll
-                        for (int r = 0; r < 4; ++r)
-                            if (v < n && col + r < d) stream_store(row + col + r, val[r]);
-                    }
-                }
-            }
-#pragma unroll
-            for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-                for (int nt = 0; nt < 2; ++nt) acc[mt][nt] = f32x4{0, 0, 0, 0};
         }
     };
-    const int last = nsteps - 1;
-    if constexpr (SHALLOW) {
-        BkStep b0, b1;
-        load_step(0, b0);
-        __builtin_amdgcn_sched_barrier(0);
-        for (int st = 0; st < nsteps; st += 2) {
-            load_step(min(st + 1, last), b1);
-            step(st, b0);
-            load_step(min(st + 2, last), b0);
-            if (st + 1 < nsteps) step(st + 1, b1);
+
+    // Per stage t: wait for stage t (stage t + 1 may stay in flight), barrier (stage t visible;
+    // every wave done with stage t - 1, so its ring slot, the split buffer and its feature registers
+    // are free), issue stage t + 2 into them, split, barrier, products.  The three feature buffers
+    // rotate by unrolling; prefetches past the chunk reload its last stage (the same bytes into the
+    // same places), and every load has landed before the workgroup ends (its LDS is then reused).
+    // The loop runs whole triples and has no early exit, the last one or two stages follow it: an exit
+    // edge back into the loop header, or prologue loads reordered across the two stages, leaves the
+    // compiler's wait analysis unable to tell which loads stage t needs, and it then waits for all of
+    // them, the stage t + 2 prefetch included.
+    f32x4 f0[RFF], f1[RFF], f2[RFF];
+    constexpr int VPS = RFL + RFF;  // vector-memory operations per stage
+    if (nst <= 0) return;
+    issue(0, f0);
+    __builtin_amdgcn_sched_barrier(0);
+    issue(min(1, nst - 1), f1);
+    __builtin_amdgcn_sched_barrier(0);
+    const int nfull = nst - nst % 3;
+    for (int t = 0; t < nfull; t += 3) {
+        wait_vmcnt<VPS>();
+        lds_barrier();
+        issue(min(t + 2, nst - 1), f2);
+        stage(t, f0);
+        wait_vmcnt<VPS>();
+        lds_barrier();
+        issue(min(t + 3, nst - 1), f0);
+        stage(t + 1, f1);
+        wait_vmcnt<VPS>();
+        lds_barrier();
+        issue(min(t + 4, nst - 1), f1);
+        stage(t + 2, f2);
+    }
+    if (nst % 3 != 0) {  // stages nfull (in f0) and nfull + 1 (in f1) are issued
+        wait_vmcnt<VPS>();
+        lds_barrier();
+        stage(nfull, f0);
+        if (nst % 3 == 2) {
+            wait_vmcnt<0>();
+            lds_barrier();
+            stage(nfull + 1, f1);
         }
-        return;
     }
-    BkStep b0, b1, b2, b3;
-    // rounds of four with no early exit (the last round predicated), as in the backward above
-    load_step(0, b0);
-    __builtin_amdgcn_sched_barrier(0);
-    load_step(min(1, last), b1);
-    __builtin_amdgcn_sched_barrier(0);
-    load_step(min(2, last), b2);
-    __builtin_amdgcn_sched_barrier(0);
-    for (int st = 0; st < nsteps; st += 4) {
-        load_step(min(st + 3, last), b3);
-        step(st, b0);
-        load_step(min(st + 4, last), b0);
-        if (st + 1 < nsteps) step(st + 1, b1);
-        load_step(min(st + 5, last), b1);
-        if (st + 2 < nsteps) step(st + 2, b2);
-        load_step(min(st + 6, last), b2);
-        if (st + 3 < nsteps) step(st + 3, b3);
-    }
+    wait_vmcnt<0>();
+
+    // lane (m16, g4), register r: matrix-core row 4*g4 + r -> basis row 4(4*g4 + r) + a; column m16 of
+    // tile tt -> block column 64 wave + 4 m16 + tt
+    const int col = dbase + cw;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+            const int row = kbase + 16 * g4 + 4 * r + a;
+            if (row >= k || col >= d) continue;
+            const f32x4 v = f32x4{acc[a][0][r], acc[a][1][r], acc[a][2][r], acc[a][3][r]};
+            *reinterpret_cast<f32x4 *>(O + (size_t)row * d + col) = v;  // d % 4 == 0: all 4 columns exist
+        }
 }
 
-template <int KS>
-__global__ __launch_bounds__(512, 1) void proj_bwd_mck_kernel(const float *__restrict__ phi,
-                                                            const float *__restrict__ mass,
-                                                            const float *__restrict__ dA, int n, int k, int d,
-                                                            int vsplit, int dblocks, int ntasks,
-                                                            float *__restrict__ dF)
+__global__ __launch_bounds__(256, 2) void proj_fwd_x3r_kernel(const float *__restrict__ phi,
+                                                             const float *__restrict__ mass,
+                                                             const float *__restrict__ feat, int n, int k, int d,
+                                                             int nsplit, int dblocks, int kblocks, int ntiles,
+                                                             float *__restrict__ out)
 {
     const int bid = blockIdx.x;
     const int xs = bid & 7, q = bid >> 3;
-    const int db = q % dblocks;
-    const int j = (q / dblocks) * 8 + xs;
-    if (j >= ntasks) return;  // whole workgroup, before any barrier
-    const int vs = j % vsplit, s = j / vsplit;
-    const int ntile = (n + BB_VT - 1) / BB_VT;
-    const int t0 = (int)(((long)vs * ntile) / vsplit), t1 = (int)(((long)(vs + 1) * ntile) / vsplit);
-    bwdk_block<KS>(phi + (size_t)s * n * k, mass + (size_t)s * n, dA + (size_t)s * k * d, dF + (size_t)s * n * d, n,
-                   k, d, t0, t1, db * BK_COLS);
+    const int dk = dblocks * kblocks;
+    const int db = (q % dk) % dblocks, kb = (q % dk) / dblocks;
+    const int j = (q / dk) * 8 + xs;
+    if (j >= ntiles) return;  // whole workgroup, before any barrier
+    const int split = j % nsplit, s = j / nsplit;
+    const int nst_all = (n + XS - 1) / XS;
+    const int st0 = (int)(((long)split * nst_all) / nsplit), st1 = (int)(((long)(split + 1) * nst_all) / nsplit);
+    x3r_block(phi + (size_t)s * n * k, mass + (size_t)s * n, feat + (size_t)s * n * d, n, k, d, st0 * XS,
+              min(n, st1 * XS), kb, db * 256, out + (size_t)j * k * d);
 }
 
-// Uneven batches: one workgroup per work item.
-// KS <= 5: the dA^T parts take at most 66 KB of LDS, so with the shallow pipeline (<= 128 VGPRs) two
-// workgroups share a CU.
-template <int KS>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(KS <= 5 ? 4 : 1))) void
-proj_bwd_mck_items_kernel(const McItem *__restrict__ items)
+// Uneven batches: one workgroup per work item (items of whole 32-vertex stages only).
+__global__ __launch_bounds__(256, 2) void proj_fwd_x3r_items_kernel(const FwdItem *__restrict__ items)
 {
-    const McItem w = items[blockIdx.x];
-    if (w.t0 >= w.t1) return;  // empty slot of the table (whole workgroup, before any barrier)
-    bwdk_block<KS, (KS <= 5)>(global_ptr(w.phi), global_ptr(w.mass), global_ptr(w.dA), global_ptr(w.dF), w.n, w.k, w.d, w.t0, w.t1, w.dbase);
+    const FwdItem w = items[blockIdx.x];
+    if (w.v0 >= w.v1) return;  // empty slot of the table (whole workgroup, before any barrier)
+    x3r_block(global_ptr(w.phi), global_ptr(w.mass), global_ptr(w.feat), w.n, w.k, w.d, w.v0, w.v1, w.kbase / 64,
+              w.dbase, global_ptr(w.out));
+}
+
+bool sliced_fwd_shape_ok(int64_t n, int64_t k, int64_t d)
+{
+    return sliced_item_shape_ok(k, d) && n % 4 == 0 && n >= 4 * XS;
+}
+
+static int x3_kblocks(int64_t k) { return (int)((k + 63) / 64); }
+
+int sliced_fwd_nsplit(int64_t batch, int64_t n, int64_t k, int64_t d)
+{
+    const int64_t blocks = (d + 255) / 256 * x3_kblocks(k);
+    const int64_t stages = (n + XS - 1) / XS;
+    int64_t ns = (2 * device_cus()) / (batch * blocks);  // two workgroups per CU
+    if (ns > stages / 4) ns = stages / 4;               // keep >= 4 stages per chunk
+    if (ns < 1) ns = 1;
+    return (int)ns;
+}
+
+hipError_t launch_project_sliced(const float *phi, const float *mass, const float *feat, int64_t batch, int64_t n,
+                                 int64_t k, int64_t d, float *A, void *ws, hipStream_t st)
+{
+    const int ns = sliced_fwd_nsplit(batch, n, k, d);
+    float *out = ns > 1 ? (float *)ws : A;
+    const int dblocks = (int)((d + 255) / 256);
+    const int kblocks = x3_kblocks(k);
+    const int ntiles = (int)(batch * ns);
+    const unsigned grid = (unsigned)(8 * dblocks * kblocks * ((ntiles + 7) / 8));
+    hipLaunchKernelGGL(proj_fwd_x3r_kernel, dim3(grid), dim3(256), x3r_lds(), st, phi, mass, feat, (int)n, (int)k, (int)d,
+                       ns, dblocks, kblocks, ntiles, out);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || ns <= 1) return e;
+    return launch_reduce(out, ns, batch, k, d, A, st);
+}
+
+// 64 < k and d close to k (above)
+bool near_square(int64_t k, int64_t d) { return k > 64 && 4 * d < 5 * k; }
+
+bool sliced_item_shape_ok(int64_t k, int64_t d)
+{
+    return near_square(k, d) && k <= kMaxK && k % 4 == 0 && d % 4 == 0;
+}
+
+hipError_t launch_fwd_sliced_items(const FwdItem *items, int nitems, hipStream_t st)
+{
+    if (nitems <= 0) return hipSuccess;
+    hipLaunchKernelGGL(proj_fwd_x3r_items_kernel, dim3((unsigned)nitems), dim3(256), x3r_lds(), st, items);
+    return hipGetLastError();
 }
 
 static int bwdmc_ks(int64_t k) { return (int)((k + 31) / 32); }
@@ -833,11 +875,6 @@ static int bwdmc_ks(int64_t k) { return (int)((k + 31) / 32); }
 bool bf16_bwd_shape_ok(int64_t n, int64_t k, int64_t d)
 {
     return k >= 8 && k <= 256 && k % 8 == 0 && n >= 1 && d >= 1;
-}
-
-bool f32_split_bwd_shape_ok(int64_t n, int64_t k, int64_t d)
-{
-    return k >= 2 && k <= 64 && k % 2 == 0 && n >= 1 && d >= 1;
 }
 
 // vertex ranges per (shape, column block): the fewest that fill whole rounds of the
@@ -900,107 +937,6 @@ hipError_t launch_project_backward_bf16(const uint16_t *phi, const float *mass, 
     case 6: return dispatch_bwdmc<uint16_t, 1, 2, 6>(phi, mass, dA, batch, n, k, d, dF, st);
     case 7: return dispatch_bwdmc<uint16_t, 1, 2, 7>(phi, mass, dA, batch, n, k, d, dF, st);
     default: return dispatch_bwdmc<uint16_t, 1, 2, 8>(phi, mass, dA, batch, n, k, d, dF, st);
-    }
-}
-
-hipError_t launch_project_backward_f32_split(const float *phi, const float *mass, const float *dA, int64_t batch,
-                                             int64_t n, int64_t k, int64_t d, float *dF, hipStream_t st)
-{
-    if (bwdmc_ks(k) == 1) return dispatch_bwdmc<float, 3, 3, 1>(phi, mass, dA, batch, n, k, d, dF, st);
-    return dispatch_bwdmc<float, 3, 3, 2>(phi, mass, dA, batch, n, k, d, dF, st);
-}
-
-bool f32k_bwd_shape_ok(int64_t n, int64_t k, int64_t d)
-{
-    return k > 64 && k <= kMaxK && k % 2 == 0 && n >= 1 && d >= 1;
-}
-
-template <int KS>
-static hipError_t dispatch_bwdk(const float *phi, const float *mass, const float *dA, int64_t batch, int64_t n,
-                                int64_t k, int64_t d, float *dF, hipStream_t st)
-{
-    const size_t lds = bwdk_lds(KS);
-    static int per_cu = 0;  // resident workgroups per CU, queried once (with the LDS limit raised)
-    if (per_cu == 0) {
-        (void)hipFuncSetAttribute((const void *)proj_bwd_mck_kernel<KS>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)lds);
-        int r = 1;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&r, (const void *)proj_bwd_mck_kernel<KS>, 512, lds) !=
-                hipSuccess ||
-            r < 1)
-            r = 1;
-        per_cu = r;
-    }
-    const int dblocks = (int)((d + BK_COLS - 1) / BK_COLS);
-    const int64_t ntile = (n + BB_VT - 1) / BB_VT;
-    const int vsplit = bwdmc_vsplit(batch, dblocks, ntile, per_cu);
-    const int ntasks = (int)(batch * vsplit);
-    const unsigned grid = (unsigned)(8 * dblocks * ((ntasks + 7) / 8));
-    hipLaunchKernelGGL((proj_bwd_mck_kernel<KS>), dim3(grid), dim3(512), lds, st, phi, mass, dA, (int)n, (int)k,
-                       (int)d, vsplit, dblocks, ntasks, dF);
-    return hipGetLastError();
-}
-
-hipError_t launch_project_backward_f32k(const float *phi, const float *mass, const float *dA, int64_t batch,
-                                        int64_t n, int64_t k, int64_t d, float *dF, hipStream_t st)
-{
-    switch (bwdmc_ks(k)) {
-    case 3: return dispatch_bwdk<3>(phi, mass, dA, batch, n, k, d, dF, st);
-    case 4: return dispatch_bwdk<4>(phi, mass, dA, batch, n, k, d, dF, st);
-    case 5: return dispatch_bwdk<5>(phi, mass, dA, batch, n, k, d, dF, st);
-    case 6: return dispatch_bwdk<6>(phi, mass, dA, batch, n, k, d, dF, st);
-    case 7: return dispatch_bwdk<7>(phi, mass, dA, batch, n, k, d, dF, st);
-    case 8: return dispatch_bwdk<8>(phi, mass, dA, batch, n, k, d, dF, st);
-    case 9: return dispatch_bwdk<9>(phi, mass, dA, batch, n, k, d, dF, st);
-    default: return dispatch_bwdk<10>(phi, mass, dA, batch, n, k, d, dF, st);
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Uneven batches: one workgroup per work item
-// ---------------------------------------------------------------------------
-bool mc_item_shape_ok(int64_t k) { return k >= 2 && k <= kMaxK && k % 2 == 0; }
-int mc_item_cols(int64_t k) { return k <= 64 ? BB_COLS : BK_COLS; }
-
-template <int KS>
-static hipError_t launch_mc_items_ks(const McItem *items, int nitems, hipStream_t st)
-{
-    if constexpr (KS <= 2) {
-        const size_t lds = bwdmc_lds(3, KS);
-        static bool attr_set = false;
-        if (!attr_set) {
-            (void)hipFuncSetAttribute((const void *)proj_bwd_mc_items_kernel<KS>,
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            attr_set = true;
-        }
-        hipLaunchKernelGGL((proj_bwd_mc_items_kernel<KS>), dim3((unsigned)nitems), dim3(512), lds, st, items);
-    } else {
-        const size_t lds = bwdk_lds(KS);
-        static bool attr_set = false;
-        if (!attr_set) {
-            (void)hipFuncSetAttribute((const void *)proj_bwd_mck_items_kernel<KS>,
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            attr_set = true;
-        }
-        hipLaunchKernelGGL((proj_bwd_mck_items_kernel<KS>), dim3((unsigned)nitems), dim3(512), lds, st, items);
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_bwd_mc_items(const McItem *items, int nitems, int64_t k, hipStream_t st)
-{
-    if (nitems <= 0) return hipSuccess;
-    switch (bwdmc_ks(k)) {
-    case 1: return launch_mc_items_ks<1>(items, nitems, st);
-    case 2: return launch_mc_items_ks<2>(items, nitems, st);
-    case 3: return launch_mc_items_ks<3>(items, nitems, st);
-    case 4: return launch_mc_items_ks<4>(items, nitems, st);
-    case 5: return launch_mc_items_ks<5>(items, nitems, st);
-    case 6: return launch_mc_items_ks<6>(items, nitems, st);
-    case 7: return launch_mc_items_ks<7>(items, nitems, st);
-    case 8: return launch_mc_items_ks<8>(items, nitems, st);
-    case 9: return launch_mc_items_ks<9>(items, nitems, st);
-    default: return launch_mc_items_ks<10>(items, nitems, st);
     }
 }
 

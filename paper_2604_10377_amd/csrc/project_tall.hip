@@ -1,4 +1,4 @@
-// Forward projection A = Phi^T diag(M) F (Eq. (1)) in float32 for 64 < k <= kMaxK, any n and k, d % 4 == 0, on the
+// Forward projection A = Phi^T diag(M) F (Eq. (1)) in float32 for 64 < k <= kMaxK, 5 k / 4 <= d, any n and k, d % 4 == 0, on the
 // float16 matrix cores (fmap_split.h: both operands as two float16 parts, three products).
 //
 // A workgroup of 8 waves owns every basis row of one vertex chunk and a block of columns, so the features are read
@@ -14,7 +14,8 @@
 // lowered together and the stage is split again.  Loads go through one buffer descriptor per vertex row, whose range
 // ends with the chunk: vertices past its end read as zeros.
 //
-// Instances by k: 4 x 64 columns for k <= 128 (RG = 2 row groups of RT = 4 tiles), 2 x 64 above (RG = 4, RT = 3, 4, 5).
+// Instances by k: 4 x 64 columns for k <= 128 (RG = 2 row groups of RT = 4 tiles; d = 128: RG = 4, RT = 2), 2 x 64 above
+// (RG = 4, RT = 3, 4, 5).
 // What bounds it: at 100000 vertices, k = 300, d = 512 the matrix cores and the vector units together (taking out the
 // products or the splitting alone saves a quarter and an eighth of the time), at k <= 200 the chain of one stage
 // (latencies of LDS and memory at two waves per SIMD).  Alternating products and splitting within a wave gave 3% to 6%
@@ -325,18 +326,23 @@ __global__ __launch_bounds__(TT, 2) void proj_fwd_tall_items_kernel(const FwdIte
                        global_ptr(w.out));
 }
 
-// Instances by k: rows in blocks of 16 RG RT
-int tall_class(int64_t k) { return k <= 128 ? 0 : (k <= 192 ? 1 : (k <= 256 ? 2 : 3)); }
-int tall_cols(int64_t k) { return k <= 128 ? Tall<2, 4>::COLS : Tall<4, 4>::COLS; }
+// Instances by k (rows in blocks of 16 RG RT); up to k = 128 with 256 columns per workgroup, or 128 where that leaves
+// fewer idle columns (d = 128: half of the 256 would be idle)
+int tall_class(int64_t k, int64_t d)
+{
+    if (k <= 128) return (d + 127) / 128 * 128 < (d + 255) / 256 * 256 ? 1 : 0;
+    return k <= 192 ? 2 : (k <= 256 ? 3 : 4);
+}
+int tall_cols(int64_t k, int64_t d) { return tall_class(k, d) == 0 ? Tall<2, 4>::COLS : Tall<4, 4>::COLS; }
 
 bool tall_shape_ok(int64_t n, int64_t k, int64_t d)
 {
-    return k > 64 && k <= kMaxK && d >= 4 && d % 4 == 0 && d <= (1 << 20) && n >= 4 * TS;
+    return k > 64 && k <= kMaxK && !near_square(k, d) && d >= 4 && d % 4 == 0 && d <= (1 << 20) && n >= 4 * TS;
 }
 
 int tall_nsplit(int64_t batch, int64_t n, int64_t k, int64_t d, int64_t cap)
 {
-    const int64_t base = batch * ((d + tall_cols(k) - 1) / tall_cols(k));
+    const int64_t base = batch * ((d + tall_cols(k, d) - 1) / tall_cols(k, d));
     const int64_t stages = (n + TS - 1) / TS;
     const int64_t slots = device_cus();  // one workgroup per CU (LDS)
     int64_t most = std::min<int64_t>(stages / 4, cap);  // at least 4 stages per chunk
@@ -377,10 +383,11 @@ hipError_t launch_project_tall(const float *phi, const float *mass, const float 
 {
     float *out = ns > 1 ? (float *)ws : A;
     hipError_t e;
-    switch (tall_class(k)) {
+    switch (tall_class(k, d)) {
     case 0: e = dispatch_tall<2, 4>(phi, mass, feat, batch, n, k, d, ns, out, st); break;
-    case 1: e = dispatch_tall<4, 3>(phi, mass, feat, batch, n, k, d, ns, out, st); break;
-    case 2: e = dispatch_tall<4, 4>(phi, mass, feat, batch, n, k, d, ns, out, st); break;
+    case 1: e = dispatch_tall<4, 2>(phi, mass, feat, batch, n, k, d, ns, out, st); break;
+    case 2: e = dispatch_tall<4, 3>(phi, mass, feat, batch, n, k, d, ns, out, st); break;
+    case 3: e = dispatch_tall<4, 4>(phi, mass, feat, batch, n, k, d, ns, out, st); break;
     default: e = dispatch_tall<4, 5>(phi, mass, feat, batch, n, k, d, ns, out, st); break;
     }
     if (e != hipSuccess || ns <= 1) return e;
@@ -406,8 +413,9 @@ hipError_t launch_fwd_tall_items(const FwdItem *items, int nitems, int cls, hipS
     if (nitems <= 0) return hipSuccess;
     switch (cls) {
     case 0: return dispatch_tall_items<2, 4>(items, nitems, st);
-    case 1: return dispatch_tall_items<4, 3>(items, nitems, st);
-    case 2: return dispatch_tall_items<4, 4>(items, nitems, st);
+    case 1: return dispatch_tall_items<4, 2>(items, nitems, st);
+    case 2: return dispatch_tall_items<4, 3>(items, nitems, st);
+    case 3: return dispatch_tall_items<4, 4>(items, nitems, st);
     default: return dispatch_tall_items<4, 5>(items, nitems, st);
     }
 }

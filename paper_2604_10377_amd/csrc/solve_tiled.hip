@@ -4,7 +4,7 @@
 // A blocked left-looking Cholesky: the lower triangle of S_i = K + lambda diag(D_i)
 // is cut into 32x32 tiles, and the right-hand side is appended as one extra row
 // (index k_x), so the factorisation performs the forward substitution L y = r
-// on the fly.  A 4-wave workgroup keeps the active block column in LDS and the
+// on the fly.  A workgroup of 4 or 8 waves keeps the active block column in LDS and the
 // finished tiles in its slot of the workspace, and several systems share a CU
 // (rowsolve_ll_kernel, described below).
 
@@ -19,7 +19,6 @@ namespace {
 
 constexpr int TLD = 33;                 // row stride of a stored tile (odd: conflict-free columns)
 constexpr int TSZ = 32 * TLD;           // floats per tile
-constexpr int LDD = 36;                 // row stride of the aligned copy of the diagonal tile
 
 __device__ __forceinline__ int packed_col_t(int c, int m) { return c * m - (c * (c - 1)) / 2; }
 __device__ __forceinline__ float uniform_f(float v)
@@ -30,114 +29,152 @@ __device__ __forceinline__ float uniform_f(float v)
 __device__ __forceinline__ int tile_index(int I, int J, int TR) { return J * TR - (J * (J - 1)) / 2 + (I - J); }
 
 // LDS scratch of the diagonal-tile routine below (floats, 16-byte aligned)
-constexpr int DIAG_LR = 32 * LDD;
+constexpr int DIAG_LR = 16 * 16;
+
+// acc -= x_Q y, where x_Q is lane Q of the own row of 16 lanes (a DPP row broadcast in the
+// multiply-add; left to the compiler each becomes a move of its own, all held in registers).  x is at least two
+// instructions old.
+template <int Q>
+__device__ __forceinline__ void row_fnma(float &acc, float x, float y)
+{
+    asm volatile("v_fmac_f32_dpp %0, %1, -%2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
+                 : "+v"(acc) : "v"(x), "v"(y), "n"(Q));
+}
+// The subtractions of column P that the next pivot does not need: item I of diag_rest_count(P), in the order in
+// which the following columns need them (x: the column's entries, y: the lane's factor).
+constexpr int diag_rest_count(int P) { return P < 0 ? 0 : (P < 16 ? 15 : (P < 30 ? 30 - P : 0)); }
+template <int P, int I, int END>
+__device__ __forceinline__ void diag_rest(float (&s)[16], float x, float y)
+{
+    if constexpr (I < END && I < diag_rest_count(P)) {
+        row_fnma<(P + 2 + I) & 15>(s[(P + 2 + I) & 15], x, y);
+        diag_rest<P, I + 1, END>(s, x, y);
+    } else {
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// Column C of the factor and column C % 16 of its diagonal block's inverse; see diag_factor_inverse.  pv: the
+// pivot.  Dcol: where the own row of the factor goes, Mcol: the own column of the inverse; other lanes have
+// addresses there whose contents are not needed.  From pivot to pivot this is a chain of dependent instructions;
+// what column P leaves to do (x, y: its values) goes into its gaps.
+template <int C, int P>
+__device__ __forceinline__ void diag_column(float (&s)[16], float *Dcol, float *Mcol, int row16, float &pv, float &x,
+                                            float &y)
+{
+    constexpr int J = C & 15, N = (C + 1) & 15;
+    const float r = __builtin_amdgcn_rsqf(pv);
+    diag_rest<P, 0, 3>(s, x, y);
+    float l = s[J] * r, l2, xn;
+    asm volatile("v_mov_b32 %0, %1" : "=v"(l2) : "v"(l));
+    float ri = __builtin_amdgcn_rcpf(pv * r);  // of the diagonal entry of L: scales the inverse
+    diag_rest<P, 3, 6>(s, x, y);
+    if constexpr (C < 16) {
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l), __float_as_uint(l2), false, false);
+        l = __uint_as_float(sw[0]);
+        float l3;
+        asm volatile("v_mov_b32 %0, %2\n\tv_mov_b32 %1, %2" : "=&v"(l2), "=&v"(l3) : "v"(l));
+        diag_rest<P, 6, 9>(s, x, y);
+        const auto rw = __builtin_amdgcn_permlane16_swap(__float_as_uint(l2), __float_as_uint(l3), false, false);
+        xn = __uint_as_float(row16 == 3 ? rw[1] : rw[0]);
+    } else {
+        float l3;
+        asm volatile("v_mov_b32 %0, %1" : "=v"(l3) : "v"(l));
+        diag_rest<P, 6, 9>(s, x, y);
+        xn = __uint_as_float(__builtin_amdgcn_permlane16_swap(__float_as_uint(l2), __float_as_uint(l3), false, false)[1]);
+    }
+    const float yn = row16 == 2 ? s[J] * ri : l;
+    Dcol[C] = l;
+    Mcol[J * TLD] = yn;
+    diag_rest<P, 9, 11>(s, x, y);
+    asm volatile("s_nop 1" : "+v"(xn));  // before a DPP operand
+    if constexpr (C < 31) {
+        row_fnma<N>(s[N], xn, yn);  // the next pivot's column
+        diag_rest<P, 11, 12>(s, x, y);
+        asm volatile("s_nop 0" : "+v"(s[N]));  // before a lane read of an asm result
+        pv = uniform_f(readlane(s[N], C < 15 ? C + 1 : 33 + C));
+    }
+    diag_rest<P, C < 31 ? 12 : 11, 16>(s, x, y);
+    x = xn;
+    y = yn;
+}
+
+// Columns C0 .. C0 + 15
+template <int C0, int I = 0>
+__device__ __forceinline__ void diag_columns(float (&s)[16], float *Dcol, float *Mcol, int row16, float &pv, float &x,
+                                             float &y)
+{
+    if constexpr (I < 16) {
+        diag_column<C0 + I, I == 0 ? -1 : C0 + I - 1>(s, Dcol, Mcol, row16, pv, x, y);
+        diag_columns<C0, I + 1>(s, Dcol, Mcol, row16, pv, x, y);
+    } else {
+        diag_rest<C0 + 15, 0, 16>(s, x, y);
+    }
+}
 
 // One wave (64 lanes): Cholesky factor of the 32 x 32 diagonal tile Dt (rows at stride TLD, lower part, the
 // first kxl columns; rows past kxl, e.g. the appended right-hand side row, are eliminated with them), and the
 // inverse of the factor, Minv[q][c] at q * TLD + c (rows and columns past kxl zero).  Returns 0, or 1 + the
 // first column whose pivot is not positive and finite (then Dt and Minv hold garbage).
-//   * factor: lane r holds row r; columns in blocks of 8, each block's columns in the lanes' registers with
-//     the entries L_qc taken by readlane, then the block's rank-8 update of the later columns from one LDS
-//     broadcast of the block (rows of the block column, 16-byte reads).  Every step is branch-free (a
-//     column past kxl or after a failure multiplies by 0): branches per column made the compiler copy the
-//     row registers at every join;
-//   * inverse: the two 16 x 16 diagonal blocks of L^{-1}, one per half of lanes 0..31 (lane = column), from
-//     the rows of L in LDS (16-byte reads, each half at its own address), then the lower-left block
-//     M21 = -M22 L21 M11 as two 16 x 16 x 16 products on the float32 matrix cores.
-// Lr ([32][LDD], 16-byte aligned) is scratch: the block broadcasts of the factor, then the rows of L, then
-// (over rows 0..7, free by then) the product L21 M11.
+//   * lane (i, g), i = lane % 16 of row g of lanes, holds 16 entries in registers, and step c subtracts from each a
+//     DPP row broadcast times a value of the lane: 16 instructions for all of the following.  While c < 16, rows 0
+//     and 1 of lanes hold columns 0..15 of tile rows i and 16 + i, row 3 holds columns 16..31 of tile row 16 + i,
+//     and row 2 column i of the inverse of the upper diagonal block, which starts as a column of the identity and
+//     takes the same broadcasts.  From c = 16 on, row 3 goes on with tile row 16 + i and row 2 starts on the lower
+//     block's inverse.  Column c is scaled where it is held and spread to the other rows of lanes by permlane
+//     swaps.  Finished columns go to LDS at once; their registers hold garbage from then on.  Columns past kxl are
+//     eliminated as well and come out as garbage, which reaches neither the columns before them nor Minv;
+//   * then the lower-left block M21 = -M22 L21 M11 as two 16 x 16 x 16 products on the float32 matrix cores.
+// Bound by the instructions of the one wave, some 30 per column at five cycles each (8-byte encodings), and what
+// stands around the columns: 8200 cycles alone on its SIMD; 14400 when each entry L_qc was a lane read and the
+// inverse followed the factor.
+// Lr (16 x 16) is scratch for the product L21 M11.
 __device__ __forceinline__ int diag_factor_inverse(float *Dt, float *Lr, float *Minv, int kxl, int lane)
 {
     // the lane index made opaque, so its masks are formed where used, not hoisted into registers
     asm volatile("" : "+v"(lane));
-    const int l32 = lane & 31;
-    float sr[32];
-#pragma unroll
-    for (int q = 0; q < 32; ++q) sr[q] = (lane < 32) ? Dt[l32 * TLD + q] : 0.f;
-    int fail = 0;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-#pragma unroll
-        for (int c = 8 * b; c < 8 * b + 8; ++c) {
-            const float pv = uniform_f(readlane(sr[c], c));
-            const bool act = c < kxl && fail == 0;
-            const bool bad = !(pv > 0.f) || !isfinite(pv);
-            fail = (act && bad) ? c + 1 : fail;
-            const bool go = act && !bad;
-            const float l0 = sr[c] * __builtin_amdgcn_rsqf(go ? pv : 1.f);
-            sr[c] = go ? l0 : sr[c];
-            const float l = go ? l0 : 0.f;
-#pragma unroll
-            for (int q = c + 1; q < 8 * b + 8; ++q) sr[q] -= l * readlane(l, q);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        // columns past kxl take no part (zeroed: nothing reads them afterwards)
-#pragma unroll
-        for (int u = 0; u < 8; ++u) sr[8 * b + u] = (8 * b + u < kxl) ? sr[8 * b + u] : 0.f;
-        if (b < 3) {
-            if (lane < 32) {
-                *reinterpret_cast<f32x4 *>(&Lr[8 * l32]) = f32x4{sr[8 * b], sr[8 * b + 1], sr[8 * b + 2], sr[8 * b + 3]};
-                *reinterpret_cast<f32x4 *>(&Lr[8 * l32 + 4]) =
-                    f32x4{sr[8 * b + 4], sr[8 * b + 5], sr[8 * b + 6], sr[8 * b + 7]};
-            }
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int q = 8 * b + 8; q < 32; ++q) {
-                const f32x4 x0 = *reinterpret_cast<const f32x4 *>(&Lr[8 * q]);
-                const f32x4 x1 = *reinterpret_cast<const f32x4 *>(&Lr[8 * q + 4]);
-#pragma unroll
-                for (int u = 0; u < 4; ++u) sr[q] -= sr[8 * b + u] * x0[u];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) sr[q] -= sr[8 * b + 4 + u] * x1[u];
-                // finished here: left free, the compiler defers later columns' updates past the next block
-                // and keeps all their loaded rows live at once
-                asm volatile("" : "+v"(sr[q]));
-            }
-            __builtin_amdgcn_wave_barrier();
-        }
-    }
-    fail = __builtin_amdgcn_readfirstlane(fail);
-    if (fail != 0) return fail;
-    if (lane < 32) {
-#pragma unroll
-        for (int q = 0; q < 32; ++q) Dt[l32 * TLD + q] = sr[q];
-#pragma unroll
-        for (int q = 0; q < 32; q += 4)
-            *reinterpret_cast<f32x4 *>(&Lr[l32 * LDD + q]) = f32x4{sr[q], sr[q + 1], sr[q + 2], sr[q + 3]};
-    }
-    __builtin_amdgcn_wave_barrier();
+    const int l32 = lane & 31, i16 = lane & 15, k4 = lane >> 4;
+    float s[16];
     {
-        const int hb = (lane >> 4) & 1, jj = lane & 15;
-        const float *Lb = Lr + 16 * hb * LDD + 16 * hb;
-        float mb[16];
+        const float *D = Dt + l32 * TLD + (lane < 32 ? 0 : 16);
 #pragma unroll
-        for (int qq = 0; qq < 16; ++qq) {
-            float t = (qq == jj) ? 1.f : 0.f;
-            f32x4 row[4];
+        for (int q = 0; q < 16; ++q) s[q] = D[q];
+        // all loaded before any is replaced (else a branch around each load)
+        asm volatile(""
+                     : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]), "+v"(s[4]), "+v"(s[5]), "+v"(s[6]), "+v"(s[7]),
+                       "+v"(s[8]), "+v"(s[9]), "+v"(s[10]), "+v"(s[11]), "+v"(s[12]), "+v"(s[13]), "+v"(s[14]),
+                       "+v"(s[15]));
 #pragma unroll
-            for (int g = 0; g <= qq / 4; ++g) row[g] = *reinterpret_cast<const f32x4 *>(&Lb[qq * LDD + 4 * g]);
+        for (int q = 0; q < 16; ++q) s[q] = k4 == 2 ? (q == i16 ? 1.f : 0.f) : s[q];
+    }
+    float pv = uniform_f(readlane(s[0], 0)), x = 0.f, y = 0.f;
+    // rows 2 and 3 of lanes write copies of rows 0 and 1 of Dt; all but row 2 write to the rows of Minv filled later
+    diag_columns<0>(s, Dt + l32 * TLD, Minv + (k4 == 2 ? 0 : 16 * TLD) + i16, k4, pv, x, y);
 #pragma unroll
-            for (int tt = 0; tt < qq; ++tt) t -= row[tt / 4][tt % 4] * mb[tt];
-            mb[qq] = (16 * hb + qq < kxl) ? t * __builtin_amdgcn_rcpf(row[qq / 4][qq % 4]) : 0.f;
-            asm volatile("" : "+v"(mb[qq]));
-        }
-        if (lane < 32) {
+    for (int q = 0; q < 16; ++q) s[q] = k4 == 2 ? (q == i16 ? 1.f : 0.f) : s[q];
+    // row 3 writes Dt, the others the scratch; row 2 writes the lower block of Minv, the others the block on its left
+    diag_columns<16>(s, k4 == 3 ? Dt + l32 * TLD : Lr + i16, Minv + 16 * TLD + (k4 == 2 ? 16 : 0) + i16, k4, pv, x, y);
+    // a pivot that is zero, negative, infinite or NaN times its reciprocal root is NaN, and so are the later ones
+    const float dg = Dt[l32 * TLD + l32];
+    const unsigned bad = (unsigned)__ballot(lane < kxl && dg != dg);  // kxl <= 32
+    if (bad != 0u) return __ffs((int)bad);
+    // the block right of M11 is zero, and so are rows and columns past kxl (the last tile's)
+    if (lane < 16) {
 #pragma unroll
-            for (int qq = 0; qq < 16; ++qq) {
-                Minv[(16 * hb + qq) * TLD + 16 * hb + jj] = mb[qq];
-                Minv[(16 * hb + qq) * TLD + 16 * (1 - hb) + jj] = 0.f;  // upper block; the lower one follows
-            }
-        }
+        for (int q = 0; q < 16; ++q) Minv[q * TLD + 16 + lane] = 0.f;
+    }
+    if (kxl < 32) {
+        for (int q = min(kxl, 32); q < 32; ++q)
+            if (lane < 32) Minv[q * TLD + lane] = 0.f;
     }
     __builtin_amdgcn_wave_barrier();
     {
         // 16 x 16 x 4 float32 matrix-core steps: lane (i, k) = (lane % 16, lane / 16) supplies A[i][k] and
         // B[k][i]; the result row 4 (lane / 16) + r, column lane % 16 is register r
-        const int i16 = lane & 15, k4 = lane >> 4;
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int st = 0; st < 4; ++st)  // T = L21 M11
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(Lr[(16 + i16) * LDD + 4 * st + k4],
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(Dt[(16 + i16) * TLD + 4 * st + k4],
                                                        Minv[(4 * st + k4) * TLD + i16], acc, 0, 0, 0);
 #pragma unroll
         for (int r = 0; r < 4; ++r) Lr[(4 * k4 + r) * 16 + i16] = acc[r];
@@ -148,7 +185,7 @@ __device__ __forceinline__ int diag_factor_inverse(float *Dt, float *Lr, float *
             acc2 = __builtin_amdgcn_mfma_f32_16x16x4f32(Minv[(16 + i16) * TLD + 16 + 4 * st + k4],
                                                         Lr[(4 * st + k4) * 16 + i16], acc2, 0, 0, 0);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) Minv[(16 + 4 * k4 + r) * TLD + i16] = -acc2[r];
+        for (int r = 0; r < 4; ++r) Minv[(16 + 4 * k4 + r) * TLD + i16] = 16 + 4 * k4 + r < kxl ? -acc2[r] : 0.f;
     }
     __builtin_amdgcn_wave_barrier();
     return 0;
@@ -163,7 +200,7 @@ enum { RT_FWD = 0, RT_BWD_RECOMPUTE = 2 };
 //
 // Keeping every tile of a system in LDS (118 KB at k_x = 200) would hold a CU
 // to one system, idle while one wave factorises a diagonal tile.  Here a
-// workgroup of 4 waves keeps only the active block column in LDS (40 KB in all
+// workgroup of 4 (8) waves keeps only the active block column in LDS (37 KB in all
 // at k_x = 200) and writes each finished tile L_Ip, and the inverse of each
 // diagonal tile, to its own slot of the workspace (32 x 32 row-major tiles in
 // the lower-triangle order of the tile grid; the diagonal positions hold the
@@ -177,7 +214,9 @@ enum { RT_FWD = 0, RT_BWD_RECOMPUTE = 2 };
 //      registers: lane (m, h) supplies row m, columns 16 h .. 16 h + 15, with
 //      the K order of the matrix-core steps permuted alike for both operands.
 //      One wave updates the diagonal tile and goes on to step 3 at once, while
-//      the others update the tiles below it; the updated tiles go to LDS;
+//      the others update the tiles below it, and the next diagonal tile as far as
+//      it goes, so that the serial wave of the next step starts one product short
+//      of done; the updated tiles go to LDS;
 //   3. that wave factorises the diagonal tile and forms its inverse
 //      (diag_factor_inverse);
 //   4. the panel L_Ip = S_Ip L_pp^{-T} on the matrix cores, stored to the slot.
@@ -186,22 +225,26 @@ enum { RT_FWD = 0, RT_BWD_RECOMPUTE = 2 };
 // blocks' contribution L_Ip^T c_I as matrix-vector products over the slot's
 // tiles, then c_p = L_pp^{-T} v as one product with the stored inverse.
 // ---------------------------------------------------------------------------
-constexpr int LLW = 4;          // waves per workgroup
+// Waves per workgroup: where two workgroups fill a CU's workspace slots (k_x >= 224), eight waves each; four where
+// four do.  Eight shorten the serial path of one system, and the registers allow 16 waves per CU either way.
+// k = 256, one system per CU: the factorisation took 218000 cycles with four waves, 187000 with eight.
+constexpr int ll_waves(int TRM) { return TRM == 10 ? 8 : 4; }
 constexpr int LTS = 32 * 32;    // floats per tile in the workspace slot
 
-constexpr int ll_lds_floats(int TRM) { return TRM * TSZ + TSZ + DIAG_LR + 2 * TRM * 32 + LLW * 32 + LLW + 4; }
+constexpr int ll_lds_floats(int TRM) { return TRM * TSZ + TSZ + DIAG_LR + 2 * TRM * 32 + ll_waves(TRM) + 4; }
 
 __device__ __forceinline__ f32x4 ldg4(const float *p) { return *reinterpret_cast<const f32x4 *>(p); }
 
 // STORE: the factor is written to Lout (forward mode with stored factors).
 template <int TMAX, int MODE, bool STORE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TMAX == 10 ? 2 : 4))) void rowsolve_ll_kernel(
+__global__ __launch_bounds__(64 * ll_waves(TMAX)) __attribute__((amdgpu_waves_per_eu(4))) void rowsolve_ll_kernel(
     const float *__restrict__ K, const float *__restrict__ rhs, const float *__restrict__ ex,
     const float *__restrict__ ey, const float *__restrict__ lam, int mask_kind, float gamma, int kx, int ky, int nsys,
     float *out, float *__restrict__ Lout, int *__restrict__ info, const float *__restrict__ Cfwd,
     float *__restrict__ dlam_part, float *__restrict__ Lws, int cus, const int *__restrict__ only)
 {
     constexpr int TRM = TMAX;
+    constexpr int NW = ll_waves(TMAX), NTHR = 64 * NW;
     constexpr int NTL = TMAX * (TMAX + 1) / 2;
     extern __shared__ __align__(16) float smem[];
     float *bc = smem;                    // tile j: rows 32 (p + j) .. 32 (p + j) + 31 of block column p
@@ -209,15 +252,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TMAX == 10 
     float *s_lr = s_minv + TSZ;          // scratch of the diagonal-tile routine
     float *s_dval = s_lr + DIAG_LR;      // mask row D_i
     float *s_vec = s_dval + TRM * 32;    // y, then c
-    float *s_part = s_vec + TRM * 32;    // [LLW][32]
-    float *s_red = s_part + LLW * 32;    // [LLW]
-    int *s_fail = reinterpret_cast<int *>(s_red + LLW);
+    float *s_red = s_vec + TRM * 32;     // [NW]
+    int *s_fail = reinterpret_cast<int *>(s_red + NW);
     float *Ls = Lws + (size_t)blockIdx.x * NTL * LTS;
 
     const int tid = threadIdx.x, wave = tid >> 6;
     // the wave that runs the serial diagonal steps: different for the workgroups that share a CU (ids one grid
     // round of CUs apart), so that their diagonal chains do not all land on the same SIMD
-    const int dwave = (blockIdx.x / cus) % LLW;
+    const int dwave = (blockIdx.x / cus) % NW;
     const int T = (kx + 31) >> 5;   // column tiles
     const int TR = (kx + 32) >> 5;  // tile rows (row kx is the right-hand side)
     const int AR = kx >> 5, ar = kx & 31;
@@ -237,17 +279,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TMAX == 10 
         mp.inv_scale = 1.f;
         if (mask_kind == 1) {
             float mx = -INFINITY;
-            for (int q = tid; q < kx; q += 256) mx = fmaxf(mx, ex[(size_t)p * kx + q]);
-            for (int q = tid; q < ky; q += 256) mx = fmaxf(mx, ey[(size_t)p * ky + q]);
+            for (int q = tid; q < kx; q += NTHR) mx = fmaxf(mx, ex[(size_t)p * kx + q]);
+            for (int q = tid; q < ky; q += NTHR) mx = fmaxf(mx, ey[(size_t)p * ky + q]);
             mx = wave_max(mx);
             if (lane == 0) s_red[wave] = mx;
             __syncthreads();
-            mx = fmaxf(fmaxf(s_red[0], s_red[1]), fmaxf(s_red[2], s_red[3]));
+            mx = s_red[0];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) mx = fmaxf(mx, s_red[w]);
             if ((!(mx > 0.f) || !isfinite(mx)) && fail0 == 0) fail0 = -2;
             mp.inv_scale = 1.f / mx;
         }
         const float muy = ey[(size_t)p * ky + i];
-        for (int q = tid; q < TRM * 32; q += 256) {
+        for (int q = tid; q < TRM * 32; q += NTHR) {
             const float dv = (q < kx && fail0 != -2) ? mask_entry(muy, ex[(size_t)p * kx + q], mp) : 0.f;
             s_dval[q] = dv;
             s_vec[q] = 0.f;
@@ -275,54 +319,69 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TMAX == 10 
             // Each wave loads its own tiles straight into its accumulators (no barrier between the loads and
             // the update).  The diagonal-tile wave takes the diagonal tile alone and goes straight on to
             // factorise it (step 3, its own LDS writes, no barrier), while the other waves take the tiles
-            // below it.
+            // below it and, from step 1 on, as tile nt the next diagonal tile less its products of the blocks
+            // before ps: the diagonal-tile wave then starts step ps + 1 from that, one product short.  It is
+            // passed on in a tile that the shrinking block column no longer uses, the last one and the one before
+            // it in turn (the last is free from step 1 on, the other from step 2).
             {
-                const int j0 = wave == dwave ? 0 : 1 + (wave - dwave + LLW - 1) % LLW;
-                const int jstep = wave == dwave ? nt : LLW - 1;
-                for (int j = j0; j < nt; j += jstep) {
+                const int j0 = wave == dwave ? 0 : 1 + (wave - dwave + NW - 1) % NW;
+                const int jend = wave == dwave ? 1 : nt + (ps >= 1 && ps + 1 < T ? 1 : 0);
+                for (int j = j0; j < jend; j += NW - 1) {
+                    const bool ahead = j == nt;           // the next diagonal tile
+                    const bool begun = j == 0 && ps >= 2;  // the diagonal tile begun in the step before
+                    const int cb = ahead ? ps + 1 : ps;   // block column of the tile
+                    const int q0 = begun ? ps - 1 : 0;
                     // lane-derived values formed per tile (kept out of the registers held across the update)
                     int ln = lane;
                     asm volatile("" : "+v"(ln));
                     const int l32 = ln & 31, half = ln >> 5;
-                    const int col = 32 * ps + l32;
+                    const int col = 32 * cb + l32;
                     const int colc = min(col, kx - 1);
-                    float *X = bc + j * TSZ;
-                    const int I = ps + j;
+                    float *X = bc + (ahead ? TRM - 1 - ((ps + 1) & 1) : j) * TSZ;
+                    const int I = ahead ? cb : ps + j;
                     const int off = l32 * 32 + 16 * half;
                     // this tile's entries of K (unconditional loads from clamped addresses) and the first
                     // tile pair of the update, all in flight together
                     f32x16 acc;
+                    if (begun) {
+                        const float *B = bc + (TRM - 1 - (ps & 1)) * TSZ;
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int rowc = min(32 * I + acc32_row(r, ln), kx);
-                        acc[r] = *(rowc == kx ? rp + colc : Kp + (size_t)rowc * kx + colc);
+                        for (int r = 0; r < 16; ++r) acc[r] = B[acc32_row(r, ln) * TLD + l32];
+                    } else {
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            const int rowc = min(32 * I + acc32_row(r, ln), kx);
+                            acc[r] = *(rowc == kx ? rp + colc : Kp + (size_t)rowc * kx + colc);
+                        }
                     }
                     f32x4 a0[4], b0[4];
                     if (ps > 0) {
-                        const float *ap = Ls + (size_t)tile_index(I, 0, TR) * LTS + off;
-                        const float *bp = Ls + (size_t)tile_index(ps, 0, TR) * LTS + off;
+                        const float *ap = Ls + (size_t)tile_index(I, q0, TR) * LTS + off;
+                        const float *bp = Ls + (size_t)tile_index(cb, q0, TR) * LTS + off;
 #pragma unroll
                         for (int u = 0; u < 4; ++u) {
                             a0[u] = ldg4(ap + 4 * u);
                             b0[u] = ldg4(bp + 4 * u);
                         }
                     }
-                    const float dsh = lsh * s_dval[col];  // the shift of this column's diagonal entry
+                    if (!begun) {
+                        const float dsh = lsh * s_dval[col];  // the shift of this column's diagonal entry
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int row = 32 * I + acc32_row(r, ln);
-                        const float v = acc[r];
-                        float x = 0.f;
-                        if (row < kx && col < kx) x = v + (row == col ? dsh : 0.f);
-                        else if (row == kx && col < kx) x = v;
-                        acc[r] = x;
+                        for (int r = 0; r < 16; ++r) {
+                            const int row = 32 * I + acc32_row(r, ln);
+                            const float v = acc[r];
+                            float x = 0.f;
+                            if (row < kx && col < kx) x = v + (row == col ? dsh : 0.f);
+                            else if (row == kx && col < kx) x = v;
+                            acc[r] = x;
+                        }
                     }
                     // whole tile pairs (16 floats of each operand per lane), the next pair in flight while one is
                     // multiplied
-                    for (int q = 0; q < ps; ++q) {
+                    for (int q = q0; q < ps; ++q) {
                         const int qn = min(q + 1, ps - 1);
                         const float *ap = Ls + (size_t)tile_index(I, qn, TR) * LTS + off;
-                        const float *bp = Ls + (size_t)tile_index(ps, qn, TR) * LTS + off;
+                        const float *bp = Ls + (size_t)tile_index(cb, qn, TR) * LTS + off;
                         f32x4 a1[4], b1[4];
 #pragma unroll
                         for (int u = 0; u < 4; ++u) {
@@ -345,7 +404,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TMAX == 10 
             }
             // ---- 3. diagonal tile and its inverse (one wave) ----------------------------------
             if (wave == dwave) {
+                __builtin_amdgcn_s_setprio(3);  // the one serial step: ahead of the waves that share its SIMD
                 const int f = diag_factor_inverse(bc, s_lr, s_minv, kxl, lane);
+                __builtin_amdgcn_s_setprio(0);
                 if (f != 0) {
                     if (lane == 0) *s_fail = 32 * ps + f;
                 } else {
@@ -361,13 +422,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TMAX == 10 
             if (STORE) {
                 // L_pp into the packed factor, consecutive threads on consecutive rows of a column
                 float *Lo = Lout + ((size_t)p * ky + i) * (size_t)(kx * (kx + 1) / 2);
-                for (int e = tid; e < 1024; e += 256) {
+                for (int e = tid; e < 1024; e += NTHR) {
                     const int c = e >> 5, r = e & 31;
                     if (r >= c && r < kxl) Lo[packed_col_t(32 * ps + c, kx) + (r - c)] = bc[r * TLD + c];
                 }
             }
             // ---- 4. panel L_Ip = S_Ip Minv^T (I > ps) -----------------------------------------------
-            for (int j = 1 + wave; j < nt; j += LLW) {
+            for (int j = 1 + wave; j < nt; j += NW) {
                 const int I = ps + j;
                 const float *X = bc + j * TSZ;
                 f32x16 nv = zero16();
@@ -394,7 +455,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TMAX == 10 
                 // the block column's tiles of L below the diagonal into the packed factor, consecutive threads on
                 // consecutive rows of one column
                 float *Lo = Lout + ((size_t)p * ky + i) * (size_t)(kx * (kx + 1) / 2);
-                for (int e = tid; e < (nt - 1) * 1024; e += 256) {
+                for (int e = tid; e < (nt - 1) * 1024; e += NTHR) {
                     const int j = 1 + (e >> 10), c = (e >> 5) & 31, r = e & 31;
                     const int R = 32 * (ps + j) + r, Cc = 32 * ps + c;
                     if (R < kx && Cc < kx) Lo[packed_col_t(Cc, kx) + R - Cc] = bc[j * TSZ + r * TLD + c];
@@ -414,16 +475,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TMAX == 10 
             asm volatile("" : "+v"(tb));
             const int tid = tb, lane = tb & 63;
             const int l32 = lane & 31, half = lane >> 5;
-            for (int e0 = tid; e0 < T * 1024; e0 += 8 * 256) {
+            for (int e0 = tid; e0 < T * 1024; e0 += 8 * NTHR) {
                 float v[8];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
-                    const int e = min(e0 + 256 * u, T * 1024 - 1);
+                    const int e = min(e0 + NTHR * u, T * 1024 - 1);
                     v[u] = Ls[(size_t)tile_index(e >> 10, e >> 10, TR) * LTS + (e & 1023)];
                 }
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
-                    const int e = e0 + 256 * u;
+                    const int e = e0 + NTHR * u;
                     if (e < T * 1024) bc[(e >> 10) * TSZ + ((e >> 5) & 31) * TLD + (e & 31)] = v[u];
                 }
             }
@@ -454,7 +515,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TMAX == 10 
                     z += __shfl_xor(z, 32, 64);
                     if (half == 0) s_vec[32 * wave + l32] -= z;
                 }
-                for (int q = wave + LLW; q < ps; q += LLW) {  // further earlier blocks (k_x > 128)
+                for (int q = wave + NW; q < ps; q += NW) {  // further earlier blocks
                     const float *Lt = Ls + (size_t)tile_index(ps, q, TR) * LTS;
 #pragma unroll
                     for (int u = 0; u < 16; ++u) lv[u] = Lt[(2 * u + half) * 32 + l32];
@@ -469,11 +530,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TMAX == 10 
         }
 
         // ---- outputs ----------------------------------------------------------------------
-        for (int q = tid; q < kx; q += 256) out[((size_t)p * ky + i) * kx + q] = fail == 0 ? s_vec[q] : NAN;
+        for (int q = tid; q < kx; q += NTHR) out[((size_t)p * ky + i) * kx + q] = fail == 0 ? s_vec[q] : NAN;
         if (info && tid == 0) info[(size_t)p * ky + i] = fail;
         if (MODE != RT_FWD && dlam_part) {
             float term = 0.f;
-            for (int q = tid; q < kx; q += 256)
+            for (int q = tid; q < (tid < 256 ? kx : 0); q += 256)  // by 256 threads whatever the waves: one order
                 term += (fail == 0 ? s_vec[q] : NAN) * s_dval[q] * Cfwd[((size_t)p * ky + i) * kx + q];
             term = wave_sum(term);
             if (lane == 0) s_red[wave] = term;
@@ -658,12 +719,13 @@ static void launch_ll(const float *K, const float *rhs, const float *ex, const f
     }
     // one round of resident workgroups (the runtime's occupancy for this instance, at most the four per CU the
     // workspace holds slots for): a persistent grid larger than what fits would leave the surplus workgroups
-    // waiting for whole early workgroups, which loop over several systems each.  At TMAX = 10 three would fit
-    // but measured slower than two (k = 300: 1.23 against 1.05 ms per forward solve).
+    // waiting for whole early workgroups, which loop over several systems each.  At TMAX = 10 the
+    // registers allow two workgroups of eight waves.
     static int per_cu = 0;
     if (per_cu == 0) {
         int n = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void *)rowsolve_ll_kernel<TMAX, MODE, STORE>, 256, lds) !=
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void *)rowsolve_ll_kernel<TMAX, MODE, STORE>,
+                                                         64 * ll_waves(TMAX), lds) !=
                 hipSuccess ||
             n < 1)
             n = 1;
@@ -672,7 +734,8 @@ static void launch_ll(const float *K, const float *rhs, const float *ex, const f
     }
     const int64_t nsys = P * ky;
     const int64_t grid = std::min<int64_t>(nsys, (int64_t)per_cu * cu_count());
-    hipLaunchKernelGGL((rowsolve_ll_kernel<TMAX, MODE, STORE>), dim3((unsigned)grid), dim3(256), lds, st, K, rhs, ex, ey, lam,
+    hipLaunchKernelGGL((rowsolve_ll_kernel<TMAX, MODE, STORE>), dim3((unsigned)grid), dim3(64 * ll_waves(TMAX)), lds, st, K,
+                       rhs, ex, ey, lam,
                        mask_kind, gamma, (int)kx, (int)ky, (int)nsys, out, Lout, info, Cfwd, dlam_part, ws, cu_count(),
                        only);
 }

@@ -96,22 +96,27 @@ __global__ __launch_bounds__(256) void vec_form_kernel(const float *__restrict__
     if (e == 0) ey0[pr] = 0.f;
 }
 
-// The same entries for kx, ky <= 32: a workgroup takes VF_ROWS rows of H of one pair.  It stages D1, D2 and K
-// in LDS (rows padded to 33 floats), forms D1 D1^T and D2^T D2 there once (the dot products in the order of
-// the kernel above), and writes each row of H with consecutive threads on consecutive columns.  Every entry
-// follows the same formula, in the same order, as in the kernel above.
-constexpr int VF_KM = 32, VF_LD = 33, VF_ROWS = 32;
+// The same entries for kx, ky <= 32: a workgroup takes `rows` rows of H of one pair.  It stages D1, D2 and K in LDS
+// (rows padded to 33 floats) and forms D1 D1^T, and the rows of D2^T D2 that it needs, there once (the dot products
+// in the order of the kernel above).  A thread keeps one column b = (p, q) of H and walks down the rows, so the
+// indices are split once per thread and once per i, and the two factors from D2 stay in registers over a row block
+// (i, 0..kx-1); consecutive threads write consecutive columns.  Every entry follows the same formula, in the same
+// order, as in the kernel above.  Bound by the writes of H:
+// 256 pairs of n = 256 (67 MB) 15 us, 4.3 TB/s; 41 us when each entry divided its own indices and read all six
+// factors from LDS.
+constexpr int VF_KM = 32, VF_LD = 33;
 
 __global__ __launch_bounds__(256) void vec_form_lds_kernel(const float *__restrict__ K, const float *__restrict__ R,
                                                            const float *__restrict__ D1, const float *__restrict__ D2,
                                                            const float *__restrict__ lam, int kx, int ky, int n,
-                                                           float *__restrict__ H, float *__restrict__ g,
+                                                           int rows, float *__restrict__ H, float *__restrict__ g,
                                                            float *__restrict__ ex0, float *__restrict__ ey0, int bpp)
 {
     __shared__ float sD1[VF_KM * VF_LD], sD2[VF_KM * VF_LD], sK[VF_KM * VF_LD], sP1[VF_KM * VF_LD],
         sP2[VF_KM * VF_LD];
     const int pr = blockIdx.x / bpp, bx = blockIdx.x - pr * bpp;
-    const int a0 = bx * VF_ROWS, tid = threadIdx.x;
+    const int a0 = bx * rows, a1 = min(a0 + rows, n), tid = threadIdx.x;
+    const int i0 = a0 / kx, i1 = (a1 - 1) / kx + 1;  // blocks i of the rows
     const float *Kp = K + (size_t)pr * kx * kx;
     const float *D1p = D1 + (size_t)pr * kx * kx;
     const float *D2p = D2 + (size_t)pr * ky * ky;
@@ -131,26 +136,31 @@ __global__ __launch_bounds__(256) void vec_form_lds_kernel(const float *__restri
         for (int c = 0; c < kx; ++c) t = fmaf(sD1[j * VF_LD + c], sD1[q * VF_LD + c], t);
         sP1[j * VF_LD + q] = t;
     }
-    for (int e = tid; e < ky * ky; e += 256) {  // (D2^T D2)_ip
-        const int i = e / ky, p = e - i * ky;
+    for (int e = tid; e < (i1 - i0) * ky; e += 256) {  // (D2^T D2)_ip
+        const int i = i0 + e / ky, p = e % ky;
         float t = 0.f;
         for (int c = 0; c < ky; ++c) t = fmaf(sD2[c * VF_LD + i], sD2[c * VF_LD + p], t);
         sP2[i * VF_LD + p] = t;
     }
     __syncthreads();
     const float lm = lam[pr];
-    const int a1 = min(a0 + VF_ROWS, n);
-    for (int a = a0; a < a1; ++a) {
-        const int i = a / kx, j = a - i * kx;
-        float *Hr = H + (size_t)pr * n * n + (size_t)a * n;
-        for (int b = tid; b < n; b += 256) {
-            const int p = b / kx, q = b - p * kx;
-            float s = 0.f;
-            if (i == p) s += sP1[j * VF_LD + q];
-            if (j == q) s += sP2[i * VF_LD + p];
-            s -= sD2[i * VF_LD + p] * sD1[j * VF_LD + q] + sD2[p * VF_LD + i] * sD1[q * VF_LD + j];
-            const float base = i == p ? sK[j * VF_LD + q] : 0.f;
-            Hr[b] = fmaf(lm, s, base);
+    for (int b = tid; b < n; b += 256) {
+        const int p = b / kx, q = b - p * kx;
+        const float *d1q = sD1 + q * VF_LD;
+        float *Hb = H + (size_t)pr * n * n + b;
+        for (int i = i0; i < i1; ++i) {
+            const float d2ip = sD2[i * VF_LD + p], d2pi = sD2[p * VF_LD + i], p2 = sP2[i * VF_LD + p];
+            const bool same = i == p;
+            const int j0 = max(a0 - i * kx, 0), j1 = min(a1 - i * kx, kx);
+#pragma unroll 4
+            for (int j = j0; j < j1; ++j) {
+                const float p1 = sP1[j * VF_LD + q], k0 = sK[j * VF_LD + q];
+                float s = 0.f;
+                s += same ? p1 : 0.f;
+                s += j == q ? p2 : 0.f;
+                s -= d2ip * sD1[j * VF_LD + q] + d2pi * d1q[j];
+                Hb[(size_t)(i * kx + j) * n] = fmaf(lm, s, same ? k0 : 0.f);
+            }
         }
     }
     if (bx == 0) {
@@ -177,9 +187,11 @@ hipError_t launch_solve_vectorized(const float *A, const float *B, const float *
     float *g = (float *)(base + L.g), *ex0 = (float *)(base + L.ex0), *ey0 = (float *)(base + L.ey0);
     launch_gram(A, B, P, kx, ky, d, true, K, R, st);
     if (kx <= VF_KM && ky <= VF_KM) {
-        const int bpp = (int)((n + VF_ROWS - 1) / VF_ROWS);
+        // 64 rows share the staging where that still gives four workgroups per CU, 32 otherwise
+        const int64_t rows = P * ((n + 63) / 64) >= 4 * (int64_t)device_cus() ? 64 : 32;
+        const int bpp = (int)((n + rows - 1) / rows);
         hipLaunchKernelGGL(vec_form_lds_kernel, dim3((unsigned)(P * bpp)), dim3(256), 0, st, K, R, D1, D2, lam, (int)kx,
-                           (int)ky, (int)n, H, g, ex0, ey0, bpp);
+                           (int)ky, (int)n, (int)rows, H, g, ex0, ey0, bpp);
     } else {
         const int bpp = (int)((n * n + 255) / 256);
         hipLaunchKernelGGL(vec_form_kernel, dim3((unsigned)(P * bpp)), dim3(256), 0, st, K, R, D1, D2, lam, (int)kx,

@@ -22,12 +22,18 @@ from . import _lib
 from ._lib import FMAP_BF16, FMAP_F32, FMAP_MASK_LAPLACIAN, FMAP_MASK_RESOLVENT, FmapError  # noqa: F401
 
 
-def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
+    return None if t is None else t.data_ptr()
 
 
-def _stream(dev: torch.device):
-    return ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream(dev: torch.device) -> int:
+    """The current stream of `dev` as a handle (without a torch.cuda.Stream object where torch offers that)."""
+    if _raw_stream is not None and dev.type == "cuda" and dev.index is not None:
+        return _raw_stream(dev.index)
+    return torch.cuda.current_stream(dev).cuda_stream
 
 
 def _need(t: torch.Tensor, name: str, dtype, shape, dev) -> None:
@@ -35,9 +41,9 @@ def _need(t: torch.Tensor, name: str, dtype, shape, dev) -> None:
         raise TypeError(f"{name} must be a tensor")
     if t.device != dev:
         raise ValueError(f"{name} is on {t.device}, expected {dev}")
-    if dtype is not None and t.dtype not in (dtype if isinstance(dtype, tuple) else (dtype,)):
+    if t.dtype is not dtype and dtype is not None and not (isinstance(dtype, tuple) and t.dtype in dtype):
         raise TypeError(f"{name} has dtype {t.dtype}, expected {dtype}")
-    if tuple(t.shape) != tuple(shape):
+    if t.shape != shape:
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
@@ -160,6 +166,13 @@ def fmap_solve(A: torch.Tensor, B: torch.Tensor, evals_x: torch.Tensor, evals_y:
     _need(evals_x, "evals_x", torch.float32, (P, kx), dev)
     _need(evals_y, "evals_y", torch.float32, (P, ky), dev)
     _need(lam, "lam", torch.float32, (P,), dev)
+    return _solve(dev, P, kx, ky, d, _ptr(A), _ptr(B), _ptr(evals_x), _ptr(evals_y), _ptr(lam), mask_kind, gamma,
+                  refine_steps, cond_fp64_threshold, store_factors, want_cond, C, factors, info, workspace)
+
+
+def _solve(dev, P, kx, ky, d, A, B, evals_x, evals_y, lam, mask_kind, gamma, refine_steps=0, cond_fp64_threshold=0.0,
+           store_factors=True, want_cond=False, C=None, factors=None, info=None, workspace=None):
+    """fmap_solve with its checked inputs as addresses."""
     if C is None:
         C = torch.empty((P, ky, kx), dtype=torch.float32, device=dev)
     if info is None:
@@ -172,7 +185,7 @@ def fmap_solve(A: torch.Tensor, B: torch.Tensor, evals_x: torch.Tensor, evals_y:
     cond = torch.empty((P,), dtype=torch.float32, device=dev) if want_cond else None
     workspace = _workspace(fmap_solve_workspace_bytes(P, kx, ky, d), dev, workspace)
     _lib.check("fmap_solve", _lib.lib().fmap_solve(
-        _ptr(A), _ptr(B), _ptr(evals_x), _ptr(evals_y), _ptr(lam), int(mask_kind), float(gamma), P, kx, ky, d,
+        A, B, evals_x, evals_y, lam, int(mask_kind), float(gamma), P, kx, ky, d,
         int(refine_steps), float(cond_fp64_threshold), _ptr(C), _ptr(factors), _ptr(info), _ptr(cond),
         _ptr(workspace), _wsbytes(workspace), _stream(dev)))
     return C, factors, info, cond
@@ -195,13 +208,20 @@ def fmap_solve_backward(dC: torch.Tensor, A: torch.Tensor, B: torch.Tensor, C: t
         dA = torch.empty((P, kx, d), dtype=torch.float32, device=dev)
     if dB is None:
         dB = torch.empty((P, ky, d), dtype=torch.float32, device=dev)
+    dlam = _solve_backward(dev, P, kx, ky, d, dC, _ptr(A), _ptr(B), C, _ptr(evals_x), _ptr(evals_y), _ptr(lam),
+                           mask_kind, gamma, factors, want_dlam, _ptr(dA), _ptr(dB), info, workspace)
+    return dA, dB, dlam
+
+
+def _solve_backward(dev, P, kx, ky, d, dC, A, B, C, evals_x, evals_y, lam, mask_kind, gamma, factors, want_dlam, dA, dB,
+                    info=None, workspace=None):
+    """fmap_solve_backward with its checked inputs and its outputs as addresses; returns dlam or None."""
     dlam = torch.empty((P,), dtype=torch.float32, device=dev) if want_dlam else None
     workspace = _workspace(fmap_solve_workspace_bytes(P, kx, ky, d), dev, workspace)
     _lib.check("fmap_solve_backward", _lib.lib().fmap_solve_backward(
-        _ptr(dC), _ptr(A), _ptr(B), _ptr(C), _ptr(evals_x), _ptr(evals_y), _ptr(lam), int(mask_kind), float(gamma),
-        P, kx, ky, d, _ptr(factors), _ptr(dA), _ptr(dB), _ptr(dlam), _ptr(info), _ptr(workspace),
-        _wsbytes(workspace), _stream(dev)))
-    return dA, dB, dlam
+        _ptr(dC), A, B, _ptr(C), evals_x, evals_y, lam, int(mask_kind), float(gamma), P, kx, ky, d, _ptr(factors), dA,
+        dB, _ptr(dlam), _ptr(info), _ptr(workspace), _wsbytes(workspace), _stream(dev)))
+    return dlam
 
 
 # ---------------------------------------------------------------------------- projector input, resolutions
@@ -343,6 +363,16 @@ def fmap_overlap_metrics(scores: torch.Tensor, truth: torch.Tensor, offsets: tor
 
 # ---------------------------------------------------------------------------- autograd
 
+def _halves(AB, evals, lam, P: int) -> bool:
+    """Whether AB [2P, k, d], evals [2P, k] and lam [P] can be passed on as the addresses of their two halves
+    (otherwise they go through the slices and the checks of the general entry points)."""
+    b, k, _ = AB.shape
+    dev = AB.device
+    return (b == 2 * P and evals.shape == (b, k) and lam.shape == (P,) and AB.dtype is torch.float32 and
+            evals.dtype is torch.float32 and lam.dtype is torch.float32 and evals.device == dev and lam.device == dev and
+            AB.is_contiguous() and evals.is_contiguous() and lam.is_contiguous())
+
+
 class FmapSolveFn(torch.autograd.Function):
     """C = solve(project(Phi_x, M_x, F_x), project(Phi_y, M_y, F_y)) with a hand-written backward.
 
@@ -357,9 +387,14 @@ class FmapSolveFn(torch.autograd.Function):
     def forward(ctx, feat, phi, mass, evals, lam, mask_kind, gamma, bwd="stored"):
         P = lam.shape[0]
         AB = fmap_project(phi, mass, feat)
-        A, B = AB[:P], AB[P:]
-        C, factors, info, _ = fmap_solve(A, B, evals[:P].contiguous(), evals[P:].contiguous(), lam, mask_kind, gamma,
-                                         store_factors=(bwd == "stored"))
+        if _halves(AB, evals, lam, P):  # the two halves by address: a small call is bound by the host
+            _, k, d = AB.shape
+            a, e = AB.data_ptr(), evals.data_ptr()
+            C, factors, info, _ = _solve(AB.device, P, k, k, d, a, a + 4 * P * k * d, e, e + 4 * P * k, lam.data_ptr(),
+                                         mask_kind, gamma, store_factors=(bwd == "stored"))
+        else:
+            C, factors, info, _ = fmap_solve(AB[:P], AB[P:], evals[:P].contiguous(), evals[P:].contiguous(), lam,
+                                             mask_kind, gamma, store_factors=(bwd == "stored"))
         ctx.mask_kind, ctx.gamma, ctx.P = mask_kind, gamma, P
         ctx.save_for_backward(phi, mass, evals, lam, AB, C, factors if factors is not None else torch.empty(0))
         ctx.has_factors = factors is not None
@@ -371,10 +406,21 @@ class FmapSolveFn(torch.autograd.Function):
         phi, mass, evals, lam, AB, C, factors = ctx.saved_tensors
         P = ctx.P
         dAB = torch.empty_like(AB)
-        _, _, dlam = fmap_solve_backward(dC.contiguous(), AB[:P], AB[P:], C, evals[:P].contiguous(),
-                                         evals[P:].contiguous(), lam, ctx.mask_kind, ctx.gamma,
-                                         factors if ctx.has_factors else None, want_dlam=ctx.needs_input_grad[4],
-                                         dA=dAB[:P], dB=dAB[P:])
+        dC = dC.contiguous()
+        factors = factors if ctx.has_factors else None
+        if _halves(AB, evals, lam, P):
+            dev, (_, k, d) = AB.device, AB.shape
+            _need(dC, "dC", torch.float32, (P, k, k), dev)
+            _need(C, "C", torch.float32, (P, k, k), dev)
+            if factors is not None:
+                _need(factors, "factors", torch.float32, (P, fmap_factor_floats(k, k)), dev)
+            a, e, g, half = AB.data_ptr(), evals.data_ptr(), dAB.data_ptr(), 4 * P * k * d
+            dlam = _solve_backward(dev, P, k, k, d, dC, a, a + half, C, e, e + 4 * P * k, lam.data_ptr(), ctx.mask_kind,
+                                   ctx.gamma, factors, ctx.needs_input_grad[4], g, g + half)
+        else:
+            _, _, dlam = fmap_solve_backward(dC, AB[:P], AB[P:], C, evals[:P].contiguous(), evals[P:].contiguous(), lam,
+                                             ctx.mask_kind, ctx.gamma, factors, want_dlam=ctx.needs_input_grad[4],
+                                             dA=dAB[:P], dB=dAB[P:])
         dF = fmap_project_backward(phi, mass, dAB) if ctx.needs_input_grad[0] else None
         return dF, None, None, None, dlam, None, None, None
 

@@ -427,41 +427,39 @@ __global__ __launch_bounds__(64 * ll_waves(TMAX)) __attribute__((amdgpu_waves_pe
                     if (r >= c && r < kxl) Lo[packed_col_t(32 * ps + c, kx) + (r - c)] = bc[r * TLD + c];
                 }
             }
-            // ---- 4. panel L_Ip = S_Ip Minv^T (I > ps) -----------------------------------------------
+            // ---- 4. panel L_Ip = S_Ip Minv^T (I > ps), formed transposed: lane l32 holds row l32 of the tile, register
+            //         r column acc32_row(r).  Four columns at a time go to the row-major slot, and whole columns
+            //         (consecutive lanes on consecutive rows) to the packed factor, straight from the registers ----
             for (int j = 1 + wave; j < nt; j += NW) {
                 const int I = ps + j;
                 const float *X = bc + j * TSZ;
                 f32x16 nv = zero16();
 #pragma unroll
                 for (int t = 0; t < 16; ++t)
-                    nv = mfma32x32x2(X[l32 * TLD + 2 * t + half], s_minv[l32 * TLD + 2 * t + half], nv);
-                float *Lt = Ls + (size_t)tile_index(I, ps, TR) * LTS;
+                    nv = mfma32x32x2(s_minv[l32 * TLD + 2 * t + half], X[l32 * TLD + 2 * t + half], nv);
+                float *Lt = Ls + (size_t)tile_index(I, ps, TR) * LTS + l32 * 32;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) Lt[acc32_row(r, lane) * 32 + l32] = nv[r];
-                if (STORE) {
-                    // the tile of L also back into LDS (over S_Ip, which this wave alone reads) for the packed output
-                    __builtin_amdgcn_wave_barrier();
+                for (int r = 0; r < 16; r += 4)
+                    *reinterpret_cast<f32x4 *>(Lt + acc32_row(r, lane)) = f32x4{nv[r], nv[r + 1], nv[r + 2], nv[r + 3]};
+                if (STORE && 32 * I + l32 < kx) {
+                    float *Lo = Lout + ((size_t)p * ky + i) * (size_t)(kx * (kx + 1) / 2);
+                    int c = 32 * ps + 4 * half;  // a block with rows below it is 32 columns wide
+                    unsigned e = (unsigned)(packed_col_t(c, kx) + 32 * I + l32 - c);
+                    asm volatile("" : "+v"(c), "+v"(e));  // else sixteen offsets are carried from tile to tile
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) bc[j * TSZ + acc32_row(r, lane) * TLD + l32] = nv[r];
+                    for (int r = 0; r < 16; ++r) {
+                        Lo[e] = nv[r];
+                        const int step = (r & 3) == 3 ? 5 : 1;  // columns to the next register's
+                        e += step * (kx - c - 1) - step * (step - 1) / 2;
+                        c += step;
+                    }
                 }
-                if (I == AR) {
+                if (I == AR && l32 == ar) {
 #pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        if (acc32_row(r, lane) == ar) s_vec[32 * ps + l32] = l32 < kxl ? nv[r] : 0.f;
+                    for (int r = 0; r < 16; ++r) s_vec[32 * ps + acc32_row(r, lane)] = nv[r];
                 }
             }
             __syncthreads();
-            if (STORE) {
-                // the block column's tiles of L below the diagonal into the packed factor, consecutive threads on
-                // consecutive rows of one column
-                float *Lo = Lout + ((size_t)p * ky + i) * (size_t)(kx * (kx + 1) / 2);
-                for (int e = tid; e < (nt - 1) * 1024; e += NTHR) {
-                    const int j = 1 + (e >> 10), c = (e >> 5) & 31, r = e & 31;
-                    const int R = 32 * (ps + j) + r, Cc = 32 * ps + c;
-                    if (R < kx && Cc < kx) Lo[packed_col_t(Cc, kx) + R - Cc] = bc[j * TSZ + r * TLD + c];
-                }
-                __syncthreads();
-            }
         }
         const int fail = __builtin_amdgcn_readfirstlane(*s_fail);
 

@@ -8,8 +8,8 @@
 // Large k_x: one wave per system; lane j holds rows j, j + 64, ... (NS slots).
 // The factor is packed lower, column-major, so column c is contiguous:
 //   * forward L y = r column by column (y_c = r_c / L_cc, then the rows below
-//     subtract L_qc y_c), with the slot and lane of c compile-time, so y_c and
-//     L_cc are single readlanes and each slot takes one fused multiply-add;
+//     subtract L_qc y_c), with the slot and lane of c compile-time, so y_c is
+//     one readlane and each slot takes one fused multiply-add;
 //   * back substitution L^T x = y one slot of 64 columns at a time, lane c
 //     taking column c: the slots already solved contribute the dot product of
 //     the lane's own contiguous column segment with their x, and the 64 x 64
@@ -92,12 +92,20 @@ __global__ __launch_bounds__(256) void trisolve_stored_kernel(const float *__res
     };
 
     // ---- forward substitution L y = r, column by column: slot s and the lane of column c are compile-time, so
-    // y_c and L_cc are single readlanes, and the rows below c take one fused multiply-add per slot (the slot of
-    // c under a lane mask).  Columns come in groups of 8, the next group's loads in flight while one is used;
-    // a group loads only the slots at or below its own (the rows above the diagonal are never needed).
+    // y_c is one readlane (of the running row times the reciprocal column), and the rows below c take one fused
+    // multiply-add per slot (the slot of c under a lane mask).  Columns come in groups of 8, the next group's loads
+    // in flight while one is used; a group loads only the slots at or below its own (the rows above the diagonal
+    // are never needed).  The pivots are collected on the way (lane c the one of column c), checked afterwards, and
+    // their reciprocals scale the solved entries here and below; zero past k_x, they take those entries out of all
+    // sums.  (Loading the pivots first by a gather read a line for each: 16 pairs of k = 200 244 us per reverse-mode
+    // call against 220; testing each pivot before use cost ten instructions per column, 98 us against 77 for 4
+    // pairs of k = 200.)
+    float inv[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) inv[s] = 1.f;
     if (fail == 0) {
-        float ba[8][NS], bb[8][NS];
-        auto load_group = [&](int q, float (&buf)[8][NS]) {  // q = 8 s + g, compile-time
+        float buf[2][8][NS];
+        auto load_group = [&](int q, float (&bf)[8][NS]) {  // q = 8 s + g, compile-time
             const int s0 = q / 8;
 #pragma unroll
             for (int t = 0; t < 8; ++t) {
@@ -105,40 +113,40 @@ __global__ __launch_bounds__(256) void trisolve_stored_kernel(const float *__res
                 const int so = pcol(c, kx) - c;
 #pragma unroll
                 for (int sl = 0; sl < NS; ++sl)
-                    if (sl >= s0) buf[t][sl] = ldf(j + 64 * sl, so);
+                    if (sl >= s0) bf[t][sl] = ldf(j + 64 * sl, so);
             }
         };
-        auto fwd_group = [&](int q, const float (&buf)[8][NS]) {
+        auto fwd_group = [&](int q, const float (&bf)[8][NS]) {
             const int s0 = q / 8;
             int lane = j;
             asm volatile("" : "+v"(lane));  // masks formed per column, not hoisted into scalar registers
 #pragma unroll
             for (int t = 0; t < 8; ++t) {
-                const int c = 8 * q + t, cl = c & 63;
-                const float dg = uniform_f(readlane(buf[t][s0], cl));
-                const bool act = c < kx && fail == 0;
-                const bool bad = !(dg > 0.f) || !isfinite(dg);
-                fail = (act && bad) ? c + 1 : fail;
-                const bool go = act && !bad;
-                const float yc = go ? uniform_f(readlane(y[s0], cl) * __builtin_amdgcn_rcpf(dg)) : 0.f;
-                y[s0] = (lane > cl) ? y[s0] - buf[t][s0] * yc : ((lane == cl && go) ? yc : y[s0]);
+                const int cl = (8 * q + t) & 63;
+                const float yc = uniform_f(readlane(y[s0] * __builtin_amdgcn_rcpf(bf[t][s0]), cl));
+                inv[s0] = lane == cl ? bf[t][s0] : inv[s0];
+                y[s0] = lane > cl ? y[s0] - bf[t][s0] * yc : y[s0];
 #pragma unroll
                 for (int sl = 0; sl < NS; ++sl)
-                    if (sl > s0) y[sl] -= buf[t][sl] * yc;
+                    if (sl > s0) y[sl] -= bf[t][sl] * yc;
             }
         };
         constexpr int NQ = 8 * NS;
-        load_group(0, ba);
+        load_group(0, buf[0]);
 #pragma unroll
-        for (int q = 0; q < NQ; q += 2) {
+        for (int q = 0; q < NQ; ++q) {
             if (8 * q >= kx) break;
-            load_group(q + 1 < NQ ? q + 1 : q, bb);
-            fwd_group(q, ba);
-            if (8 * (q + 1) >= kx || q + 1 >= NQ) break;
-            load_group(q + 2 < NQ ? q + 2 : q + 1, ba);
-            fwd_group(q + 1, bb);
+            if (q + 1 < NQ) load_group(q + 1, buf[(q + 1) & 1]);
+            fwd_group(q, buf[q & 1]);
         }
-        fail = __builtin_amdgcn_readfirstlane(fail);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const int q = j + 64 * s;
+            const uint64_t bad = __ballot(q < kx && (!(inv[s] > 0.f) || !isfinite(inv[s])));
+            if (fail == 0 && bad != 0) fail = 64 * s + (int)__builtin_ctzll(bad) + 1;
+            inv[s] = q < kx ? __builtin_amdgcn_rcpf(inv[s]) : 0.f;
+            y[s] = q < kx ? y[s] * inv[s] : 0.f;
+        }
     }
 
     // ---- back substitution L^T x = y, 64 columns (one slot) at a time from the last, lane c taking column
@@ -155,30 +163,24 @@ __global__ __launch_bounds__(256) void trisolve_stored_kernel(const float *__res
             if (64 * s0 >= kx) continue;
             const int col = 64 * s0 + j;
             const int cb = pcol(min(col, kx - 1), kx) - min(col, kx - 1);  // factor offset of (row 0, this column)
-            const bool colok = col < kx;
-            // the finished slots' rows 64 sl .. 64 sl + 63 of this lane's column in chunks of 16, slots from the
+            // the finished slots' rows 64 sl .. 64 sl + 63 of this lane's column in chunks of 32, slots from the
             // last, the next chunk's loads in flight while one is used (every slot below NS holds rows:
-            // NS = ceil(k_x / 64)).  The diagonal block's column segment is loaded after them, except in the
-            // widest instance, where loading it first measured faster (k = 300: 0.350 against 0.376 ms per
-            // reverse-mode call; k = 200: 0.235 against 0.252 ms the other way round).
-            float dl[64];
-            if constexpr (NS >= 5) {
-#pragma unroll
-                for (int r = 0; r < 64; ++r) dl[r] = ldf(cb + r, 64 * s0);
-            }
+            // NS = ceil(k_x / 64)), then the diagonal block's column segment.  A lane reads its own lines, 64 of
+            // 128 bytes per wave, which do not stay in L1: chunks of 16 rows fetched each line twice (reverse-mode
+            // call, 8 pairs of k = 300: 377 us against 337; 16 of k = 200: 223 against 210).
             float v = y[s0];
-            constexpr int CH = 4;                // chunks of 16 rows per slot
+            constexpr int CH = 2;                // chunks of 32 rows per slot
             const int nch = CH * (NS - 1 - s0);  // compile-time once s0 is unrolled
-            float la[16], lb[16];
-            auto load_chunk = [&](int c, float (&buf)[16]) {
-                const int sl = NS - 1 - c / CH, r0 = 16 * (c % CH);
+            float la[32], lb[32];
+            auto load_chunk = [&](int c, float (&buf)[32]) {
+                const int sl = NS - 1 - c / CH, r0 = 32 * (c % CH);
 #pragma unroll
-                for (int r = 0; r < 16; ++r) buf[r] = ldf(cb + r0 + r, 64 * sl);
+                for (int r = 0; r < 32; ++r) buf[r] = ldf(cb + r0 + r, 64 * sl);
             };
-            auto use_chunk = [&](int c, const float (&buf)[16]) {
-                const int sl = NS - 1 - c / CH, r0 = 16 * (c % CH);
+            auto use_chunk = [&](int c, const float (&buf)[32]) {
+                const int sl = NS - 1 - c / CH, r0 = 32 * (c % CH);
 #pragma unroll
-                for (int r = 0; r < 16; ++r) v -= buf[r] * uniform_f(readlane(x[sl], r0 + r));
+                for (int r = 0; r < 32; ++r) v -= buf[r] * uniform_f(readlane(x[sl], r0 + r));
             };
             if (nch > 0) load_chunk(0, la);
 #pragma unroll
@@ -189,21 +191,17 @@ __global__ __launch_bounds__(256) void trisolve_stored_kernel(const float *__res
                 if (c + 2 < nch) load_chunk(c + 2, la);
                 use_chunk(c + 1, lb);
             }
-            if constexpr (NS < 5) {
+            float dl[64];
 #pragma unroll
-                for (int r = 0; r < 64; ++r) dl[r] = ldf(cb + r, 64 * s0);
-            }
+            for (int r = 0; r < 64; ++r) dl[r] = ldf(cb + r, 64 * s0);
             int lane = j;
             asm volatile("" : "+v"(lane));
-            float xs = 0.f;
 #pragma unroll
             for (int c2 = 63; c2 >= 0; --c2) {
-                const bool act = 64 * s0 + c2 < kx;
-                const float xc = act ? uniform_f(readlane(v, c2) * __builtin_amdgcn_rcpf(readlane(dl[c2], c2))) : 0.f;
+                const float xc = uniform_f(readlane(v * inv[s0], c2));
                 v = (lane < c2) ? v - dl[c2] * xc : v;
-                xs = (lane == c2) ? xc : xs;
             }
-            x[s0] = colok ? xs : 0.f;
+            x[s0] = col < kx ? v * inv[s0] : 0.f;
         }
     }
 #pragma unroll

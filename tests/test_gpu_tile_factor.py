@@ -49,3 +49,22 @@ def test_zero_pivot(dev, k, pivot):
     for C, info in _solve(dev, (A, B, ex, ey, lam)):
         assert (info[0] == pivot + 1).all() and np.isnan(C[0]).all()
         assert (info[1] == 0).all() and np.isfinite(C[1]).all()
+
+
+@pytest.mark.parametrize("value", [0.0, -1.0, float("nan"), float("inf")])
+@pytest.mark.parametrize("k,pivots", [(66, (65,)), (130, (0, 64)), (200, (63, 199)), (200, (64, 127)), (300, (299,))])
+def test_bad_stored_pivot(dev, k, pivots, value):
+    """The reverse mode with a stored factor reports the first pivot that is not positive and finite, row by row."""
+    import torch
+    from paper_2604_10377_amd import fmap as F
+    A, B, ex, ey, lam = (torch.from_numpy(a).to(dev) for a in _inputs(3, 1, k))
+    C, fac, _, _ = F.fmap_solve(A, B, ex, ey, lam, 0, 0.5)
+    m, row = k * (k + 1) // 2, k // 2
+    for c in pivots:
+        fac[0, row * m + c * k - c * (c - 1) // 2] = value
+    info = torch.full((1, k), 7, dtype=torch.int32, device=dev)
+    print("stored pivot", k, pivots, value, flush=True)
+    F.fmap_solve_backward(torch.ones_like(C), A, B, C, ex, ey, lam, 0, 0.5, fac, info=info)
+    want = torch.zeros(k, dtype=torch.int32)
+    want[row] = pivots[0] + 1
+    assert torch.equal(info[0].cpu(), want)

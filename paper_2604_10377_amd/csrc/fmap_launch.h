@@ -137,6 +137,11 @@ void launch_adjoint_general(const float *V, const float *C, const float *A, cons
 // K = A A^T [P][kx][kx] and, with with_R, R = B A^T [P][ky][kx] in float32.
 void launch_gram(const float *A, const float *B, int64_t P, int64_t kx, int64_t ky, int64_t d, bool with_R,
                  float *K, float *R, hipStream_t st);
+// The row systems of given normal products K [P][kx][kx], R [P][ky][kx], without stored factors.  tiles:
+// tiled_workspace_bytes(P, kx, ky) bytes when kx > kSmallK.
+void launch_solve_products(const float *K, const float *R, const float *ex, const float *ey, const float *lam,
+                           int mask_kind, float gamma, int64_t P, int64_t kx, int64_t ky, float *C, int *info,
+                           float *tiles, hipStream_t st);
 // One system per pair with a given symmetric matrix: S [P][n][n] (n <= kMaxK), right-hand side g [P][n],
 // solution out [P][n], info [P]; ex_zero [P][n] and ey_zero [P] must hold zeros (no mask shift is added) and
 // lam [P] only flags an invalid value.  tiles: tiled_workspace_bytes(P, n, 1) bytes when n > kSmallK.

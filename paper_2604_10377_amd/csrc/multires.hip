@@ -6,9 +6,12 @@
 //    is the solve of Eqs. (4)-(7) restricted to the first k_x' source and k_y'
 //    target eigenpairs: the leading k_x' rows of A, the leading k_y' rows of B,
 //    the eigenvalues truncated alike (the mask, and the resolvent normaliser,
-//    are those of the truncated spectra).  The leading rows are gathered into
-//    contiguous workspace arrays by one copy launch, then the batched solve
-//    runs as for a plain call; the largest resolution reuses A and B in place.
+//    are those of the truncated spectra).  Its normal products are the leading
+//    blocks of those of a larger resolution, entry by entry the same sums, so
+//    where one resolution covers the others the products are formed once for
+//    it, and the others' blocks are gathered from them.  Otherwise the leading
+//    rows of A and B are gathered per resolution and the batched solve runs as
+//    for a plain call.
 //
 // 2. The projector given directly.  Eq. (1) writes A = Phi^+ F with the
 //    pseudo-inverse; a caller holding Phi^+ (k x n) passes its transpose P
@@ -27,11 +30,18 @@ namespace fmap {
 
 namespace {
 
-struct RowCopy {             // dst[p][r][c] = src[p][r][c] for r < rows, pairs p
+struct RowCopy {              // dst[p][r][c] = src[p][r][c] for r < rows, c < cols, pairs p; dst dense
     const float *src;
     float *dst;
     int64_t src_pair_stride;  // floats between pairs in src
+    int src_row_stride;       // and between rows
     int rows, cols;
+};
+
+// Up to 8 resolutions of four arrays (1.3 KB of kernel arguments)
+constexpr int MAX_COPIES = 32;
+struct RowCopies {
+    RowCopy job[MAX_COPIES];
 };
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -62,14 +72,18 @@ ResLayout res_layout(int64_t P, int64_t kx, int64_t ky, int64_t d)
 
 }  // namespace
 
-__global__ __launch_bounds__(256) void copy_rows_kernel(RowCopy j0, RowCopy j1, RowCopy j2, RowCopy j3, int P)
+// One wave per row: the row's pair and place are split once, in scalar registers, and the lanes walk the columns
+// (an element-wise copy divided two 64-bit indices per float: 6 us for 5 MB, bound by that).
+__global__ __launch_bounds__(256) void copy_rows_kernel(RowCopies js, int64_t P)
 {
-    const RowCopy &j = blockIdx.y == 0 ? j0 : blockIdx.y == 1 ? j1 : blockIdx.y == 2 ? j2 : j3;
-    const int64_t per = (int64_t)j.rows * j.cols;
-    const int64_t n = per * P;
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (int64_t)gridDim.x * 256) {
-        const int64_t p = e / per, q = e % per;
-        j.dst[e] = j.src[p * j.src_pair_stride + q];
+    const RowCopy &j = js.job[blockIdx.y];
+    const int64_t rows = P * j.rows;
+    for (int64_t w = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); w < rows;
+         w += (int64_t)gridDim.x * 4) {
+        const int64_t p = w / j.rows, r = w - p * j.rows;
+        const float *src = j.src + p * j.src_pair_stride + r * j.src_row_stride;
+        float *dst = j.dst + w * j.cols;
+        for (int c = threadIdx.x & 63; c < j.cols; c += 64) dst[c] = src[c];
     }
 }
 
@@ -90,28 +104,92 @@ size_t resolutions_workspace_bytes(int64_t P, int64_t kx, int64_t ky, int64_t d,
     return mx;
 }
 
+static void launch_copies(const RowCopies &js, int n, int64_t P, hipStream_t st)
+{
+    int64_t rows = 1;
+    for (int i = 0; i < n; ++i) rows = std::max<int64_t>(rows, P * js.job[i].rows);
+    hipLaunchKernelGGL(copy_rows_kernel, dim3((unsigned)std::min<int64_t>((rows + 3) / 4, 4096), n), dim3(256), 0, st,
+                       js, P);
+}
+
 hipError_t launch_solve_resolutions(const float *A, const float *B, const float *ex, const float *ey, const float *lam,
                                     int mask_kind, float gamma, int64_t P, int64_t kx, int64_t ky, int64_t d, int nres,
                                     const int32_t *kxs, const int32_t *kys, float *const *C, int32_t *const *info,
                                     void *ws, hipStream_t st)
 {
     char *base = (char *)ws;
+    // the resolution that covers all others, if there is one
+    const int64_t mx = *std::max_element(kxs, kxs + nres), my = *std::max_element(kys, kys + nres);
+    int top = -1;
+    for (int r = 0; r < nres; ++r)
+        if (kxs[r] == mx && kys[r] == my) top = r;
+    const bool in_place = mx == kx && my == ky;
+    // A and B in place take the products' 16-byte loads only if aligned; gathered rows always do
+    const bool aligned = !in_place || d % 4 != 0 || ((((uintptr_t)A) | ((uintptr_t)B)) & 15) == 0;
+    if (nres > 1 && top >= 0 && aligned) {
+        const ResLayout L = res_layout(P, mx, my, d);
+        const SolveWs S = solve_workspace_layout(P, mx, my, d);
+        char *sb = base + L.solve;
+        float *K = (float *)(sb + S.K), *R = (float *)(sb + S.R), *tiles = (float *)(sb + S.tiles);
+        const float *At = A, *Bt = B;
+        if (!in_place) {
+            RowCopies js{};
+            js.job[0] = RowCopy{A, (float *)(base + L.A), kx * d, (int)d, (int)mx, (int)d};
+            js.job[1] = RowCopy{B, (float *)(base + L.B), ky * d, (int)d, (int)my, (int)d};
+            launch_copies(js, 2, P, st);
+            At = js.job[0].dst;
+            Bt = js.job[1].dst;
+        }
+        launch_gram(At, Bt, P, mx, my, d, true, K, R, st);
+        // The blocks of the others and their spectra go where a refinement would keep its float64 products: room for
+        // any one resolution, mostly for all, gathered by one launch for as many as fit.
+        float *room = (float *)(sb + S.K64);
+        const size_t cap = (S.dlam - S.K64) / sizeof(float);
+        for (int r0 = 0; r0 < nres;) {
+            RowCopies js{};
+            int n = 0, r1 = r0;
+            size_t used = 0;
+            for (; r1 < nres && n + 4 <= MAX_COPIES; ++r1) {
+                if (kxs[r1] == mx && kys[r1] == my && in_place) continue;
+                const size_t x = kxs[r1], y = kys[r1], need = (size_t)P * (x * x + y * x + x + y);
+                if (used + need > cap) break;
+                float *o = room + used;
+                js.job[n++] = RowCopy{K, o, mx * mx, (int)mx, (int)x, (int)x};
+                js.job[n++] = RowCopy{R, o + P * x * x, my * mx, (int)mx, (int)y, (int)x};
+                js.job[n++] = RowCopy{ex, o + P * (x * x + y * x), kx, (int)kx, 1, (int)x};
+                js.job[n++] = RowCopy{ey, o + P * (x * x + y * x + x), ky, (int)ky, 1, (int)y};
+                used += need;
+            }
+            if (n > 0) launch_copies(js, n, P, st);
+            n = 0;
+            for (; r0 < r1; ++r0) {
+                const bool whole = kxs[r0] == mx && kys[r0] == my && in_place;
+                int32_t *inf = (info && info[r0]) ? info[r0] : (int32_t *)(base + L.info);
+                const RowCopy *j = js.job + n;
+                launch_solve_products(whole ? K : j[0].dst, whole ? R : j[1].dst, whole ? ex : j[2].dst,
+                                      whole ? ey : j[3].dst, lam, mask_kind, gamma, P, kxs[r0], kys[r0], C[r0], inf,
+                                      tiles, st);
+                n += whole ? 0 : 4;
+            }
+        }
+        return hipGetLastError();
+    }
     for (int r = 0; r < nres; ++r) {
         const int64_t kxr = kxs[r], kyr = kys[r];
         const ResLayout L = res_layout(P, kxr, kyr, d);
         int32_t *inf = (info && info[r]) ? info[r] : (int32_t *)(base + L.info);
         const float *Ar = A, *Br = B, *exr = ex, *eyr = ey;
         if (kxr != kx || kyr != ky) {
-            RowCopy ja{A, (float *)(base + L.A), kx * d, (int)kxr, (int)d};
-            RowCopy jb{B, (float *)(base + L.B), ky * d, (int)kyr, (int)d};
-            RowCopy jx{ex, (float *)(base + L.ex), kx, 1, (int)kxr};
-            RowCopy jy{ey, (float *)(base + L.ey), ky, 1, (int)kyr};
-            const int64_t most = P * std::max(kxr, kyr) * d;
-            hipLaunchKernelGGL(copy_rows_kernel, dim3(blocks_for(most), 4), dim3(256), 0, st, ja, jb, jx, jy, (int)P);
-            Ar = ja.dst;
-            Br = jb.dst;
-            exr = jx.dst;
-            eyr = jy.dst;
+            RowCopies js{};
+            js.job[0] = RowCopy{A, (float *)(base + L.A), kx * d, (int)d, (int)kxr, (int)d};
+            js.job[1] = RowCopy{B, (float *)(base + L.B), ky * d, (int)d, (int)kyr, (int)d};
+            js.job[2] = RowCopy{ex, (float *)(base + L.ex), kx, (int)kx, 1, (int)kxr};
+            js.job[3] = RowCopy{ey, (float *)(base + L.ey), ky, (int)ky, 1, (int)kyr};
+            launch_copies(js, 4, P, st);
+            Ar = js.job[0].dst;
+            Br = js.job[1].dst;
+            exr = js.job[2].dst;
+            eyr = js.job[3].dst;
         }
         hipError_t e = launch_solve(Ar, Br, exr, eyr, lam, mask_kind, gamma, P, kxr, kyr, d, 0, 0.f, C[r], nullptr, inf,
                                     nullptr, base + L.solve, st);

@@ -644,6 +644,18 @@ void launch_rowsolve_dense(const float *S, const float *g, const float *ex_zero,
                               nullptr, tiles, st);
 }
 
+void launch_solve_products(const float *K, const float *R, const float *ex, const float *ey, const float *lam,
+                           int mask_kind, float gamma, int64_t P, int64_t kx, int64_t ky, float *C, int *info,
+                           float *tiles, hipStream_t st)
+{
+    if (kx <= kSmallK)
+        launch_rowsolve<RS_FWD>(K, R, ex, ey, lam, mask_kind, gamma, P, kx, ky, C, nullptr, info, nullptr, nullptr, st,
+                                4);
+    else
+        launch_rowsolve_tiled(RS_FWD, K, R, ex, ey, lam, mask_kind, gamma, P, kx, ky, C, nullptr, info, nullptr,
+                              nullptr, tiles, st);
+}
+
 hipError_t launch_solve(const float *A, const float *B, const float *ex, const float *ey, const float *lam,
                         int32_t mask_kind, float gamma, int64_t P, int64_t kx, int64_t ky, int64_t d,
                         int32_t refine_steps, float cond_threshold, float *C, float *factors, int32_t *info,

@@ -227,9 +227,9 @@ fmap_status fmap_solve_vectorized(const float *A, const float *B, const float *o
 /*     g = x * (A z)_re + y * (A z)_im        g [vertices][channels] float      */
 /* Variant A is Re(conj(z) * (A z)), a learned rotation and isotropic scaling   */
 /* of each tangent vector; variant B fixes the rotation at +-45 degrees and     */
-/* allows anisotropic scaling.  Float32 arithmetic (float32 matrix cores for    */
-/* channels in {32, 64, 128, 256} and 16-byte aligned z; a plain kernel         */
-/* otherwise).  Forward only.                                                   */
+/* allows anisotropic scaling.  Float32 level (two-part float16 splits on the   */
+/* matrix cores with float32 accumulation for channels in {32, 64, 128, 256}    */
+/* and 16-byte aligned z; a plain float32 kernel otherwise).  Forward only.     */
 /* ------------------------------------------------------------------------ */
 #define FMAP_GRADFEAT_A 0
 #define FMAP_GRADFEAT_B 1

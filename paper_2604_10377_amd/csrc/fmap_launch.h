@@ -83,7 +83,7 @@ int tall_class(int64_t k, int64_t d);
 int tall_cols(int64_t k, int64_t d);
 hipError_t launch_fwd_tall_items(const FwdItem *items, int nitems, int cls, hipStream_t st);
 hipError_t launch_project_bf16(const uint16_t *phi, const float *mass, const uint16_t *feat, int64_t batch, int64_t n,
-                               int64_t k, int64_t d, float *A, void *ws, hipStream_t st);
+                               int64_t k, int64_t d, int ns, float *A, void *ws, hipStream_t st);
 int device_cus();
 
 struct ProjPlan {

@@ -7,6 +7,12 @@ namespace fmap {
 typedef __attribute__((address_space(3))) void lds_void_t;
 typedef __attribute__((address_space(1))) void glb_void_t;
 
+// One dword per lane, from any 4-byte aligned address
+__device__ __forceinline__ void dma4(const float *g, float *lds_base)
+{
+    __builtin_amdgcn_global_load_lds((glb_void_t *)g, (lds_void_t *)lds_base, 4, 0, 0);
+}
+
 __device__ __forceinline__ void dma16(const float *g, float *lds_base)
 {
     __builtin_amdgcn_global_load_lds((glb_void_t *)g, (lds_void_t *)lds_base, 16, 0, 0);

@@ -261,7 +261,8 @@ static bool aligned16(const void *p) { return ((uintptr_t)p & 15) == 0; }
 static int64_t budget_nsplit(int64_t batch, int64_t n, int64_t k, int64_t d, int32_t dtype)
 {
     int64_t ns = plan_project(batch, n, k, d, dtype).nsplit;
-    if (dtype == 1 && bf16_fwd_shape_ok(n, k, d)) ns = std::max<int64_t>(ns, bf16_fwd_nsplit(batch, n, k, d));
+    if (dtype == 1 && bf16_fwd_shape_ok(n, k, d) && n % 4 == 0)
+        ns = std::max<int64_t>(ns, bf16_fwd_nsplit(batch, n, k, d));
     if (dtype == 0 && k <= kMaxK && d % 4 == 0 && n % 4 == 0 && n >= 128) {
         const int64_t blocks = batch * ((d + 255) / 256), quarter = (n + 31) / 32 / 4, cus = device_cu_count();
         if (k <= 64) ns = std::max(ns, std::min((cus + blocks - 1) / blocks, quarter));
@@ -273,18 +274,22 @@ static int64_t budget_nsplit(int64_t batch, int64_t n, int64_t k, int64_t d, int
 
 // Chunks of the split kernels: within that budget, or more while the partial sums fit the built-in scratch array (a few
 // shapes of any n then still spread over the chip, and no call outgrows the array).
-static int64_t split_cap(int64_t batch, int64_t n, int64_t k, int64_t d)
+static int64_t split_cap(int64_t batch, int64_t n, int64_t k, int64_t d, int32_t dtype)
 {
     const int64_t fit = (int64_t)(32u << 20) / (batch * k * d * (int64_t)sizeof(float));
-    return std::max(fit, budget_nsplit(batch, n, k, d, 0));
+    return std::max(fit, budget_nsplit(batch, n, k, d, dtype));
+}
+static int bf16_chunks(int64_t batch, int64_t n, int64_t k, int64_t d)
+{
+    return (int)std::min<int64_t>(bf16_fwd_nsplit(batch, n, k, d), split_cap(batch, n, k, d, 1));
 }
 static int tall_chunks(int64_t batch, int64_t n, int64_t k, int64_t d)
 {
-    return tall_nsplit(batch, n, k, d, split_cap(batch, n, k, d));
+    return tall_nsplit(batch, n, k, d, split_cap(batch, n, k, d, 0));
 }
 static int short_chunks(int64_t batch, int64_t n, int64_t k, int64_t d)
 {
-    return (int)std::min<int64_t>(short_nsplit(batch, n, k, d), split_cap(batch, n, k, d));
+    return (int)std::min<int64_t>(short_nsplit(batch, n, k, d), split_cap(batch, n, k, d, 0));
 }
 
 size_t project_workspace_bytes(int64_t batch, int64_t n, int64_t k, int64_t d, int32_t dtype)
@@ -292,6 +297,7 @@ size_t project_workspace_bytes(int64_t batch, int64_t n, int64_t k, int64_t d, i
     int64_t ns = budget_nsplit(batch, n, k, d, dtype);
     if (dtype == 0 && tall_shape_ok(n, k, d)) ns = std::max<int64_t>(ns, tall_chunks(batch, n, k, d));
     if (dtype == 0 && short_shape_ok(n, k, d)) ns = std::max<int64_t>(ns, short_chunks(batch, n, k, d));
+    if (dtype == 1 && bf16_fwd_shape_ok(n, k, d)) ns = std::max<int64_t>(ns, bf16_chunks(batch, n, k, d));
     if (ns <= 1) return 0;
     return (size_t)batch * ns * k * d * sizeof(float);
 }
@@ -407,8 +413,9 @@ hipError_t launch_project(const void *phi, const float *mass, const void *feat, 
     if (dtype == 0 && short_shape_ok(n, k, d) && aligned16(feat) && aligned16(A) && aligned16(ws))
         return launch_project_short((const float *)phi, mass, (const float *)feat, batch, n, k, d,
                                     short_chunks(batch, n, k, d), A, ws, st);
-    if (dtype == 1 && bf16_fwd_shape_ok(n, k, d) && aligned16(phi) && aligned16(mass) && aligned16(feat))
-        return launch_project_bf16((const uint16_t *)phi, mass, (const uint16_t *)feat, batch, n, k, d, A, ws, st);
+    if (dtype == 1 && bf16_fwd_shape_ok(n, k, d) && aligned16(phi) && aligned16(feat))
+        return launch_project_bf16((const uint16_t *)phi, mass, (const uint16_t *)feat, batch, n, k, d,
+                                   bf16_chunks(batch, n, k, d), A, ws, st);
     ProjPlan p = plan_project(batch, n, k, d, dtype);
     float *out = p.nsplit > 1 ? (float *)ws : A;
     if (dtype == 0) launch_fwd_dt<float>(phi, mass, feat, batch, n, k, d, p, out, st);

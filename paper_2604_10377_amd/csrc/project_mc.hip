@@ -19,6 +19,10 @@
 // only roundings of substance are the bf16 inputs themselves.  A single bf16
 // rounding of the product would add a relative error near 2^-8/sqrt(3) to A
 // for incoherent data, as large as the whole error budget of this path.
+// Vertex counts that are no multiple of 4 take three parts (all 24 bits): they
+// ran in float32 on the general kernel before and keep its precision, at half
+// again the matrix work of two parts (32 shapes of n = 49999, k = 200,
+// d = 384, the step with its solve and backward: 15.6 ms before, 3.0 now).
 //
 // Workgroup = 4 waves = KW row slabs of 64 basis rows x (4/KW) column slabs of
 // 128 feature columns; KW = 4 covers k <= 256 with one 128-column block of d,
@@ -50,6 +54,21 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
     return __builtin_bit_cast(uint32_t, v);
 }
 
+// x (two values per dword) as NP bf16 parts, each the rounding of what the previous parts left
+template <int NP>
+__device__ __forceinline__ void split_pack(float x0, float x1, uint32_t *out)
+{
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        const uint32_t h = pack_bf16(x0, x1);
+        out[p] = h;
+        if (p + 1 < NP) {
+            x0 -= __uint_as_float(h << 16);
+            x1 -= __uint_as_float(h & 0xffff0000u);
+        }
+    }
+}
+
 __device__ __forceinline__ f32x4 mfma16x16x32bf16(u32x4_t a, u32x4_t b, f32x4 c)
 {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b),
@@ -71,7 +90,8 @@ struct Bf16Fwd {
     static constexpr int NPMAX = KW * 4;         // basis windows for k <= 64 KW
 };
 
-template <int KW>
+// PARTS: bf16 parts of basis x mass, 2 or 3.
+template <int KW, int PARTS>
 __global__ __launch_bounds__(256, KW == 4 ? 2 : 1) void proj_fwd_bf16_kernel(const uint16_t *__restrict__ phi,
                                                             const float *__restrict__ mass,
                                                             const uint16_t *__restrict__ feat, int n, int k, int d,
@@ -130,8 +150,8 @@ __global__ __launch_bounds__(256, KW == 4 ? 2 : 1) void proj_fwd_bf16_kernel(con
                 dma16(reinterpret_cast<const float *>(P + (size_t)v * k + off),
                       reinterpret_cast<float *>(S + w * 1024));
             } else {
-                const int off = min(4 * lane, ((rows + 3) & ~3) - 4);
-                dma16(Mv + v + off, reinterpret_cast<float *>(S + (np + C::NF) * 1024));
+                // one mass per lane: any vertex count and shape start (a 16-byte window needs n % 4 == 0)
+                dma4(Mv + v + min(lane, rows - 1), reinterpret_cast<float *>(S + (np + C::NF) * 1024));
             }
         }
     };
@@ -191,18 +211,18 @@ __global__ __launch_bounds__(256, KW == 4 ? 2 : 1) void proj_fwd_bf16_kernel(con
         }
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
-            u32x4_t Ah, Al;
+            u32x4_t Ap[PARTS];
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) {
-                const float p0 = bf16_at(x[2 * jj], a) * mv[2 * jj], p1 = bf16_at(x[2 * jj + 1], a) * mv[2 * jj + 1];
-                const uint32_t hi = pack_bf16(p0, p1);
-                Ah[jj] = hi;
-                Al[jj] = pack_bf16(p0 - __uint_as_float(hi << 16), p1 - __uint_as_float(hi & 0xffff0000u));
+                uint32_t w[PARTS];
+                split_pack<PARTS>(bf16_at(x[2 * jj], a) * mv[2 * jj], bf16_at(x[2 * jj + 1], a) * mv[2 * jj + 1], w);
+#pragma unroll
+                for (int p = 0; p < PARTS; ++p) Ap[p][jj] = w[p];
             }
 #pragma unroll
-            for (int b = 0; b < 8; ++b) acc[a][b] = mfma16x16x32bf16(Ah, B[b], acc[a][b]);
+            for (int p = 0; p < PARTS; ++p)
 #pragma unroll
-            for (int b = 0; b < 8; ++b) acc[a][b] = mfma16x16x32bf16(Al, B[b], acc[a][b]);
+                for (int b = 0; b < 8; ++b) acc[a][b] = mfma16x16x32bf16(Ap[p], B[b], acc[a][b]);
         }
         lds_barrier();  // the slot is refilled by the next iteration's issue
     }
@@ -229,7 +249,7 @@ static int bf16_kw(int64_t k) { return k <= 64 ? 1 : (k <= 128 ? 2 : 4); }
 
 bool bf16_fwd_shape_ok(int64_t n, int64_t k, int64_t d)
 {
-    return k >= 8 && k <= 256 && k % 8 == 0 && d >= 8 && d % 8 == 0 && n % 4 == 0 && n >= 4 * BS;
+    return k >= 8 && k <= 256 && k % 8 == 0 && d >= 8 && d % 8 == 0 && n >= 4 * BS;
 }
 
 int bf16_fwd_nsplit(int64_t batch, int64_t n, int64_t k, int64_t d)
@@ -244,7 +264,7 @@ int bf16_fwd_nsplit(int64_t batch, int64_t n, int64_t k, int64_t d)
     return (int)ns;
 }
 
-template <int KW>
+template <int KW, int PARTS>
 static hipError_t dispatch_bf16(const uint16_t *phi, const float *mass, const uint16_t *feat, int64_t batch,
                                 int64_t n, int64_t k, int64_t d, int ns, float *out, hipStream_t st)
 {
@@ -253,50 +273,46 @@ static hipError_t dispatch_bf16(const uint16_t *phi, const float *mass, const ui
     const size_t lds = (size_t)BNST * (np + C::NF + 1) * 1024;
     static bool attr_set = false;
     if (!attr_set) {
-        (void)hipFuncSetAttribute((const void *)proj_fwd_bf16_kernel<KW>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        (void)hipFuncSetAttribute((const void *)proj_fwd_bf16_kernel<KW, PARTS>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                   (int)((size_t)BNST * (C::NPMAX + C::NF + 1) * 1024));
         attr_set = true;
     }
     const int dblocks = (int)((d + C::DWG - 1) / C::DWG);
     const int ntiles = (int)(batch * ns);
     const unsigned grid = (unsigned)(8 * dblocks * ((ntiles + 7) / 8));
-    hipLaunchKernelGGL((proj_fwd_bf16_kernel<KW>), dim3(grid), dim3(256), lds, st, phi, mass, feat, (int)n, (int)k,
+    hipLaunchKernelGGL((proj_fwd_bf16_kernel<KW, PARTS>), dim3(grid), dim3(256), lds, st, phi, mass, feat, (int)n, (int)k,
                        (int)d, ns, dblocks, ntiles, out);
     return hipGetLastError();
 }
 
-// Partials go to `ws` ([batch][nsplit][k][d]) when nsplit > 1, else straight to A.
+// Partials go to `ws` ([batch][ns][k][d]) when ns > 1 (at most a quarter of the 32-vertex stages), else straight to A.
 hipError_t launch_project_bf16(const uint16_t *phi, const float *mass, const uint16_t *feat, int64_t batch, int64_t n,
-                               int64_t k, int64_t d, float *A, void *ws, hipStream_t st)
+                               int64_t k, int64_t d, int ns, float *A, void *ws, hipStream_t st)
 {
-    const int ns = bf16_fwd_nsplit(batch, n, k, d);
     float *out = ns > 1 ? (float *)ws : A;
     hipError_t e;
+#define FMAP_BF(KW)                                                                              \
+    e = n % 4 == 0 ? dispatch_bf16<KW, 2>(phi, mass, feat, batch, n, k, d, ns, out, st)          \
+                   : dispatch_bf16<KW, 3>(phi, mass, feat, batch, n, k, d, ns, out, st)
     switch (bf16_kw(k)) {
-    case 1: e = dispatch_bf16<1>(phi, mass, feat, batch, n, k, d, ns, out, st); break;
-    case 2: e = dispatch_bf16<2>(phi, mass, feat, batch, n, k, d, ns, out, st); break;
-    default: e = dispatch_bf16<4>(phi, mass, feat, batch, n, k, d, ns, out, st); break;
+    case 1: FMAP_BF(1); break;
+    case 2: FMAP_BF(2); break;
+    default: FMAP_BF(4); break;
     }
+#undef FMAP_BF
     if (e != hipSuccess || ns <= 1) return e;
     return launch_reduce(out, ns, batch, k, d, A, st);
 }
 
 // ---------------------------------------------------------------------------
-// Backward projection dF = diag(M) Phi dA on the bf16 matrix cores, for a bf16
-// basis (an exact operand) or a float32 basis.
-//
-// The float32 matrix rate of this GPU is 1/16 of its bf16 rate, so float32
-// products are emulated: x = h + m + l with h, m, l bf16 (each the rounding of
-// what is left), and the six products whose part indices sum to at most 2
-// (hh, hm, mh, hl, lh, mm) are accumulated in float32.  The dropped terms are
-// below 2^-24 relative, the float32 level; the six bf16 steps cost 6/16 of the
-// matrix time of the float32 step.  With a bf16 basis, dA alone is split
-// (hi + lo: 2^-16 relative).
+// Backward projection dF = diag(M) Phi dA on the bf16 matrix cores for a bf16
+// basis, an exact operand; the float32 dA is split into two bf16 parts (hi + lo:
+// 2^-16 relative), both multiplied with float32 accumulation.
 //
 // The contraction runs over k, contiguous in a basis row, so a lane's 8 K
-// slots are one row segment of its vertex: one 16-byte load (bf16) or two
-// (float32), no transpose.  dA^T is staged once per workgroup in LDS as its bf16
-// parts in [column][k] layout, so each operand is one ds_read_b128.  The roles
+// slots are one row segment of its vertex: one 16-byte load, no transpose.  dA^T
+// is staged once per workgroup in LDS as its bf16 parts in [column][k] layout, so
+// each operand is one ds_read_b128.  The roles
 // are chosen so that a lane ends up holding 4 consecutive columns of one vertex:
 // the results leave as 16-byte stores, with the mass applied in float32.
 //
@@ -332,71 +348,21 @@ __host__ __device__ constexpr size_t bwdmc_lds(int pd, int ks)
 __device__ __forceinline__ void stream_store(f32x4 *p, f32x4 v) { __builtin_nontemporal_store(v, p); }
 __device__ __forceinline__ void stream_store(float *p, float v) { __builtin_nontemporal_store(v, p); }
 
-// x (two values per dword) as NP bf16 parts, each the rounding of what the previous parts left
-template <int NP>
-__device__ __forceinline__ void split_pack(float x0, float x1, uint32_t *out)
-{
-#pragma unroll
-    for (int p = 0; p < NP; ++p) {
-        const uint32_t h = pack_bf16(x0, x1);
-        out[p] = h;
-        if (p + 1 < NP) {
-            x0 -= __uint_as_float(h << 16);
-            x1 -= __uint_as_float(h & 0xffff0000u);
-        }
-    }
-}
-
-template <typename T> struct RowSeg;  // 8 consecutive basis entries of one vertex row
-template <> struct RowSeg<uint16_t> { u32x4_t v; };
-template <> struct RowSeg<float> { f32x4 lo, hi; };
-
 // Loads are unconditional, from addresses clamped into the row; slots past k are zeroed only when
 // the operand is formed.  (A branch around each load, or a select right after it, would make the
 // compiler wait for the loads at that point and so defeat the prefetch of the next tile.)
-// bf16 rows: k % 8 == 0, so a lane's 8 slots starting at kk all exist or none do.
-__device__ __forceinline__ RowSeg<uint16_t> load_seg_bf16(const uint16_t *row, int kk, int k)
+// k % 8 == 0, so a lane's 8 slots starting at kk all exist or none do.
+__device__ __forceinline__ u32x4_t load_seg(const uint16_t *row, int kk, int k)
 {
-    RowSeg<uint16_t> r;
-    r.v = *reinterpret_cast<const u32x4_t *>(row + min(kk, k - 8));
-    return r;
-}
-// float32 rows need only be 8-byte aligned (k even): four pairs
-__device__ __forceinline__ RowSeg<float> load_seg_f32(const float *row, int kk, int k)
-{
-    RowSeg<float> r;
-    float2 q[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) q[i] = *reinterpret_cast<const float2 *>(row + min(kk + 2 * i, k - 2));
-    r.lo = f32x4{q[0].x, q[0].y, q[1].x, q[1].y};
-    r.hi = f32x4{q[2].x, q[2].y, q[3].x, q[3].y};
-    return r;
+    return *reinterpret_cast<const u32x4_t *>(row + min(kk, k - 8));
 }
 
-// the basis operand parts of one row segment starting at slot kk (slots >= k are zero)
-template <int PP>
-__device__ __forceinline__ void seg_parts(const RowSeg<uint16_t> &r, int kk, int k, u32x4_t *B)
-{
-    B[0] = (kk < k) ? r.v : u32x4_t{0, 0, 0, 0};
-}
-template <int PP>
-__device__ __forceinline__ void seg_parts(const RowSeg<float> &r, int kk, int k, u32x4_t *B)
-{
-    const float x[8] = {r.lo[0], r.lo[1], r.lo[2], r.lo[3], r.hi[0], r.hi[1], r.hi[2], r.hi[3]};
-    uint32_t w[4][PP];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const bool ok = kk + 2 * i < k;  // k even: both values of the pair exist or neither
-        split_pack<PP>(ok ? x[2 * i] : 0.f, ok ? x[2 * i + 1] : 0.f, w[i]);
-    }
-#pragma unroll
-    for (int p = 0; p < PP; ++p) B[p] = u32x4_t{w[0][p], w[1][p], w[2][p], w[3][p]};
-}
+constexpr int PD = 2;  // bf16 parts of dA
 
 // One workgroup's block: 256-vertex tiles [t0, t1) of one shape (basis P, masses Mv, G = dA, O = dF) for the
 // columns [dbase, dbase + 128).
-template <typename T, int PP, int PD, int KS>
-__device__ __forceinline__ void bwdmc_block(const T *__restrict__ P, const float *__restrict__ Mv,
+template <int KS>
+__device__ __forceinline__ void bwdmc_block(const uint16_t *__restrict__ P, const float *__restrict__ Mv,
                                             const float *__restrict__ G, float *__restrict__ O, int n, int k, int d,
                                             int t0, int t1, int dbase)
 {
@@ -430,35 +396,30 @@ __device__ __forceinline__ void bwdmc_block(const T *__restrict__ P, const float
     const bool vec = (d & 3) == 0;
 
     // basis row segments of a tile: [k step][vertex tile of 16]; rows past n are clamped (never stored)
-    // raw row segments per buffer: 16 registers per k step (float32) or 8 (bf16)
-    constexpr int NBUF = (KS * (PP == 1 ? 8 : 16) <= 36) ? 3 : 2;
-    RowSeg<T> buf0[KS][2], buf1[KS][2], buf2[NBUF == 3 ? KS : 1][2];
+    // raw row segments per buffer: 8 registers per k step
+    constexpr int NBUF = KS * 8 <= 36 ? 3 : 2;
+    u32x4_t buf0[KS][2], buf1[KS][2], buf2[NBUF == 3 ? KS : 1][2];
     float m0[2], m1[2], m2[2];
-    auto load_tile = [&](int vt, RowSeg<T> (&r)[KS][2], float (&mv)[2]) {
+    auto load_tile = [&](int vt, u32x4_t (&r)[KS][2], float (&mv)[2]) {
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt) {
             const int v = min(vt * BB_VT + wave * 32 + nt * 16 + m16, n - 1);
             mv[nt] = Mv[v];
-            const T *row = P + (size_t)v * k;
+            const uint16_t *row = P + (size_t)v * k;
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                if constexpr (PP == 1)
-                    r[ks][nt] = load_seg_bf16(row, ks * 32 + 8 * g4, k);
-                else
-                    r[ks][nt] = load_seg_f32(row, ks * 32 + 8 * g4, k);
-            }
+            for (int ks = 0; ks < KS; ++ks) r[ks][nt] = load_seg(row, ks * 32 + 8 * g4, k);
         }
     };
     // Columns are produced 32 at a time (an M-tile pair) over all K steps, and stored right away, so
-    // the stores of one pair drain while the next pair's products run.  The basis operand parts of
-    // the whole tile are formed once.
+    // the stores of one pair drain while the next pair's products run.
     const bool fullcols = vec && dbase + BB_COLS <= d;  // the common case: no column checks
-    auto compute_store = [&](int vt, const RowSeg<T> (&cur)[KS][2], const float (&mv)[2]) {
-        u32x4_t B[KS][2][PP];
+    auto compute_store = [&](int vt, const u32x4_t (&cur)[KS][2], const float (&mv)[2]) {
+        u32x4_t B[KS][2];  // zero past k
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-            for (int nt = 0; nt < 2; ++nt) seg_parts<PP>(cur[ks][nt], ks * 32 + 8 * g4, k, B[ks][nt]);
+            for (int nt = 0; nt < 2; ++nt)
+                B[ks][nt] = ks * 32 + 8 * g4 < k ? cur[ks][nt] : u32x4_t{0, 0, 0, 0};
         const int vrow = vt * BB_VT + wave * 32 + m16;
 #pragma unroll
         for (int mp = 0; mp < 8; mp += 2) {
@@ -479,16 +440,11 @@ __device__ __forceinline__ void bwdmc_block(const T *__restrict__ P, const float
                                                                     2 * (ks * 32 + 8 * g4));
                 // four independent accumulators between dependent matrix-core steps
 #pragma unroll
-                for (int i = 0; i < PP; ++i)
+                for (int p = 0; p < PD; ++p)
 #pragma unroll
-                    for (int jp = 0; jp < PD; ++jp)
-                        if (i + jp <= 2) {
+                    for (int h = 0; h < 2; ++h)
 #pragma unroll
-                            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                                for (int nt = 0; nt < 2; ++nt)
-                                    acc[h][nt] = mfma16x16x32bf16(A[h][jp], B[ks][nt][i], acc[h][nt]);
-                        }
+                        for (int nt = 0; nt < 2; ++nt) acc[h][nt] = mfma16x16x32bf16(A[h][p], B[ks][nt], acc[h][nt]);
             }
             // D layout: register r of lane (m16, g4) is column 4*g4 + r of the column tile, vertex m16
             if constexpr (TR) {
@@ -587,8 +543,9 @@ __device__ __forceinline__ void bwdmc_block(const T *__restrict__ P, const float
     }
 }
 
-template <typename T, int PP, int PD, int KS>
-__global__ __launch_bounds__(512, 2) void proj_bwd_mc_kernel(const T *__restrict__ phi, const float *__restrict__ mass,
+template <int KS>
+__global__ __launch_bounds__(512, 2) void proj_bwd_mc_kernel(const uint16_t *__restrict__ phi,
+                                                           const float *__restrict__ mass,
                                                            const float *__restrict__ dA, int n, int k, int d,
                                                            int vsplit, int dblocks, int ntasks,
                                                            float *__restrict__ dF)
@@ -601,8 +558,8 @@ __global__ __launch_bounds__(512, 2) void proj_bwd_mc_kernel(const T *__restrict
     const int vs = j % vsplit, s = j / vsplit;
     const int ntile = (n + BB_VT - 1) / BB_VT;
     const int t0 = (int)(((long)vs * ntile) / vsplit), t1 = (int)(((long)(vs + 1) * ntile) / vsplit);
-    bwdmc_block<T, PP, PD, KS>(phi + (size_t)s * n * k, mass + (size_t)s * n, dA + (size_t)s * k * d,
-                               dF + (size_t)s * n * d, n, k, d, t0, t1, db * BB_COLS);
+    bwdmc_block<KS>(phi + (size_t)s * n * k, mass + (size_t)s * n, dA + (size_t)s * k * d, dF + (size_t)s * n * d, n, k,
+                    d, t0, t1, db * BB_COLS);
 }
 
 constexpr int XS = 32;  // vertices per stage (one matrix-core K step)
@@ -896,14 +853,14 @@ static int bwdmc_vsplit(int64_t batch, int64_t dblocks, int64_t ntile, int per_c
     return best;
 }
 
-template <typename T, int PP, int PD, int KS>
-static hipError_t dispatch_bwdmc(const T *phi, const float *mass, const float *dA, int64_t batch, int64_t n, int64_t k,
+template <int KS>
+static hipError_t dispatch_bwdmc(const uint16_t *phi, const float *mass, const float *dA, int64_t batch, int64_t n, int64_t k,
                                  int64_t d, float *dF, hipStream_t st)
 {
     const size_t lds = bwdmc_lds(PD, KS);
     static bool attr_set = false;
     if (!attr_set) {
-        (void)hipFuncSetAttribute((const void *)proj_bwd_mc_kernel<T, PP, PD, KS>,
+        (void)hipFuncSetAttribute((const void *)proj_bwd_mc_kernel<KS>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         attr_set = true;
     }
@@ -912,7 +869,7 @@ static hipError_t dispatch_bwdmc(const T *phi, const float *mass, const float *d
     static int per_cu = 0;  // resident workgroups per CU (registers and LDS), queried once
     if (per_cu == 0) {
         int r = 1;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&r, (const void *)proj_bwd_mc_kernel<T, PP, PD, KS>, 512,
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&r, (const void *)proj_bwd_mc_kernel<KS>, 512,
                                                          lds) != hipSuccess || r < 1)
             r = 1;
         per_cu = r;
@@ -920,7 +877,7 @@ static hipError_t dispatch_bwdmc(const T *phi, const float *mass, const float *d
     const int vsplit = bwdmc_vsplit(batch, dblocks, ntile, per_cu);
     const int ntasks = (int)(batch * vsplit);
     const unsigned grid = (unsigned)(8 * dblocks * ((ntasks + 7) / 8));
-    hipLaunchKernelGGL((proj_bwd_mc_kernel<T, PP, PD, KS>), dim3(grid), dim3(512), lds, st, phi, mass, dA, (int)n,
+    hipLaunchKernelGGL((proj_bwd_mc_kernel<KS>), dim3(grid), dim3(512), lds, st, phi, mass, dA, (int)n,
                        (int)k, (int)d, vsplit, dblocks, ntasks, dF);
     return hipGetLastError();
 }
@@ -929,14 +886,14 @@ hipError_t launch_project_backward_bf16(const uint16_t *phi, const float *mass, 
                                         int64_t n, int64_t k, int64_t d, float *dF, hipStream_t st)
 {
     switch (bwdmc_ks(k)) {
-    case 1: return dispatch_bwdmc<uint16_t, 1, 2, 1>(phi, mass, dA, batch, n, k, d, dF, st);
-    case 2: return dispatch_bwdmc<uint16_t, 1, 2, 2>(phi, mass, dA, batch, n, k, d, dF, st);
-    case 3: return dispatch_bwdmc<uint16_t, 1, 2, 3>(phi, mass, dA, batch, n, k, d, dF, st);
-    case 4: return dispatch_bwdmc<uint16_t, 1, 2, 4>(phi, mass, dA, batch, n, k, d, dF, st);
-    case 5: return dispatch_bwdmc<uint16_t, 1, 2, 5>(phi, mass, dA, batch, n, k, d, dF, st);
-    case 6: return dispatch_bwdmc<uint16_t, 1, 2, 6>(phi, mass, dA, batch, n, k, d, dF, st);
-    case 7: return dispatch_bwdmc<uint16_t, 1, 2, 7>(phi, mass, dA, batch, n, k, d, dF, st);
-    default: return dispatch_bwdmc<uint16_t, 1, 2, 8>(phi, mass, dA, batch, n, k, d, dF, st);
+    case 1: return dispatch_bwdmc<1>(phi, mass, dA, batch, n, k, d, dF, st);
+    case 2: return dispatch_bwdmc<2>(phi, mass, dA, batch, n, k, d, dF, st);
+    case 3: return dispatch_bwdmc<3>(phi, mass, dA, batch, n, k, d, dF, st);
+    case 4: return dispatch_bwdmc<4>(phi, mass, dA, batch, n, k, d, dF, st);
+    case 5: return dispatch_bwdmc<5>(phi, mass, dA, batch, n, k, d, dF, st);
+    case 6: return dispatch_bwdmc<6>(phi, mass, dA, batch, n, k, d, dF, st);
+    case 7: return dispatch_bwdmc<7>(phi, mass, dA, batch, n, k, d, dF, st);
+    default: return dispatch_bwdmc<8>(phi, mass, dA, batch, n, k, d, dF, st);
     }
 }
 

@@ -174,23 +174,27 @@ def phase_costs(b, bf16: bool):
 def matrix_peak(phase: str, b, bf16: bool):
     """(TFLOP/s of useful products, note) for the matrix cores the library dispatches for this phase.
 
-    The bf16 paths run the bf16 matrix cores (2500 TFLOP/s dense) with more than one bf16 product per
-    useful product: basis x mass (forward) or dA (backward) split in two, or, for float32 operands,
-    both operands split in three with six products kept.  Shapes outside those paths use the float32
-    matrix cores (157.3 TFLOP/s)."""
+    The bf16 paths run the 16-bit matrix cores (2500 TFLOP/s dense) with more than one product per useful
+    product: basis x mass (forward; in three for n % 4 != 0) or dA (backward) split in two.  Float32 operands
+    are split in two float16 parts each with three products kept (in three bf16 parts with six for a forward
+    with d < 5 k / 4).  Shapes outside those paths use the float32 matrix cores (157.3 TFLOP/s)."""
     n, k, d = b.n, b.k, b.d
+    three = BF16_PEAK_TFLOPS / 3, "float16 matrix cores, float32 as 3 products of float16 parts"
     if phase == "project":
-        if bf16 and k % 8 == 0 and 8 <= k <= 256 and d % 8 == 0 and n % 4 == 0 and n >= 128:
-            return BF16_PEAK_TFLOPS / 2, "bf16 matrix cores, 2 bf16 products per product"
-        kok = (k % 2 == 0 and 4 <= k <= 64) or (k % 4 == 0 and 64 < k <= 319)
-        if not bf16 and kok and d % 4 == 0 and n % 4 == 0 and n >= 128:
-            return BF16_PEAK_TFLOPS / 6, "bf16 matrix cores, float32 emulated with 6 bf16 products"
+        if bf16 and k % 8 == 0 and 8 <= k <= 256 and d % 8 == 0 and n >= 128:
+            parts = 2 if n % 4 == 0 else 3
+            return BF16_PEAK_TFLOPS / parts, f"bf16 matrix cores, {parts} bf16 products per product"
+        if not bf16 and k <= 319 and d % 4 == 0 and n >= 128:
+            if k <= 64 or 4 * d >= 5 * k:
+                return three
+            if k % 4 == 0 and n % 4 == 0:
+                return BF16_PEAK_TFLOPS / 6, "bf16 matrix cores, float32 as 6 products of bf16 parts"
         return FP32_PEAK_TFLOPS, "float32 matrix cores"
     if phase == "project_backward":
         if bf16 and k % 8 == 0 and 8 <= k <= 256:
             return BF16_PEAK_TFLOPS / 2, "bf16 matrix cores, 2 bf16 products per product"
-        if not bf16 and k % 2 == 0 and 2 <= k <= 319:
-            return BF16_PEAK_TFLOPS / 6, "bf16 matrix cores, float32 emulated with 6 bf16 products"
+        if not bf16 and 4 <= k <= 319:
+            return three
         return FP32_PEAK_TFLOPS, "float32 matrix cores"
     return FP32_PEAK_TFLOPS, "float32"
 
@@ -208,8 +212,8 @@ def roofline_entry(flops, nbytes, seconds, mfma_peak_tflops):
 
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "headline_hbm_traffic.txt")
-KERNEL_OF_PHASE = {"project": "fmap::proj_fwd_x3r_kernel<false>",
-                   "project_backward": "fmap::proj_bwd_mc_kernel<float, 3, 3, 2>"}
+KERNEL_OF_PHASE = {"project": "fmap::proj_fwd_h2_kernel<7>",
+                   "project_backward": "fmap::proj_bwd_split_kernel<2, 8>"}
 
 
 def measured_traffic(phase: str, workload: str, pairs_per_launch: int):
@@ -227,16 +231,18 @@ def measured_traffic(phase: str, workload: str, pairs_per_launch: int):
     src = [ln for ln in lines if ln.startswith("source: ")]
     if not src:
         return None
-    rel, _, want = src[0][len("source: "):].split()[:3]
-    have = hashlib.sha256(open(os.path.join(ROOT, rel), "rb").read()).hexdigest()[:16]
-    if have != want:
-        return None
+    wants = []
+    for ln in src:  # every kernel source of the summary
+        rel, _, want = ln[len("source: "):].split()[:3]
+        if hashlib.sha256(open(os.path.join(ROOT, rel), "rb").read()).hexdigest()[:16] != want:
+            return None
+        wants.append(want)
     name = KERNEL_OF_PHASE[phase]
     for ln in lines:
         if ln.startswith(name + " ") or ln.startswith("void " + name + " "):
             read_mb, write_mb = (float(x) for x in ln.split()[-2:])
             return {"bytes": round((read_mb + write_mb) * 1e6), "read_MB": read_mb, "write_MB": write_mb,
-                    "kernel": name, "source_sha256": want}
+                    "kernel": name, "source_sha256": " ".join(wants)}
     return None
 
 
@@ -387,7 +393,7 @@ def ragged_costs(pairs, d):
             sb = SimpleNamespace(pairs=1, n=n, k=p.k, d=d)
             c = phase_costs(sb, False)
             # phase_costs counts a pair (two shapes of n vertices): halve the projection terms per shape
-            # the plan runs whole 32-vertex stages of any n on the emulated kernel: price by k and d only
+            # the plan's split kernels take any n: price by k and d only
             add("fwd", c["project"][0] / 2, c["project"][1] / 2,
                 matrix_peak("project", SimpleNamespace(pairs=1, n=128, k=p.k, d=d), False)[0])
             add("bwd", c["project_backward"][0] / 2, c["project_backward"][1] / 2,
@@ -446,7 +452,7 @@ def bench_ragged(args, F, dev):
     dom = max(pass_ms, key=pass_ms.get)
     fl, by, tm = costs[dom]
     roof = roofline_entry(fl, by, pass_ms[dom] * 1e-3, fl / tm / 1e12)  # effective peak of the pass's mix
-    roof["kernel"] = f"plan {dom} pass (graph: projection items on the emulated float32 kernels + grouped solves)"
+    roof["kernel"] = f"plan {dom} pass (graph: projection items on the split float32 kernels + grouped solves)"
     roof["traffic"] = None
     roof["pass_us"] = {k: round(v * 1e3, 2) for k, v in pass_ms.items()}
     t_roof = sum(max(t, b_ / (HBM_PEAK_GBS * 1e9)) for _, b_, t in costs.values())
@@ -613,7 +619,7 @@ def bench_overlap(args, F, dev):
     ms, stats = timed_calls(call, args, stream)
     nbytes = total * 5 + 8 * (S + 1) + S * (4 * 8 + 7 * 4)
     roof = roofline_entry(0.0, nbytes, ms * 1e-3, FP32_PEAK_TFLOPS)
-    roof["kernel"] = "fmap_overlap_metrics (clear, count, metrics kernels; the count pass carries the bytes)"
+    roof["kernel"] = "fmap_overlap_metrics (overlap_shapes_kernel carries the bytes)"
     roof["traffic"] = None
     counts.zero_()
     call()
@@ -673,8 +679,8 @@ def bench_gradfeat(args, F, dev):
     ms, stats = timed_calls(call, args, stream)
     flops = 8.0 * D * D * V + 3.0 * D * V
     nbytes = V * D * 12 + 2 * D * D * 4
-    roof = roofline_entry(flops, nbytes, ms * 1e-3, FP32_PEAK_TFLOPS)
-    roof["kernel"] = f"gradfeat_mfma_kernel<{D}> (float32 matrix cores)"
+    roof = roofline_entry(flops, nbytes, ms * 1e-3, BF16_PEAK_TFLOPS / 3)
+    roof["kernel"] = f"gradient features, D = {D} (float16 matrix cores, float32 as 3 products of float16 parts)"
     roof["traffic"] = None
     F.fmap_gradient_features(zs[0], tAr, tAi, args.variant, g=g)
     torch.cuda.synchronize()
@@ -822,7 +828,7 @@ def bench_multires(args, F, dev):
     sb = SimpleNamespace_(pairs=P, n=n, k=k, d=d)
     flops, nbytes = phase_costs(sb, False)["project"]
     roof = roofline_entry(flops, nbytes, tp * 1e-3, matrix_peak("project", sb, False)[0])
-    roof["kernel"] = "fmap_project at k = 120 (float32 emulated on the bf16 matrix cores)"
+    roof["kernel"] = "fmap_project at k = 120 (float32 on the float16 matrix cores)"
     roof["traffic"] = None
     roof["phase_us"] = {"project": round(tp * 1e3, 2), "solve_resolutions": round(ts * 1e3, 2)}
     # accuracy of pairs 0 and P-1 at every resolution, from one replay into NaN-filled outputs

@@ -463,10 +463,16 @@ hipError_t record_groups(fmap_plan *pl, hipStream_t st, bool branch, bool tiled_
     for (hipStream_t q : pl->side)
         if ((int)lanes.size() < nsmall) lanes.push_back(q);
     const hipStream_t first = lanes[0];
-    // Both parts in line where the sliced kernel takes shapes (d close to k): beside it the small shapes' kernel and the
-    // solves lose more than the overlap gives (d = 128, forward only: 11 pairs 265 us on branches, 241 in line, 254
-    // unbranched before; forward and backward: 8 pairs 291 against 266, 14 pairs 396 against 366).
-    const bool parts_in_line = pl->nsliced > 0;
+    // Both parts in line where the k > 64 part fills the chip (its inputs 60 MB or more) or the sliced kernel takes shapes
+    // (d close to k): the small shapes' kernel beside it then costs it and the solves more than the overlap gives.  d = 256,
+    // inputs of that part 39, 48 | 72, 100, 114 MB: on branches 140, 238 | 321, 294, 364 us, in line 171, 270 | 291, 273,
+    // 333.  d = 128: 11 pairs forward 265 us on branches, 241 in line; 14 pairs forward and backward 396 against 366.
+    double large_bytes = 0;
+    for (const Bucket &B : pl->buckets)
+        if (B.k > kSmallK)
+            for (int i : B.pairs)
+                large_bytes += 4.0 * ((double)pl->pairs[i].n_x + (double)pl->pairs[i].n_y) * (double)(B.k + pl->d);
+    const bool parts_in_line = nlarge > 0 && (pl->nsliced > 0 || large_bytes >= 60e6);
     if (parts_in_line) {
         if (nlarge > 0) e = part(1, st);
         if (e == hipSuccess) e = part(0, st);

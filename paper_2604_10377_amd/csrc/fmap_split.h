@@ -24,6 +24,9 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 // Scaled values of this magnitude or more do not fit (the largest float16 is 65504).
 constexpr float kSplitLimit = 65000.f;
+// The least that the largest scaled magnitude of a row or column may be: the parts resolve 2^-25, 2^-29 of it, where
+// float32 keeps 2^-24.
+constexpr float kSplitLeast = 16.f;
 
 // Power-of-two shift that brings values of magnitude <= |m| (given as float bits, sign clear) below 2^(TOP + 1):
 // [2^TOP, 2^(TOP + 1)) for normal m.  With TOP = 13 values up to 4 |m| fit, with TOP = 9 up to 64 |m| (values below

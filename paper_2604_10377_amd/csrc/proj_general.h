@@ -1,6 +1,6 @@
 // The general forward projection of one block on the float32 matrix cores (v_mfma_f32_32x32x2f32): any n, k, d and
-// alignment, float32 or bf16 inputs.  The general kernels run it for every block; the split kernel of k <= 64 for a
-// chunk whose values do not fit its scales.
+// alignment, float32 or bf16 inputs.  The general kernels run it for every block; the split kernels for a chunk whose
+// values do not fit their scales.
 #pragma once
 
 #include "fmap_device.h"
@@ -15,16 +15,15 @@ template <>
 __device__ __forceinline__ float load_elem<uint16_t>(const uint16_t *p, size_t i) { return bf16_to_f32(p[i]); }
 
 // One (shape, vertex range, k-block, column block) of the forward projection:
-// partial A rows [kbase, kbase + MT*32) x columns [dbase4 + wave*NT*32, ...)
-// over vertices [v0, v1), written to O (row-major k x d).
+// this wave's partial A rows [kbase, kbase + MT*32) x columns [dbase, dbase + NT*32)
+// over vertices [v0, v1), written to O (row-major k x d).  No barriers.
 template <typename T, int MT, int NT, int U>
 __device__ __forceinline__ void proj_fwd_tile(const T *__restrict__ P, const float *__restrict__ Mv,
                                               const T *__restrict__ F, int k, int d, int v0, int v1, int kbase,
-                                              int dbase4, float *__restrict__ O)
+                                              int dbase, float *__restrict__ O)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63;
     const int half = lane >> 5, l32 = lane & 31;
-    const int dbase = dbase4 + wave * (NT * 32);
     if (dbase >= d) return;  // whole wave idle (narrow d)
 
     int rows[MT], cols[NT];

@@ -42,7 +42,7 @@ __global__ __launch_bounds__(256) void proj_fwd_kernel(const T *__restrict__ phi
     const int v0 = split * chunk;
     const int v1 = min(n, v0 + chunk);
     proj_fwd_tile<T, MT, NT, U>(phi + (size_t)s * n * k, mass + (size_t)s * n, feat + (size_t)s * n * d, k, d, v0, v1,
-                                kb * (MT * 32), db * 4 * (NT * 32),
+                                kb * (MT * 32), (db * 4 + (threadIdx.x >> 6)) * (NT * 32),
                                 out + ((size_t)s * nsplit + split) * (size_t)k * d);
 }
 
@@ -54,7 +54,7 @@ __global__ __launch_bounds__(256) void proj_fwd_items_kernel(const FwdItem *__re
     for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
         const FwdItem w = items[it];
         proj_fwd_tile<float, MT, NT, U>(global_ptr(w.phi), global_ptr(w.mass), global_ptr(w.feat), w.k, w.d, w.v0, w.v1,
-                                        w.kbase, w.dbase, global_ptr(w.out));
+                                        w.kbase, w.dbase + (threadIdx.x >> 6) * (NT * 32), global_ptr(w.out));
     }
 }
 

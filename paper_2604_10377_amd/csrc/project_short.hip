@@ -226,7 +226,7 @@ __device__ __forceinline__ void h2_block(const float *__restrict__ P, const floa
     if (!(big < kSplitLimit)) s_sh[64] = 1;
     __syncthreads();
     if (__builtin_amdgcn_readfirstlane(s_sh[64]) != 0) {
-        proj_fwd_tile<float, 2, 2, 4>(P, Mv, F, k, d, vbeg, vend, 0, dbase, O);
+        proj_fwd_tile<float, 2, 2, 4>(P, Mv, F, k, d, vbeg, vend, 0, dbase + 64 * wave, O);
         return;
     }
 

@@ -11,8 +11,11 @@
 //
 // Each basis row and each feature column has its own power-of-two scale in LDS, taken from the first stage; a value
 // that does not fit raises a flag that the whole workgroup sees at the next stage, where the scales and the sums are
-// lowered together and the stage is split again.  Loads go through one buffer descriptor per vertex row, whose range
-// ends with the chunk: vertices past its end read as zeros.
+// lowered together and the stage is split again.  A row or column that is all zeros so far has no value to take a scale
+// from and borrows that of the largest one; its largest value is known at the end of the chunk, and where that lies
+// too low on the borrowed scale to keep its bits, or where a value is infinite, the general float32 routine computes
+// the chunk again.  Loads go through one buffer descriptor per vertex row, whose range ends with the chunk: vertices
+// past its end read as zeros.
 //
 // Instances by k: 4 x 64 columns for k <= 128 (RG = 2 row groups of RT = 4 tiles; d = 128: RG = 4, RT = 2), 2 x 64 above
 // (RG = 4, RT = 3, 4, 5).
@@ -28,6 +31,7 @@
 #include "fmap_lds.h"
 #include "fmap_launch.h"
 #include "fmap_split.h"
+#include "proj_general.h"
 
 namespace fmap {
 
@@ -45,7 +49,7 @@ struct Tall {
     static constexpr int AT = RG * RT, BT = 4 * CG;
     // 16-byte slots: the two buffers of basis tiles, the two of feature tiles, slots that idle threads write
     static constexpr int ABUF = AT * 2 * TILE, BBUF = BT * 2 * TILE, IDLE = 2 * (ABUF + BBUF);
-    static constexpr size_t LDS = (size_t)(IDLE + 2 * TILE) * 16 + (ROWS + COLS) * 12 + 16;
+    static constexpr size_t LDS = (size_t)(IDLE + 2 * TILE) * 16 + (ROWS + COLS) * 12 + 32;
 };
 
 template <int RG, int RT>
@@ -56,11 +60,13 @@ __device__ __forceinline__ void tall_block(const float *__restrict__ P, const fl
     using C = Tall<RG, RT>;
     extern __shared__ __align__(16) float smem[];
     u32x4_t *buf = reinterpret_cast<u32x4_t *>(smem);
-    uint32_t *s_mx = reinterpret_cast<uint32_t *>(buf + C::IDLE + 2 * TILE);  // [ROWS + COLS] largest magnitude
+    uint32_t *s_mx = reinterpret_cast<uint32_t *>(buf + C::IDLE + 2 * TILE);  // [ROWS + COLS] largest magnitude so far
     int *s_sh = reinterpret_cast<int *>(s_mx + C::ROWS + C::COLS);      // scale shifts
     int *s_dl = s_sh + C::ROWS + C::COLS;                               // their last changes
     uint32_t *s_top = reinterpret_cast<uint32_t *>(s_dl + C::ROWS + C::COLS);  // [2] basis, features: largest
-    int *s_flag = reinterpret_cast<int *>(s_top + 2);                          // [2] a value of the stage did not fit
+    // [2] of stages t % 2: bit 0, a value does not fit; bit 1 (in both), a scale was borrowed.  [1] the chunk goes to the
+    // general routine
+    int *s_flag = reinterpret_cast<int *>(s_top + 2);
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -153,7 +159,7 @@ __device__ __forceinline__ void tall_block(const float *__restrict__ P, const fl
         float big = 0.f;
 #pragma unroll
         for (int e = 0; e < 4; ++e) split1(t, e, r, big);
-        if (big >= kSplitLimit) s_flag[t & 1] = 1;
+        if (big >= kSplitLimit) atomicOr(&s_flag[t & 1], 1);
     };
 
     f32x4 acc[RT][4];
@@ -162,8 +168,22 @@ __device__ __forceinline__ void tall_block(const float *__restrict__ P, const fl
 #pragma unroll
         for (int c = 0; c < 4; ++c) acc[a][c] = f32x4{0, 0, 0, 0};
 
+    // Follows the largest magnitudes of the (still unweighed) values of stage t, once a row or column has borrowed a scale
+    auto follow = [&](int t, const Raw &r) {
+        const float m = isF ? ((lane & 31) < vend - (vbeg + t * TS) ? r.m : 0.f) : 1.f;
+        float mx[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float mi = __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (8 * tg + i), __float_as_int(m)));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) mx[e] = fmaxf(mx[e], fabsf(r.x[i][e] * mi));
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (active) atomicMax(&s_mx[sidx + e], __float_as_uint(mx[e]));
+    };
     // Lowers the scales so that the (weighed) values r fit, and the sums with them.  Every thread of the workgroup
-    // comes here together.  A row or column that is all zeros so far takes the scale of the largest one (sparse
+    // comes here together.  A row or column that is all zeros so far borrows the scale of the largest one (sparse
     // features: its first values are likely to be as large as the others').
     auto rescale = [&](const Raw &r) {
         if (active) {
@@ -186,7 +206,11 @@ __device__ __forceinline__ void tall_block(const float *__restrict__ P, const fl
             const int old = s_sh[e], now = min(old, split_shift(mx ? mx : s_top[e >= C::ROWS]));
             s_sh[e] = now;
             s_dl[e] = now - old;
-            s_mx[e] = 0;
+            if (mx == 0x7f800000u) s_flag[2] = 1;
+            if (mx == 0 && (e < k || e >= C::ROWS)) {
+                atomicOr(&s_flag[0], 2);
+                atomicOr(&s_flag[1], 2);
+            }
         }
         __syncthreads();
 #pragma unroll
@@ -223,6 +247,7 @@ __device__ __forceinline__ void tall_block(const float *__restrict__ P, const fl
         s_sh[e] = 126;
     }
     if (tid < 2) s_flag[tid] = s_top[tid] = 0;
+    if (tid == 0) s_flag[2] = 0;
     __syncthreads();
     weigh(0, x);
     rescale(x);
@@ -235,13 +260,16 @@ __device__ __forceinline__ void tall_block(const float *__restrict__ P, const fl
     auto stage = [&](int t, Raw &free, Raw &next) {
         const int flag = s_flag[t & 1];
         if (RT <= 4) load_b(t);
-        if (__builtin_amdgcn_readfirstlane(flag) != 0) {
-            issue(t, free);
-            weigh(t, free);
-            rescale(free);
-            split(t, free);
-            __syncthreads();
-            if (tid == 0) s_flag[t & 1] = 0;
+        if (const int bits = __builtin_amdgcn_readfirstlane(flag)) {
+            if (bits & 2) follow(t + 1, next);
+            if (bits & 1) {
+                issue(t, free);
+                weigh(t, free);
+                rescale(free);
+                split(t, free);
+                __syncthreads();
+                if (tid == 0) atomicAnd(&s_flag[t & 1], ~1);
+            }
             if (RT <= 4) load_b(t);
         }
         issue(min(t + 2, nst - 1), free);
@@ -272,12 +300,26 @@ __device__ __forceinline__ void tall_block(const float *__restrict__ P, const fl
             }
             if (RT <= 4) __builtin_amdgcn_sched_barrier(0);
         }
-        if (big >= kSplitLimit) s_flag[(t + 1) & 1] = 1;
+        if (big >= kSplitLimit) atomicOr(&s_flag[(t + 1) & 1], 1);
         lds_barrier();
     };
     for (int t = 0; t < nst; t += 2) {
         stage(t, x, y);
         if (t + 1 < nst) stage(t + 1, y, x);
+    }
+
+    if (__builtin_amdgcn_readfirstlane(s_flag[0]) & 2) {  // (s_mx is complete since the last stage's barrier)
+        for (int e = tid; e < C::ROWS + C::COLS; e += TT) {
+            const float mx = __uint_as_float(s_mx[e]);
+            if (mx > 0.f && mx * split_scale(s_sh[e]) < kSplitLeast) s_flag[2] = 1;
+        }
+    }
+    __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(s_flag[2]) != 0) {
+#pragma unroll 1
+        for (int kb = 64 * (wave / C::CG); kb < k; kb += 64 * (8 / C::CG))
+            proj_fwd_tile<float, 2, 2, 2>(P, Mv, F, k, d, vbeg, vend, kb, dbase + 64 * (wave % C::CG), O);
+        return;
     }
 
     const int col = dbase + cg * 64 + 4 * m16;

@@ -12,9 +12,10 @@
 // the basis tile they all read comes from HBM once and from that XCD's L2 afterwards.
 //
 // Scales (powers of two): each basis row and feature column takes one from the first stage of the chunk, with room for
-// values 64 times as large.  The largest scaled magnitude is followed in a register; a chunk that holds one that does
-// not fit (or an infinity) is computed again by the general float32 routine.  (Lowering the scales and the sums inside
-// the stage loop, or leaving the loop to restart it, made the register allocator spill.)
+// values 64 times as large; one that is all zeros there borrows that of the wave's largest one.  The largest magnitudes
+// are followed in registers; a chunk where one does not fit (or is infinite), or lies too low on a borrowed scale to keep
+// its bits, is computed again by the general float32 routine.  (Lowering the scales and the sums inside the stage loop,
+// or leaving the loop to restart it, made the register allocator spill.)
 //
 // What bounds it: the feature stream (5.3 TB/s with the reduction at d = 256; loads and barriers alone take 64 of the
 // 69 us of 64 shapes of n = 5000, k = 50).  Measured with the reduction, against three-part bf16 operands (six
@@ -116,27 +117,35 @@ __device__ __forceinline__ void h2_block(const float *__restrict__ P, const floa
         for (int i = 0; i < HFF; ++i) mx = fmaxf(mx, fabsf(fr[i][tt]));
         return mx;
     };
-    // Scales from the values of stage t.  The four vertex groups of a row or column agree; one that is all zeros takes
-    // the scale of the wave's largest one (sparse features: its first values are likely to be as large as the others').
+    auto over_groups = [](float mx) {
+        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+        return fmaxf(mx, __shfl_xor(mx, 32, 64));
+    };
+    // Scales from the values of stage t.  The four vertex groups of a row or column agree; one that is all zeros borrows
+    // that of the wave's largest one (sparse features: its first values are likely to be as large as the others').
+    // lanes whose column tt [0..3] or row [4] borrowed its scale, and whether any of the wave did
+    uint64_t borrowed[5], any = 0;
     auto take_scales = [&](int t, const f32x4 (&fr)[HFF]) {
         float x[8];
         basis(t, x);
-        auto over_groups = [](float mx) {
-            mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-            return fmaxf(mx, __shfl_xor(mx, 32, 64));
-        };
         float mx = over_groups(magnitude(x)), top = wave_max(mx);
         const int sh = split_shift<9>(__float_as_uint(mx > 0.f ? mx : top));
         rsc = split_scale(sh);
         if (g4 == 0) s_sh[16 * wave + m16] = sh;
+        borrowed[4] = __ballot(mx == 0.f && srow_ok);
+        any |= borrowed[4];
         float cm[4];
 #pragma unroll
-        for (int tt = 0; tt < 4; ++tt) cm[tt] = over_groups(magnitude_of(fr, tt));
+        for (int tt = 0; tt < 4; ++tt) {
+            cm[tt] = over_groups(magnitude_of(fr, tt));
+            borrowed[tt] = __ballot(cm[tt] == 0.f);
+            any |= borrowed[tt];
+        }
         top = wave_max(fmaxf(fmaxf(cm[0], cm[1]), fmaxf(cm[2], cm[3])));
 #pragma unroll
         for (int tt = 0; tt < 4; ++tt) csc[tt] = split_scale(split_shift<9>(__float_as_uint(cm[tt] > 0.f ? cm[tt] : top)));
     };
-    float big = 0.f;  // largest scaled magnitude so far
+    float rmx = 0.f, cmx[4] = {0.f, 0.f, 0.f, 0.f};  // largest magnitudes so far of the row and the columns
     auto stage = [&](int t, const f32x4 (&fr)[HFF]) {
         {
             float x[8];
@@ -151,7 +160,7 @@ __device__ __forceinline__ void h2_block(const float *__restrict__ P, const floa
             }
             parts[wave * 64 + lane] = h;
             parts[(4 + wave) * 64 + lane] = l;
-            big = fmaxf(big, magnitude(x) * rsc);
+            rmx = fmaxf(rmx, magnitude(x));
         }
         lds_barrier();
         u32x4_t A[4][2];
@@ -169,7 +178,7 @@ __device__ __forceinline__ void h2_block(const float *__restrict__ P, const floa
                 h[jj] = hh;
                 l[jj] = ll;
             }
-            big = fmaxf(big, magnitude_of(fr, tt) * csc[tt]);
+            cmx[tt] = fmaxf(cmx[tt], magnitude_of(fr, tt));
 #pragma unroll
             for (int a = 0; a < 4; ++a) acc[a][tt] = mfma16x16x32f16(A[a][1], h, acc[a][tt]);
 #pragma unroll
@@ -223,10 +232,23 @@ __device__ __forceinline__ void h2_block(const float *__restrict__ P, const floa
         }
     }
     wait_vmcnt<0>();
+    float big = rmx * rsc;
+#pragma unroll
+    for (int tt = 0; tt < 4; ++tt) big = fmaxf(big, cmx[tt] * csc[tt]);
     if (!(big < kSplitLimit)) s_sh[64] = 1;
+    if (any != 0) {
+        auto low = [&](float mx, float sc, uint64_t of) {
+            mx = over_groups(mx);
+            return (of >> lane & 1) != 0 && mx > 0.f && mx * sc < kSplitLeast;
+        };
+        bool bad = low(rmx, rsc, borrowed[4]);
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) bad = low(cmx[tt], csc[tt], borrowed[tt]) || bad;
+        if (bad) s_sh[64] = 1;
+    }
     __syncthreads();
     if (__builtin_amdgcn_readfirstlane(s_sh[64]) != 0) {
-        proj_fwd_tile<float, 2, 2, 4>(P, Mv, F, k, d, vbeg, vend, 0, dbase + 64 * wave, O);
+        proj_fwd_tile<float, 2, 2, 2>(P, Mv, F, k, d, vbeg, vend, 0, dbase + 64 * wave, O);
         return;
     }
 

@@ -1,4 +1,4 @@
-"""The scales of the split forward projection (float32): rows and columns that are zero in the first stage of 32
+"""The scales of the split forward projections (float32): rows and columns that are zero in the first stage of 32
 vertices of a chunk, or in the one where another value outgrows its scale, and are then far smaller than the others;
 infinities beside them.  220 vertices are one chunk of seven stages in every kernel.
 
@@ -13,8 +13,8 @@ import oracle
 pytestmark = pytest.mark.gpu
 TOL = 2e-6
 N = 220
-# one size for each instance of the tall kernel
-SIZES = [(70, 128), (120, 300), (150, 260), (250, 320), (319, 400)]
+# k <= 64 (three widths of its basis windows), then one size for each instance of the tall kernel
+SIZES = [(30, 128), (45, 300), (64, 512), (70, 128), (120, 300), (150, 260), (250, 320), (319, 400)]
 
 
 def _inputs(k, d, kind):
@@ -80,7 +80,7 @@ def test_plan(dev, kind):
     import torch
     from paper_2604_10377_amd import fmap as F
     pairs, arrays = [], []
-    for k in (70, 120):
+    for k in (45, 120):
         phi, mass, feat = _inputs(k, 256, kind)
         arrays.append((phi, mass, feat))
         t = [torch.from_numpy(x).to(dev) for x in (phi, mass, feat)]

@@ -11,11 +11,12 @@
 // barrier every wave reads all four tiles.  The column blocks of one vertex chunk take consecutive ids on one XCD, so
 // the basis tile they all read comes from HBM once and from that XCD's L2 afterwards.
 //
-// Scales (powers of two): each basis row and feature column takes one from the first stage of the chunk, with room for
-// values 64 times as large; one that is all zeros there borrows that of the wave's largest one.  The largest magnitudes
-// are followed in registers; a chunk where one does not fit (or is infinite), or lies too low on a borrowed scale to keep
-// its bits, is computed again by the general float32 routine.  (Lowering the scales and the sums inside the stage loop,
-// or leaving the loop to restart it, made the register allocator spill.)
+// Scales (powers of two): each basis row and feature column takes one from the first stage of the chunk (a column from
+// its vertices of nonzero mass), with room for values 64 times as large; one that is all zeros there borrows that of the
+// wave's largest one.  The largest magnitudes are followed in registers; a chunk where one does not fit (or is infinite),
+// or lies too low on a borrowed scale to keep its bits, is computed again by the general float32 routine, and so is one
+// with borrowed scales and massless vertices, whose values would hide that.  (Lowering the scales and the sums inside the
+// stage loop, or leaving the loop to restart it, made the register allocator spill.)
 //
 // What bounds it: the feature stream (5.3 TB/s with the reduction at d = 256; loads and barriers alone take 64 of the
 // 69 us of 64 shapes of n = 5000, k = 50).  Measured with the reduction, against three-part bf16 operands (six
@@ -36,7 +37,7 @@ constexpr int HNST = 3;                     // basis stages in the LDS ring
 constexpr int HFF = 8;                      // feature loads per lane per stage
 constexpr int HSTAGE = 8 * 1024 + 256;      // basis tile (32 x k floats, k <= 64) + masses
 constexpr int HPARTS = 2 * 4 * 64 * 16;     // split basis tile: [part][row tile][lane] of 16 bytes
-constexpr size_t h2_lds() { return (size_t)HNST * HSTAGE + HPARTS + 64 * sizeof(int) + 16; }
+constexpr size_t h2_lds() { return (size_t)HNST * HSTAGE + HPARTS + 64 * sizeof(int) + 16; }  // (+ row shifts, flags)
 
 // BW: basis windows of 64 floats per wave and stage, 4 BW >= k / 2
 template <int BW>
@@ -53,7 +54,7 @@ __device__ __forceinline__ void h2_block(const float *__restrict__ P, const floa
 
     char *ring = reinterpret_cast<char *>(smem);
     u32x4_t *parts = reinterpret_cast<u32x4_t *>(ring + HNST * HSTAGE);
-    int *s_sh = reinterpret_cast<int *>(parts + 2 * 4 * 64);  // [64] row shifts (row 4 R + a at 16 a + R), [1] a flag
+    int *s_sh = reinterpret_cast<int *>(parts + 2 * 4 * 64);  // [64] row shifts (row 4 R + a at 16 a + R), [2] flags
 
     // feature role: columns fc .. fc + 3 (clamped into d; d % 4 == 0) of vertices 8 g4 .. + 7
     const int cw = wave * 64 + 4 * m16;
@@ -90,16 +91,16 @@ __device__ __forceinline__ void h2_block(const float *__restrict__ P, const floa
     const int srow_c = min(srow, k - 1);
     float rsc = 0.f, csc[4];  // the row's and the columns' scales
 
-    auto basis = [&](int t, float (&x)[8]) {  // basis x mass of the split role
+    auto basis = [&](int t, float (&x)[8], float (&mv)[8]) {  // basis x mass of the split role, and the masses
         const char *S = ring + (t % HNST) * HSTAGE;
         const float *Ps = reinterpret_cast<const float *>(S);
         const float *Ms = reinterpret_cast<const float *>(S + 8 * 1024);
         const int vrem = vend - (vbeg + t * HS);
         const f32x4 m0 = *reinterpret_cast<const f32x4 *>(Ms + 8 * g4);
         const f32x4 m1 = *reinterpret_cast<const f32x4 *>(Ms + 8 * g4 + 4);
-        const float mv[8] = {m0[0], m0[1], m0[2], m0[3], m1[0], m1[1], m1[2], m1[3]};
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
+            mv[i] = i < 4 ? m0[i] : m1[i - 4];
             // the mass is masked, not the product, so the LDS reads are unconditional and issued together
             const float pv = Ps[(8 * g4 + i) * k + srow_c];
             x[i] = pv * ((srow_ok && 8 * g4 + i < vrem) ? mv[i] : 0.f);
@@ -126,8 +127,8 @@ __device__ __forceinline__ void h2_block(const float *__restrict__ P, const floa
     // lanes whose column tt [0..3] or row [4] borrowed its scale, and whether any of the wave did
     uint64_t borrowed[5], any = 0;
     auto take_scales = [&](int t, const f32x4 (&fr)[HFF]) {
-        float x[8];
-        basis(t, x);
+        float x[8], mv[8];
+        basis(t, x, mv);
         float mx = over_groups(magnitude(x)), top = wave_max(mx);
         const int sh = split_shift<9>(__float_as_uint(mx > 0.f ? mx : top));
         rsc = split_scale(sh);
@@ -136,8 +137,21 @@ __device__ __forceinline__ void h2_block(const float *__restrict__ P, const floa
         any |= borrowed[4];
         float cm[4];
 #pragma unroll
+        for (int tt = 0; tt < 4; ++tt) cm[tt] = magnitude_of(fr, tt);
+        bool massless = false;
+#pragma unroll
+        for (int i = 0; i < HFF; ++i) massless = massless || mv[i] == 0.f;
+        if (__ballot(massless) != 0) {
+#pragma unroll
+            for (int tt = 0; tt < 4; ++tt) {
+                cm[tt] = 0.f;
+#pragma unroll
+                for (int i = 0; i < HFF; ++i) cm[tt] = fmaxf(cm[tt], mv[i] != 0.f ? fabsf(fr[i][tt]) : 0.f);
+            }
+        }
+#pragma unroll
         for (int tt = 0; tt < 4; ++tt) {
-            cm[tt] = over_groups(magnitude_of(fr, tt));
+            cm[tt] = over_groups(cm[tt]);
             borrowed[tt] = __ballot(cm[tt] == 0.f);
             any |= borrowed[tt];
         }
@@ -148,8 +162,8 @@ __device__ __forceinline__ void h2_block(const float *__restrict__ P, const floa
     float rmx = 0.f, cmx[4] = {0.f, 0.f, 0.f, 0.f};  // largest magnitudes so far of the row and the columns
     auto stage = [&](int t, const f32x4 (&fr)[HFF]) {
         {
-            float x[8];
-            basis(t, x);
+            float x[8], mv[8];
+            basis(t, x, mv);
             u32x4_t h, l;
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) {
@@ -198,7 +212,7 @@ __device__ __forceinline__ void h2_block(const float *__restrict__ P, const floa
     // prefetch included.
     f32x4 f0[HFF], f1[HFF], f2[HFF];
     constexpr int VPS = BW + 1 + HFF;  // vector-memory operations per stage
-    if (tid == 0) s_sh[64] = 0;
+    if (tid < 2) s_sh[64 + tid] = 0;
     issue(0, f0);
     __builtin_amdgcn_sched_barrier(0);
     issue(min(1, nst - 1), f1);
@@ -237,16 +251,25 @@ __device__ __forceinline__ void h2_block(const float *__restrict__ P, const floa
     for (int tt = 0; tt < 4; ++tt) big = fmaxf(big, cmx[tt] * csc[tt]);
     if (!(big < kSplitLimit)) s_sh[64] = 1;
     if (any != 0) {
-        auto low = [&](float mx, float sc, uint64_t of) {
+        auto low = [&](float mx, float sc, uint64_t of, bool &foreign) {
             mx = over_groups(mx);
-            return (of >> lane & 1) != 0 && mx > 0.f && mx * sc < kSplitLeast;
+            foreign = mx > 0.f && (of >> lane & 1) != 0;
+            return foreign && mx * sc < kSplitLeast;
         };
-        bool bad = low(rmx, rsc, borrowed[4]);
+        bool foreign;
+        if (low(rmx, rsc, borrowed[4], foreign)) s_sh[64] = 1;
 #pragma unroll
-        for (int tt = 0; tt < 4; ++tt) bad = low(cmx[tt], csc[tt], borrowed[tt]) || bad;
-        if (bad) s_sh[64] = 1;
+        for (int tt = 0; tt < 4; ++tt) {
+            if (low(cmx[tt], csc[tt], borrowed[tt], foreign)) s_sh[64] = 1;
+            if (foreign) s_sh[65] = 1;
+        }
     }
     __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(s_sh[65]) != 0) {
+        for (int v = vbeg + tid; v < vend; v += 256)
+            if (Mv[v] == 0.f) s_sh[64] = 1;
+        __syncthreads();
+    }
     if (__builtin_amdgcn_readfirstlane(s_sh[64]) != 0) {
         proj_fwd_tile<float, 2, 2, 2>(P, Mv, F, k, d, vbeg, vend, 0, dbase + 64 * wave, O);
         return;

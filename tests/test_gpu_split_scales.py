@@ -1,6 +1,6 @@
 """The scales of the split forward projections (float32): rows and columns that are zero in the first stage of 32
 vertices of a chunk, or in the one where another value outgrows its scale, and are then far smaller than the others;
-infinities beside them.  220 vertices are one chunk of seven stages in every kernel.
+infinities beside them; vertices without mass.  220 vertices are one chunk of seven stages in every kernel.
 
 Tolerance, per entry: the two-part products keep 22 bits of each operand, the general float32 routine 24, and either
 sums at most 110 steps in float32: a few 2^-24 sqrt(steps) of the sum of the entry's terms' magnitudes, 2e-6.
@@ -44,12 +44,20 @@ def _inputs(k, d, kind):
     elif kind == "infinite basis value":
         phi[:96, 5] = 0
         phi[70, 3] = np.inf
+    elif kind == "no mass":
+        mass[10] = 0
+        feat[10] = 1e8
+    elif kind == "no mass beside a late column":
+        mass[10] = mass[40] = 0
+        feat[:32, 5] = 0
+        feat[late, 5] *= 1e-8
+        feat[10, 5] = feat[40, 5] = 1
     return phi.astype(np.float32), mass.astype(np.float32), feat.astype(np.float32)
 
 
 KINDS = ["late column 1e-6", "late column 1e-10", "late column 1e-30", "late row 1e-6", "late row 1e-10", "late row 1e-30",
          "zero where a column outgrows", "zero where a row outgrows", "zero until a column has outgrown",
-         "infinite feature", "infinite basis value"]
+         "infinite feature", "infinite basis value", "no mass", "no mass beside a late column"]
 
 
 def _check(A, phi, mass, feat):
@@ -75,7 +83,7 @@ def test_every_row_and_column_keeps_its_bits(dev, k, d, kind):
 
 
 @pytest.mark.parametrize("kind", ["late column 1e-10", "late row 1e-10", "zero where a column outgrows",
-                                  "infinite feature"])
+                                  "infinite feature", "no mass beside a late column"])
 def test_plan(dev, kind):
     import torch
     from paper_2604_10377_amd import fmap as F

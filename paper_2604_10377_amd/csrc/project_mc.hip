@@ -209,6 +209,14 @@ __global__ __launch_bounds__(256, KW == 4 ? 2 : 1) void proj_fwd_bf16_kernel(con
             x[i].x = pp[0];
             x[i].y = pp[1];
         }
+        if (vrem < BS) {  // past the last vertex the windows repeat other rows' values, which may be NaN
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const uint32_t keep = 8 * g4 + i < vrem ? ~0u : 0u;
+                x[i].x &= keep;
+                x[i].y &= keep;
+            }
+        }
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
             u32x4_t Ap[PARTS];

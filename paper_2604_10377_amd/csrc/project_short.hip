@@ -101,9 +101,10 @@ __device__ __forceinline__ void h2_block(const float *__restrict__ P, const floa
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             mv[i] = i < 4 ? m0[i] : m1[i - 4];
-            // the mass is masked, not the product, so the LDS reads are unconditional and issued together
-            const float pv = Ps[(8 * g4 + i) * k + srow_c];
-            x[i] = pv * ((srow_ok && 8 * g4 + i < vrem) ? mv[i] : 0.f);
+            // past the last vertex the tile repeats its last value, which may be a NaN: the product is masked (its bits,
+            // so that the LDS reads stay unconditional and are issued together)
+            const uint32_t keep = (srow_ok && 8 * g4 + i < vrem) ? ~0u : 0u;
+            x[i] = __uint_as_float(__float_as_uint(Ps[(8 * g4 + i) * k + srow_c] * mv[i]) & keep);
         }
     };
     auto magnitude = [](const float (&x)[8]) {

@@ -31,9 +31,19 @@ __device__ __forceinline__ int tile_index(int I, int J, int TR) { return J * TR 
 // LDS scratch of the diagonal-tile routine below (floats, 16-byte aligned)
 constexpr int DIAG_LR = 16 * 16;
 
+// Wait states.  The compiler keeps the distances that the hardware asks for between its own instructions, but does not
+// see inside the inline assembly here, neither its writes nor its reads.  After a vector instruction that writes a
+// register, two must pass before a DPP operand or a permlane swap reads it, and one before a lane read does.  So
+//   * the DPP operand x of row_fnma: an s_nop 1 tied to the column's own broadcast (xn); used for the columns after it,
+//     it is older;
+//   * both registers of each permlane swap, written by moves in assembly (left to the compiler, the two copies are
+//     one): swap_pad, where fewer than two instructions of diag_rest stand between;
+//   * the next pivot, read from the result of a row_fnma: an s_nop 0 tied to it.
+// diag_rest ends with a scheduling barrier, so what stands before it in the source stays before it.  A CPU test counts
+// the distances in the compiled code.
+
 // acc -= x_Q y, where x_Q is lane Q of the own row of 16 lanes (a DPP row broadcast in the
-// multiply-add; left to the compiler each becomes a move of its own, all held in registers).  x is at least two
-// instructions old.
+// multiply-add; left to the compiler each becomes a move of its own, all held in registers).
 template <int Q>
 __device__ __forceinline__ void row_fnma(float &acc, float x, float y)
 {
@@ -54,6 +64,14 @@ __device__ __forceinline__ void diag_rest(float (&s)[16], float x, float y)
     }
 }
 
+// Before a permlane swap of a and b, written by assembly with items I .. END - 1 of diag_rest<P> after it
+template <int P, int I, int END>
+__device__ __forceinline__ void swap_pad(float &a, float &b)
+{
+    constexpr int between = (diag_rest_count(P) < END ? diag_rest_count(P) : END) - I;
+    if constexpr (between < 2) asm volatile("s_nop %2" : "+v"(a), "+v"(b) : "n"(between == 1 ? 0 : 1));
+}
+
 // Column C of the factor and column C % 16 of its diagonal block's inverse; see diag_factor_inverse.  pv: the
 // pivot.  Dcol: where the own row of the factor goes, Mcol: the own column of the inverse; other lanes have
 // addresses there whose contents are not needed.  From pivot to pivot this is a chain of dependent instructions;
@@ -70,28 +88,31 @@ __device__ __forceinline__ void diag_column(float (&s)[16], float *Dcol, float *
     float ri = __builtin_amdgcn_rcpf(pv * r);  // of the diagonal entry of L: scales the inverse
     diag_rest<P, 3, 6>(s, x, y);
     if constexpr (C < 16) {
+        swap_pad<P, 3, 6>(l, l2);
         const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l), __float_as_uint(l2), false, false);
         l = __uint_as_float(sw[0]);
         float l3;
         asm volatile("v_mov_b32 %0, %2\n\tv_mov_b32 %1, %2" : "=&v"(l2), "=&v"(l3) : "v"(l));
         diag_rest<P, 6, 9>(s, x, y);
+        swap_pad<P, 6, 9>(l2, l3);
         const auto rw = __builtin_amdgcn_permlane16_swap(__float_as_uint(l2), __float_as_uint(l3), false, false);
         xn = __uint_as_float(row16 == 3 ? rw[1] : rw[0]);
     } else {
         float l3;
         asm volatile("v_mov_b32 %0, %1" : "=v"(l3) : "v"(l));
         diag_rest<P, 6, 9>(s, x, y);
+        swap_pad<P, 6, 9>(l2, l3);
         xn = __uint_as_float(__builtin_amdgcn_permlane16_swap(__float_as_uint(l2), __float_as_uint(l3), false, false)[1]);
     }
     const float yn = row16 == 2 ? s[J] * ri : l;
     Dcol[C] = l;
     Mcol[J * TLD] = yn;
     diag_rest<P, 9, 11>(s, x, y);
-    asm volatile("s_nop 1" : "+v"(xn));  // before a DPP operand
+    asm volatile("s_nop 1" : "+v"(xn));  // a DPP operand next
     if constexpr (C < 31) {
         row_fnma<N>(s[N], xn, yn);  // the next pivot's column
         diag_rest<P, 11, 12>(s, x, y);
-        asm volatile("s_nop 0" : "+v"(s[N]));  // before a lane read of an asm result
+        asm volatile("s_nop 0" : "+v"(s[N]));  // a lane read next
         pv = uniform_f(readlane(s[N], C < 15 ? C + 1 : 33 + C));
     }
     diag_rest<P, C < 31 ? 12 : 11, 16>(s, x, y);

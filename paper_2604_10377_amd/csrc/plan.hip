@@ -591,6 +591,8 @@ std::string signature(const fmap_plan *pl)
     return std::string(buf) + ks;
 }
 
+// The grids are stored as tuned and cut to the items at each launch: a plan of the same signature can have many more
+// general items than the one that was timed (features that are not 16-byte aligned; the first may have had none).
 // Line format: "<signature>|chunk grid_fwd rb grid_bwd w_0 w_1 ..." with one row-solve width per k group.
 bool cache_lookup(const char *path, const std::string &sig, fmap_plan *pl)
 {
@@ -788,7 +790,7 @@ fmap_status fmap_plan_create(const fmap_pair *pairs, int32_t npairs, int64_t d, 
         for (int c : chunks) {
             FMAP_TRY(set_fwd(c));
             for (int gm : {1, 2, 4}) {
-                const int g = std::max(1, std::min(gm * cus, pl->nfwd));
+                const int g = gm * cus;
                 const float t = time_ms(st, [&]() { (void)launch_projections_fwd(pl, g, st); });
                 if (t < best) {
                     best = t;
@@ -831,7 +833,7 @@ fmap_status fmap_plan_create(const fmap_pair *pairs, int32_t npairs, int64_t d, 
                 if (pl->nbwd == 0) break;  // rows per item and grid are the general kernel's
                 FMAP_TRY(set_bwd(rb));
                 for (int gm : {1, 2, 4}) {
-                    const int g = std::max(1, std::min(gm * cus, std::max(pl->nbwd, 1)));
+                    const int g = gm * cus;
                     const float t = time_ms(st, [&]() { (void)launch_projections_bwd(pl, g, st); });
                     if (t < best) {
                         best = t;

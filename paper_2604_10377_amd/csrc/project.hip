@@ -362,6 +362,7 @@ int device_cus() { return device_cu_count(); }
 
 hipError_t launch_fwd_items(const FwdItem *items, int nitems, int kmax, int grid, hipStream_t st)
 {
+    grid = std::min(grid, nitems);
     if (kmax <= 32)
         hipLaunchKernelGGL((proj_fwd_items_kernel<1, 2, 8>), dim3(grid), dim3(256), 0, st, items, nitems);
     else
@@ -371,6 +372,7 @@ hipError_t launch_fwd_items(const FwdItem *items, int nitems, int kmax, int grid
 
 hipError_t launch_bwd_items(const BwdItem *items, int nitems, int kmax, int grid, hipStream_t st)
 {
+    grid = std::min(grid, nitems);
     const int kc = kmax < BWD_KC ? kmax : BWD_KC;
     const size_t lds = (size_t)((kc + 1) & ~1) * bwd_stride(8) * sizeof(float);
     static bool attr_set = false;

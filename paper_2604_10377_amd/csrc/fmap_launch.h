@@ -1,6 +1,8 @@
 // Host-side launch entry points shared between the kernel files and the C ABI.
 #pragma once
 
+#include <algorithm>
+
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
@@ -85,6 +87,14 @@ hipError_t launch_fwd_tall_items(const FwdItem *items, int nitems, int cls, hipS
 hipError_t launch_project_bf16(const uint16_t *phi, const float *mass, const uint16_t *feat, int64_t batch, int64_t n,
                                int64_t k, int64_t d, int ns, float *A, void *ws, hipStream_t st);
 int device_cus();
+// Rounds of resident workgroups that `tasks` times `dblocks` column blocks take, when the column blocks of a task run on
+// one of the 8 XCDs and the tasks are dealt to them in turn; `slots` workgroups are resident on the whole chip.  The
+// XCD with the most tasks decides: 84 tasks of 3 blocks are 252 workgroups, but 33 on four of the XCDs with 32 slots.
+inline int64_t xcd_rounds(int64_t tasks, int64_t dblocks, int64_t slots)
+{
+    const int64_t each = std::max<int64_t>(slots / 8, 1);
+    return ((tasks + 7) / 8 * dblocks + each - 1) / each;
+}
 
 struct ProjPlan {
     int MT, NT, kblocks, dblocks, nsplit, chunk;

@@ -218,11 +218,13 @@ void tall_chunks(const fmap_plan *pl, const std::vector<Shape> &shapes, int (&ch
             }
         int64_t t = std::max<int64_t>(256, (work / device_cus() + 31) / 32 * 32);
         for (; t < longest; t += 32) {
-            int64_t items = 0;
+            int64_t tasks = 0, blocks = 1;
             for (const Shape &s : shapes)
-                if (tall_shape(s, pl->d) && tall_class(s.k, pl->d) == c)
-                    items += (s.n + t - 1) / t * ((pl->d + tall_cols(s.k, pl->d) - 1) / tall_cols(s.k, pl->d));
-            if (items <= device_cus()) break;
+                if (tall_shape(s, pl->d) && tall_class(s.k, pl->d) == c) {
+                    tasks += (s.n + t - 1) / t;
+                    blocks = (pl->d + tall_cols(s.k, pl->d) - 1) / tall_cols(s.k, pl->d);
+                }
+            if (xcd_rounds(tasks, blocks, device_cus()) <= 1) break;
         }
         chunk[c] = (int)t;
     }
@@ -332,10 +334,10 @@ void build_bwd_items(fmap_plan *pl, int rb, std::vector<BwdItem> &bi, std::vecto
             }
         int tpi = (int)std::max<int64_t>(1, tiles * blocks / resident);
         for (; tpi < most; ++tpi) {
-            int64_t items = 0;
+            int64_t tasks = 0;
             for (const Shape &s : shapes)
-                if (s.bucket == b) items += ((s.n + verts - 1) / verts + tpi - 1) / tpi * blocks;
-            if (items <= resident) break;
+                if (s.bucket == b) tasks += ((s.n + verts - 1) / verts + tpi - 1) / tpi;
+            if (xcd_rounds(tasks, blocks, resident) <= 1) break;
         }
         std::vector<McItem> ranges;  // (shape, tile range) tasks, column block still open
         for (const Shape &s : shapes) {

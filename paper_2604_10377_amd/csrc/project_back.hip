@@ -306,13 +306,13 @@ int back_verts(int64_t k, int64_t d) { return 32 * (k <= 64 ? 2 : 1) * (k > 192 
 
 // vertex ranges per (shape, column block): the fewest that fill whole rounds of the resident workgroups (>= 95% of the
 // last round busy), at most one range per tile
-static int back_vsplit(int64_t base, int64_t ntile, int64_t slots)
+static int back_vsplit(int64_t batch, int64_t dblocks, int64_t ntile, int64_t slots)
 {
+    const int64_t base = batch * dblocks;
     int best = 1;
     double best_e = 0.0;
     for (int64_t v = 1; v <= ntile && base * v <= 4 * slots; ++v) {
-        const int64_t tot = base * v, rounds = (tot + slots - 1) / slots;
-        const double e = (double)tot / (double)(rounds * slots);
+        const double e = (double)(base * v) / (double)(xcd_rounds(batch * v, dblocks, slots) * slots);
         if (e >= 0.95) return (int)v;
         if (e > best_e + 1e-9) {
             best_e = e;
@@ -335,7 +335,7 @@ static hipError_t dispatch_back(const float *phi, const float *mass, const float
     }
     const int dblocks = (int)((d + C::COLS - 1) / C::COLS);
     const int64_t ntile = (n + C::VERTS - 1) / C::VERTS;
-    const int vsplit = back_vsplit(batch * dblocks, ntile, (int64_t)device_cus() * C::PER_CU);
+    const int vsplit = back_vsplit(batch, dblocks, ntile, (int64_t)device_cus() * C::PER_CU);
     const int ntasks = (int)(batch * vsplit);
     const unsigned grid = (unsigned)(8 * dblocks * ((ntasks + 7) / 8));
     hipLaunchKernelGGL((proj_bwd_split_kernel<KS, CW>), dim3(grid), dim3(512), C::LDS, st, phi, mass, dA, (int)n, (int)k,

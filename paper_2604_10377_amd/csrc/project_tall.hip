@@ -384,15 +384,14 @@ bool tall_shape_ok(int64_t n, int64_t k, int64_t d)
 
 int tall_nsplit(int64_t batch, int64_t n, int64_t k, int64_t d, int64_t cap)
 {
-    const int64_t base = batch * ((d + tall_cols(k, d) - 1) / tall_cols(k, d));
+    const int64_t dblocks = (d + tall_cols(k, d) - 1) / tall_cols(k, d), base = batch * dblocks;
     const int64_t stages = (n + TS - 1) / TS;
     const int64_t slots = device_cus();  // one workgroup per CU (LDS)
     int64_t most = std::min<int64_t>(stages / 4, cap);  // at least 4 stages per chunk
     int64_t ns = 1;
     double best = 0.0;
     for (int64_t v = 1; v <= most && v * base <= 2 * slots; ++v) {
-        const int64_t tot = base * v, rounds = (tot + slots - 1) / slots;
-        const double e = (double)tot / (double)(rounds * slots);
+        const double e = (double)(base * v) / (double)(xcd_rounds(batch * v, dblocks, slots) * slots);
         if (e > best + 0.02) {
             best = e;
             ns = v;

@@ -17,7 +17,7 @@
 // the chunk again.  Loads go through one buffer descriptor per vertex row, whose range ends with the chunk: vertices
 // past its end read as zeros.
 //
-// Instances by k: 4 x 64 columns for k <= 128 (RG = 2 row groups of RT = 4 tiles; d = 128: RG = 4, RT = 2), 2 x 64 above
+// Instances by k: 4 x 64 columns for k <= 128 (RG = 2 row groups of RT = 4 tiles; d <= 128: RG = 4, RT = 2), 2 x 64 above
 // (RG = 4, RT = 3, 4, 5).
 // What bounds it: at 100000 vertices, k = 300, d = 512 the matrix cores and the vector units together (taking out the
 // products or the splitting alone saves a quarter and an eighth of the time), at k <= 200 the chain of one stage
@@ -368,11 +368,13 @@ __global__ __launch_bounds__(TT, 2) void proj_fwd_tall_items_kernel(const FwdIte
                        global_ptr(w.out));
 }
 
-// Instances by k (rows in blocks of 16 RG RT); up to k = 128 with 256 columns per workgroup, or 128 where that leaves
-// fewer idle columns (d = 128: half of the 256 would be idle)
+// Instances by k (rows in blocks of 16 RG RT); up to k = 128 with 256 columns per workgroup, or 128 where d fits those.
+// (Wider d take 256 also where the last block is half idle: blocks of 128 split the basis once each.  k = 100, blocks of
+// 128 and of 256, us: 8 shapes of n = 5000, d = 300 43.5, 32.9; 32 of n = 5000, d = 352 127, 97; 4 of n = 20000, d = 640
+// 96, 75.)
 int tall_class(int64_t k, int64_t d)
 {
-    if (k <= 128) return (d + 127) / 128 * 128 < (d + 255) / 256 * 256 ? 1 : 0;
+    if (k <= 128) return d <= 128 ? 1 : 0;
     return k <= 192 ? 2 : (k <= 256 ? 3 : 4);
 }
 int tall_cols(int64_t k, int64_t d) { return tall_class(k, d) == 0 ? Tall<2, 4>::COLS : Tall<4, 4>::COLS; }

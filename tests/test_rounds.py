@@ -15,3 +15,10 @@ def test_one_round(batch, n, k, d):
     each, blocks = 256 // 8, 3  # CUs of an XCD; 128 columns per block for these d
     if batch * chunks * blocks <= 256:
         assert -(-batch * chunks // 8) * blocks <= each
+
+
+@pytest.mark.parametrize("batch,n,k,d", [(8, 5001, 101, 300), (4, 20001, 127, 352), (10, 9999, 70, 384)])
+def test_wide_blocks_fill_the_chip(batch, n, k, d):
+    """Up to k = 128, d above 128 is cut into blocks of 256 columns: two for these."""
+    chunks = F.fmap_project_workspace_bytes(batch, n, k, d) // (4 * batch * k * d)
+    assert 0.9 * 256 <= 2 * batch * chunks <= 2 * 256

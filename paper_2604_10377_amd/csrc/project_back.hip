@@ -304,22 +304,21 @@ int back_cols(int64_t k, int64_t d) { return 32 * back_cw(k, d); }
 int back_slots(int64_t k) { return device_cus() * (k <= 64 ? 2 : 1); }
 int back_verts(int64_t k, int64_t d) { return 32 * (k <= 64 ? 2 : 1) * (k > 192 ? 1 : 8 / back_cw(k, d)); }
 
-// vertex ranges per (shape, column block): the fewest that fill whole rounds of the resident workgroups (>= 95% of the
-// last round busy), at most one range per tile
+// Vertex ranges per (shape, column block), at most one range per tile: the fewest that take the least time, counted as
+// rounds of resident workgroups times the tiles of the longest range plus three for what a workgroup does first (its
+// columns of dA, 3 to 5 us).  (The fewest that keep 95% of the last round busy took a third round of one tile each where
+// one round of four was 94% full: 2 shapes of n = 5000, k = 100, d = 600 25.0 us, 15.4 now.)
 static int back_vsplit(int64_t batch, int64_t dblocks, int64_t ntile, int64_t slots)
 {
-    const int64_t base = batch * dblocks;
-    int best = 1;
-    double best_e = 0.0;
-    for (int64_t v = 1; v <= ntile && base * v <= 4 * slots; ++v) {
-        const double e = (double)(base * v) / (double)(xcd_rounds(batch * v, dblocks, slots) * slots);
-        if (e >= 0.95) return (int)v;
-        if (e > best_e + 1e-9) {
-            best_e = e;
-            best = (int)v;
+    int64_t best = 1, least = INT64_MAX;
+    for (int64_t v = 1; v <= ntile && (v == 1 || batch * dblocks * v <= 4 * slots); ++v) {
+        const int64_t time = xcd_rounds(batch * v, dblocks, slots) * ((ntile + v - 1) / v + 3);
+        if (time < least) {
+            least = time;
+            best = v;
         }
     }
-    return best;
+    return (int)best;
 }
 
 template <int KS, int CW>

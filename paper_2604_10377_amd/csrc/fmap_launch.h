@@ -58,8 +58,8 @@ int bf16_fwd_nsplit(int64_t batch, int64_t n, int64_t k, int64_t d);
 bool bf16_bwd_shape_ok(int64_t n, int64_t k, int64_t d);
 hipError_t launch_project_backward_bf16(const uint16_t *phi, const float *mass, const float *dA, int64_t batch,
                                         int64_t n, int64_t k, int64_t d, float *dF, hipStream_t st);
-// float32 forward projection for 64 < k <= kMaxK with d < 5 k / 4, operands split into three bf16 parts (k % 4 == 0,
-// d % 4 == 0, n % 4 == 0; items of whole 32-vertex stages): the shapes whose results hang on the last bits of A.
+// float32 forward projection for 64 < k <= kMaxK, operands split into three bf16 parts (k % 4 == 0, d % 4 == 0,
+// n % 4 == 0; items of whole 32-vertex stages): small calls, and shapes with d < 5 k / 4 of any size.
 bool near_square(int64_t k, int64_t d);
 bool sliced_fwd_shape_ok(int64_t n, int64_t k, int64_t d);
 hipError_t launch_project_sliced(const float *phi, const float *mass, const float *feat, int64_t batch, int64_t n,
@@ -69,6 +69,7 @@ hipError_t launch_fwd_sliced_items(const FwdItem *items, int nitems, hipStream_t
 // float32 forward projection for 64 < k <= kMaxK and d >= 5 k / 4 on the float16 matrix cores, operands split into two parts
 // (d % 4 == 0, 16-byte aligned features, any n and k).
 bool tall_shape_ok(int64_t n, int64_t k, int64_t d);
+bool tall_too_small(int64_t batch, int64_t n, int64_t k, int64_t d);
 // Chunks of the vertex sum, at most `cap`.
 int tall_nsplit(int64_t batch, int64_t n, int64_t k, int64_t d, int64_t cap);
 hipError_t launch_project_tall(const float *phi, const float *mass, const float *feat, int64_t batch, int64_t n,

@@ -407,11 +407,12 @@ hipError_t launch_reduce(const float *part, int nsplit, int64_t batch, int64_t k
 hipError_t launch_project(const void *phi, const float *mass, const void *feat, int32_t dtype, int64_t batch, int64_t n,
                           int64_t k, int64_t d, float *A, void *ws, hipStream_t st)
 {
+    if (dtype == 0 && sliced_fwd_shape_ok(n, k, d) && (near_square(k, d) || tall_too_small(batch, n, k, d)) &&
+        aligned16(phi) && aligned16(mass) && aligned16(feat))
+        return launch_project_sliced((const float *)phi, mass, (const float *)feat, batch, n, k, d, A, ws, st);
     if (dtype == 0 && tall_shape_ok(n, k, d) && aligned16(feat) && aligned16(A) && aligned16(ws))
         return launch_project_tall((const float *)phi, mass, (const float *)feat, batch, n, k, d,
                                    tall_chunks(batch, n, k, d), A, ws, st);
-    if (dtype == 0 && sliced_fwd_shape_ok(n, k, d) && aligned16(phi) && aligned16(mass) && aligned16(feat))
-        return launch_project_sliced((const float *)phi, mass, (const float *)feat, batch, n, k, d, A, ws, st);
     if (dtype == 0 && short_shape_ok(n, k, d) && aligned16(feat) && aligned16(A) && aligned16(ws))
         return launch_project_short((const float *)phi, mass, (const float *)feat, batch, n, k, d,
                                     short_chunks(batch, n, k, d), A, ws, st);

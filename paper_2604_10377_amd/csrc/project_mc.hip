@@ -573,13 +573,17 @@ __global__ __launch_bounds__(512, 2) void proj_bwd_mc_kernel(const uint16_t *__r
 constexpr int XS = 32;  // vertices per stage (one matrix-core K step)
 
 // ---------------------------------------------------------------------------
-// Forward projection with float32 basis and features on the bf16 matrix cores for 64 < k and d < 5 k / 4 (k % 4 == 0):
-// both operands split into three bf16 parts, six products kept (float32 level).
+// Forward projection with float32 basis and features on the bf16 matrix cores for 64 < k (k % 4 == 0): both operands
+// split into three bf16 parts, six products kept (float32 level).  For calls that are too small for the tall kernel
+// (64 shapes of n = 5000, k = 120, d = 256 take 139 us here and 115 there; the line stands at tall_too_small), and for
+// d < 5 k / 4.
 //
-// With d so close to k, A A^T is nearly singular (condition about 4000 at k = 120, d = 128) and the last bits of A
-// decide C to 2e-5: any other order or rounding of these sums, the tall kernel's more exact ones included, moves results
-// by more than two float32 builds of the same sums should differ.  These shapes therefore keep the rounding they had;
-// all others run on the tall kernel (k = 120, d = 256: 139 against 115 us).
+// With d so close to k, A A^T is nearly singular, and C moves by the last bits of A times its condition number (about
+// 4000 at k = 120, d = 128): in uneven batches with little regularisation the tall kernel's sums moved C by 2e-5 to
+// 3e-5, more than the results of one build should differ from those of another.  So these shapes keep the sums they
+// had.  That is all the rule is for, it gains no accuracy: against float64, k = 72 to 200 and d = k + 4 to 5 k / 4
+// (condition 3e2 to 1e4), A is 2.2e-7 off here and 1.8e-7 there, C 4.1e-7 to 5.4e-7 and 3.7e-7 to 5.1e-7 with
+// independent features, 1.2e-6 to 1.6e-6 either way with correlated ones.  (k <= 64 has one kernel for every d.)
 //
 // Workgroup = 4 waves over a 256-column block and the 64-row slice [64 kb, 64 kb + 64) of the basis, each stage of 32
 // vertices holding that 64-float slice of every vertex row (8 windows of 4 vertices).  The row blocks and column blocks
@@ -789,7 +793,7 @@ __global__ __launch_bounds__(256, 2) void proj_fwd_x3r_items_kernel(const FwdIte
 
 bool sliced_fwd_shape_ok(int64_t n, int64_t k, int64_t d)
 {
-    return sliced_item_shape_ok(k, d) && n % 4 == 0 && n >= 4 * XS;
+    return k > 64 && k <= kMaxK && k % 4 == 0 && d % 4 == 0 && n % 4 == 0 && n >= 4 * XS;
 }
 
 static int x3_kblocks(int64_t k) { return (int)((k + 63) / 64); }

@@ -379,6 +379,18 @@ int tall_class(int64_t k, int64_t d)
 }
 int tall_cols(int64_t k, int64_t d) { return tall_class(k, d) == 0 ? Tall<2, 4>::COLS : Tall<4, 4>::COLS; }
 
+// Calls too small for this kernel: a workgroup needs 2 us before its first stage and 1.8 us a stage, so with few stages
+// per CU the sliced kernel's smaller workgroups are done sooner, where it takes the shape.  Sliced against tall, by stages
+// per CU: k <= 128 and wide d (256 columns a workgroup) 0.5 to 1 1 / 1.36, 2 to 2.5 1 / 1.13, 4.5 to 5 1 / 1.02, 5 to 6
+// 1.01, 8 to 10 1.06; k <= 128, d <= 128 1 to 1.5 1 / 1.21, 2.5 to 3 1.01; k > 128 2 to 2.5 1 / 1.15, 4 to 4.5 1.00, 5 to
+// 6 1.02 to 1.07 (2 shapes of n = 1000, k = 100, d = 256 12.5 us against 20.7; 4 of n = 5000 23.1 against 24.6; 16 of
+// n = 5000 38.3 against 35.8).  Error against float64 at n = 1000 2.0e-7 sliced, 1.7e-7 tall.
+bool tall_too_small(int64_t batch, int64_t n, int64_t k, int64_t d)
+{
+    const int64_t cols = tall_cols(k, d), stages = batch * ((n + TS - 1) / TS) * ((d + cols - 1) / cols);
+    return 2 * stages < (k > 128 ? 8 : (d > 128 ? 10 : 5)) * (int64_t)device_cus();
+}
+
 bool tall_shape_ok(int64_t n, int64_t k, int64_t d)
 {
     return k > 64 && k <= kMaxK && !near_square(k, d) && d >= 4 && d % 4 == 0 && d <= (1 << 20) && n >= 4 * TS;

@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 TOL = 2e-6
 N = 220
 # k <= 64 (three widths of its basis windows), then one size for each instance of the tall kernel
-SIZES = [(30, 128), (45, 300), (64, 512), (70, 128), (120, 300), (150, 260), (250, 320), (319, 400)]
+SIZES = [(30, 128), (45, 300), (64, 512), (70, 128), (122, 300), (150, 260), (250, 320), (319, 400)]
 
 
 def _inputs(k, d, kind):

@@ -304,18 +304,34 @@ int back_cols(int64_t k, int64_t d) { return 32 * back_cw(k, d); }
 int back_slots(int64_t k) { return device_cus() * (k <= 64 ? 2 : 1); }
 int back_verts(int64_t k, int64_t d) { return 32 * (k <= 64 ? 2 : 1) * (k > 192 ? 1 : 8 / back_cw(k, d)); }
 
-// Vertex ranges per (shape, column block), at most one range per tile: the fewest that take the least time, counted as
-// rounds of resident workgroups times the tiles of the longest range plus three for what a workgroup does first (its
-// columns of dA, 3 to 5 us).  (The fewest that keep 95% of the last round busy took a third round of one tile each where
-// one round of four was 94% full: 2 shapes of n = 5000, k = 100, d = 600 25.0 us, 15.4 now.)
-static int back_vsplit(int64_t batch, int64_t dblocks, int64_t ntile, int64_t slots)
+// Vertex ranges per (shape, column block), at most one range per tile.
+// One workgroup per CU (k > 64): the fewest ranges that take the least time, counted as rounds of resident workgroups
+// times the tiles of the longest range plus three for what a workgroup does first (its columns of dA, 3 to 5 us).  (The
+// fewest that keep 95% of the last round busy took a third round of one tile each where one round of four was 94% full:
+// 2 shapes of n = 5000, k = 100, d = 600 25.0 us, 15.4 now.)
+// Two per CU (k <= 64): one's start hides behind the other's tiles, and more, shorter ranges even out the rounds: the
+// fewest that keep 95% of the last round busy (32 shapes of n = 2992, k = 38, d = 300 54 us, counted as above 65; 16 of
+// n = 5000, k = 30, d = 128 10.7 and 12.6).
+static int back_vsplit(int64_t batch, int64_t dblocks, int64_t ntile, int64_t slots, int per_cu)
 {
+    const int64_t base = batch * dblocks;
     int64_t best = 1, least = INT64_MAX;
-    for (int64_t v = 1; v <= ntile && (v == 1 || batch * dblocks * v <= 4 * slots); ++v) {
-        const int64_t time = xcd_rounds(batch * v, dblocks, slots) * ((ntile + v - 1) / v + 3);
-        if (time < least) {
-            least = time;
-            best = v;
+    double best_e = 0.0;
+    for (int64_t v = 1; v <= ntile && (v == 1 || base * v <= 4 * slots); ++v) {
+        if (per_cu > 1) {
+            const int64_t tot = base * v, rounds = (tot + slots - 1) / slots;
+            const double e = (double)tot / (double)(rounds * slots);
+            if (e >= 0.95) return (int)v;
+            if (e > best_e + 1e-9) {
+                best_e = e;
+                best = v;
+            }
+        } else {
+            const int64_t time = xcd_rounds(batch * v, dblocks, slots) * ((ntile + v - 1) / v + 3);
+            if (time < least) {
+                least = time;
+                best = v;
+            }
         }
     }
     return (int)best;
@@ -334,7 +350,7 @@ static hipError_t dispatch_back(const float *phi, const float *mass, const float
     }
     const int dblocks = (int)((d + C::COLS - 1) / C::COLS);
     const int64_t ntile = (n + C::VERTS - 1) / C::VERTS;
-    const int vsplit = back_vsplit(batch, dblocks, ntile, (int64_t)device_cus() * C::PER_CU);
+    const int vsplit = back_vsplit(batch, dblocks, ntile, (int64_t)device_cus() * C::PER_CU, C::PER_CU);
     const int ntasks = (int)(batch * vsplit);
     const unsigned grid = (unsigned)(8 * dblocks * ((ntasks + 7) / 8));
     hipLaunchKernelGGL((proj_bwd_split_kernel<KS, CW>), dim3(grid), dim3(512), C::LDS, st, phi, mass, dA, (int)n, (int)k,

@@ -43,13 +43,16 @@ struct Back {
     static constexpr int KW = KS >= 7 ? 2 : 1;          // waves along k
     static constexpr int VW = 8 / (CW * KW);            // waves along the vertices
     static_assert(VW >= 1, "eight waves");
+    // (the last pass alone is clamped into the row: the others end below the least k of the instance)
+    static constexpr int least_k() { return KS == 1 ? 4 : (KS == 6 ? 129 : (KS == 10 ? 257 : 32 * KS - 31)); }
     static constexpr int STEPS = 2 * KS / KW;           // matrix-core steps of 16 k per wave
-    static constexpr int VT = KS <= 2 ? 2 : 1;          // vertex tiles of 32 per wave
+    static constexpr int VT = KS <= 2 && CW > 2 ? 2 : 1;  // vertex tiles of 32 per wave
     static constexpr int VERTS = 32 * VT * VW;          // vertices per tile of the workgroup
     static constexpr int COLS = 32 * CW;                // columns per workgroup
     static constexpr int RPW = VERTS / 8;               // rows a wave loads
     static constexpr int LR = 64 / RPW;                 // lanes per row
     static constexpr int PASS = (4 * KS + LR - 1) / LR; // 8-value pieces per lane
+    static_assert(8 * LR * (PASS - 1) < least_k(), "passes below the row's end");
     static constexpr int BUF = VERTS * KS * 8;          // 16-byte slots per tile (two float16 parts per value)
     static constexpr int XCH = KW > 1 ? 8 * 8 * 64 : 0; // floats that the waves along k exchange
     static constexpr size_t LDS = (size_t)2 * BUF * 16 + (2 * VERTS * 2 + XCH) * sizeof(float);
@@ -295,14 +298,22 @@ __global__ __launch_bounds__(512, KS <= 2 ? 4 : 2) void proj_bwd_split_items_ker
 
 bool back_shape_ok(int64_t k, int64_t d) { return k >= 4 && k <= kMaxK && d >= 1 && d <= (1 << 20); }
 
-// 256 columns per workgroup, or 128 where that leaves fewer idle columns or the weights need two waves along k
+// 256 columns per workgroup, or 128 where that leaves fewer idle columns or the weights need two waves along k.  Up to 64
+// columns (coordinates, a few signals) two waves along the columns and four along the vertices, where the larger tile
+// fits LDS: 64 shapes of n = 2001, four waves along the columns and two, us: k = 30, d = 16 10.9, 8.7; k = 100, d = 3 23.0,
+// 18.4; k = 200, d = 16 37.4, 27.1.
 static int back_cw(int64_t k, int64_t d)
 {
+    if (d <= 64 && (k <= 128 || (k > 192 && k <= 256))) return 2;
     return k > 192 || (d + 127) / 128 * 128 < (d + 255) / 256 * 256 ? 4 : 8;
 }
 int back_cols(int64_t k, int64_t d) { return 32 * back_cw(k, d); }
 int back_slots(int64_t k) { return device_cus() * (k <= 64 ? 2 : 1); }
-int back_verts(int64_t k, int64_t d) { return 32 * (k <= 64 ? 2 : 1) * (k > 192 ? 1 : 8 / back_cw(k, d)); }
+int back_verts(int64_t k, int64_t d)
+{
+    const int cw = back_cw(k, d);
+    return 32 * (k <= 64 && cw > 2 ? 2 : 1) * (8 / cw / (k > 192 ? 2 : 1));
+}
 
 // Vertex ranges per (shape, column block), at most one range per tile.
 // One workgroup per CU (k > 64): the fewest ranges that take the least time, counted as rounds of resident workgroups
@@ -372,17 +383,19 @@ static hipError_t dispatch_back_items(const McItem *items, int nitems, hipStream
     return hipGetLastError();
 }
 
+#define FMAP_BACK_CW(FN, KS, ...)                                                                                     \
+    return cw == 8 ? FN<KS, 8>(__VA_ARGS__) : (cw == 4 ? FN<KS, 4>(__VA_ARGS__) : FN<KS, 2>(__VA_ARGS__))
 #define FMAP_BACK(FN, ...)                                                     \
-    const bool wide = back_cw(k, d) == 8;                                      \
+    const int cw = back_cw(k, d);                                              \
     switch ((k + 31) / 32) {                                                   \
-    case 1: return wide ? FN<1, 8>(__VA_ARGS__) : FN<1, 4>(__VA_ARGS__);       \
-    case 2: return wide ? FN<2, 8>(__VA_ARGS__) : FN<2, 4>(__VA_ARGS__);       \
-    case 3: return wide ? FN<3, 8>(__VA_ARGS__) : FN<3, 4>(__VA_ARGS__);       \
-    case 4: return wide ? FN<4, 8>(__VA_ARGS__) : FN<4, 4>(__VA_ARGS__);       \
+    case 1: FMAP_BACK_CW(FN, 1, __VA_ARGS__);                                  \
+    case 2: FMAP_BACK_CW(FN, 2, __VA_ARGS__);                                  \
+    case 3: FMAP_BACK_CW(FN, 3, __VA_ARGS__);                                  \
+    case 4: FMAP_BACK_CW(FN, 4, __VA_ARGS__);                                  \
     case 5:                                                                    \
-    case 6: return wide ? FN<6, 8>(__VA_ARGS__) : FN<6, 4>(__VA_ARGS__);       \
-    case 7: return FN<7, 4>(__VA_ARGS__);                                      \
-    case 8: return FN<8, 4>(__VA_ARGS__);                                      \
+    case 6: return cw == 8 ? FN<6, 8>(__VA_ARGS__) : FN<6, 4>(__VA_ARGS__);    \
+    case 7: return cw == 4 ? FN<7, 4>(__VA_ARGS__) : FN<7, 2>(__VA_ARGS__);    \
+    case 8: return cw == 4 ? FN<8, 4>(__VA_ARGS__) : FN<8, 2>(__VA_ARGS__);    \
     default: return FN<10, 4>(__VA_ARGS__);                                    \
     }
 

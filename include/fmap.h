@@ -75,6 +75,18 @@ const char *fmap_status_str(fmap_status s); /* static string, never NULL        
 /* [batch][k][d] float.  Products are accumulated in float32 (matrix cores);    */
 /* the sum over vertices is split into chunks whose partial sums are added in  */
 /* a fixed order, so results are deterministic.                               */
+/* Precision of float32 calls.  An entry is within a few 2^-24 of the sum of    */
+/* its terms' magnitudes.  Where the operands are split into two float16 parts  */
+/* (most calls with k <= 319 and d % 4 == 0), each keeps 22 bits and shares one  */
+/* power of two with its basis row or feature column over a chunk of vertices:  */
+/* every row and column has its own, but a value below 2^-11 of the largest of   */
+/* its row or column in the chunk keeps fewer bits and is off by at most 2^-34   */
+/* of that largest (2^-6 and 2^-29 where the row or column is zero in the        */
+/* chunk's first 32 vertices).  It shows only in entries whose large values meet */
+/* zeros, or values as small, in the other operand.  A chunk whose values        */
+/* outgrow their scale, or hold an infinity, is summed in float32 products.      */
+/* bfloat16 calls: basis x mass keeps 16 bits (24 where n % 4 != 0).            */
+/* NaN reaches its row or column.  An infinity gives infinities or NaN there.   */
 /* workspace: fmap_project_workspace_bytes(...) bytes (may be 0, then NULL ok). */
 /* ------------------------------------------------------------------------ */
 size_t fmap_project_workspace_bytes(int64_t batch, int64_t n, int64_t k, int64_t d, int32_t in_dtype);
@@ -100,7 +112,12 @@ fmap_status fmap_project_noalloc(const void *phi, const float *mass, const void 
 /* Adjoint of the projection (the chain rule of Eq. (1)):                      */
 /*     dF[b] = diag(mass[b]) Phi[b] dA[b].                                      */
 /* phi [batch][n][k] in `phi_dtype`, mass [batch][n], dA [batch][k][d] float,    */
-/* dF [batch][n][d] float (overwritten).                                         */
+/* dF [batch][n][d] float (overwritten).  float32 basis: as above, with one      */
+/* power of two per basis row (over k) and per column of dA: an entry is within  */
+/* a few 2^-24 of the sum of its terms' magnitudes, and a value below 2^-17 of   */
+/* the largest of its row or column is off by at most 2^-38 of that one (basis   */
+/* columns and rows of dA far apart in scale lose bits to it).  bfloat16 basis:   */
+/* dA keeps 16 bits.                                                            */
 fmap_status fmap_project_backward(const void *phi, const float *mass, int32_t phi_dtype, const float *dA,
                                   int64_t batch, int64_t n, int64_t k, int64_t d, float *dF, void *stream);
 
@@ -229,7 +246,9 @@ fmap_status fmap_solve_vectorized(const float *A, const float *B, const float *o
 /* of each tangent vector; variant B fixes the rotation at +-45 degrees and     */
 /* allows anisotropic scaling.  Float32 level (two-part float16 splits on the   */
 /* matrix cores with float32 accumulation for channels in {32, 64, 128, 256}    */
-/* and 16-byte aligned z; a plain float32 kernel otherwise).  Forward only.     */
+/* and 16-byte aligned z; a plain float32 kernel otherwise): a channel below    */
+/* 2^-17 of the vertex's largest is off by at most 2^-38 of that one, as is an   */
+/* entry of A of its row's largest.  Forward only.                              */
 /* ------------------------------------------------------------------------ */
 #define FMAP_GRADFEAT_A 0
 #define FMAP_GRADFEAT_B 1

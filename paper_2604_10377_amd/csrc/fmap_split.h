@@ -4,7 +4,12 @@
 // parts, h = f16(s x) and l = f16(s x - h), both round-to-nearest-even: 22
 // significant bits and a sign on the residual, so |s x - h - l| <= 2^-23 |s x|
 // for values within 2^-17 of the largest one that shares the scale, and at most
-// 2^-25 in units where that largest value is 2^13 or more.  Of the four part
+// 2^-25 in units where that largest value is 2^13 or more (the short forward:
+// 2^9).  Smaller values lose bits to the largest; an entry of the product shows
+// it only where that one meets zeros, or values as small, in the other operand.
+// (A chunk could be sent to float32 products whenever a group of values lies that
+// low, but features with compact or Gaussian support do so as a rule, and their
+// tails do not reach the results.)  Of the four part
 // products, hh, hl and lh are accumulated in float32 (v_mfma_f32_16x16x32_f16);
 // the dropped ll is below 2^-22 relative and random in sign.
 //

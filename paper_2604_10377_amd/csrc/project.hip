@@ -2,8 +2,12 @@
 //     A[b] = Phi[b]^T diag(M[b]) F[b]          (forward)
 //     dF[b] = diag(M[b]) Phi[b] dA[b]           (its adjoint)
 //
-// Both are tall-skinny contractions over vertex-major (n-major) arrays and run
-// on the float32 matrix cores (v_mfma_f32_32x32x2f32).
+// Both are tall-skinny contractions over vertex-major (n-major) arrays.  This
+// file holds the general kernels, on the float32 matrix cores
+// (v_mfma_f32_32x32x2f32) for any size, type and alignment, the sums of the
+// forward's chunks, and the dispatch: most float32 calls run on the split
+// kernels (project_short.hip, project_tall.hip, project_back.hip; the sliced one
+// and the bf16 ones in project_mc.hip).
 //
 // Forward: the reduction over n is split into `nsplit` chunks.  A workgroup
 // (4 waves) owns one (shape, chunk, k-block, d-block); each wave owns an

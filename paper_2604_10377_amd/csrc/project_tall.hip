@@ -23,8 +23,8 @@
 // products or the splitting alone saves a quarter and an eighth of the time), at k <= 200 the chain of one stage
 // (latencies of LDS and memory at two waves per SIMD).  Alternating products and splitting within a wave gave 3% to 6%
 // for RT <= 4; at RT = 5 it spills.  Measured against the sliced kernel with six bf16 products, projection and
-// reduction: 16 shapes of n = 100000, k = 300, d = 512 2992 -> 1905 us; 64 of n = 5000, k = 120, d = 256 139 -> 115 us;
-// 8 of n = 9998, k = 200, d = 256 (the general kernel took n % 4 != 0) 151 -> 62 us.  The error against float64 falls
+// reduction: 16 shapes of n = 100000, k = 300, d = 512 3043 -> 1879 us; 64 of n = 5000, k = 120, d = 256 141 -> 114 us;
+// 8 of n = 9998, k = 200, d = 256 (the general kernel took n % 4 != 0) 137 -> 55 us.  The error against float64 falls
 // with the number of roundings (three products instead of six): 3.7e-6 -> 2.1e-6, 5.7e-7 -> 4.0e-7, 4.6e-7 -> 3.0e-7.
 #include <algorithm>
 

@@ -49,8 +49,10 @@ int back_slots(int64_t k);
 hipError_t launch_project_back(const float *phi, const float *mass, const float *dA, int64_t batch, int64_t n, int64_t k,
                                int64_t d, float *dF, hipStream_t st);
 hipError_t launch_bwd_split_items(const McItem *items, int nitems, int64_t k, int64_t d, hipStream_t st);
-// Fixed-order sum of split-K partials [batch][nsplit][k][d] into A [batch][k][d].
-hipError_t launch_reduce(const float *part, int nsplit, int64_t batch, int64_t k, int64_t d, float *A, hipStream_t st);
+// Fixed-order sum of split-K partials [batch][nsplit][k][d] into A [batch][k][d]; `parts`: in four parts where few
+// elements have many chunks.
+hipError_t launch_reduce(const float *part, int nsplit, int64_t batch, int64_t k, int64_t d, float *A, bool parts,
+                         hipStream_t st);
 // bf16 forward projection on the bf16 matrix cores (k % 8 == 0, k <= 256, d % 8 == 0, any n).
 bool bf16_fwd_shape_ok(int64_t n, int64_t k, int64_t d);
 int bf16_fwd_nsplit(int64_t batch, int64_t n, int64_t k, int64_t d);

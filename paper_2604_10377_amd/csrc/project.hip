@@ -87,6 +87,38 @@ __global__ __launch_bounds__(256) void proj_reduce_kernel(const float *__restric
     }
 }
 
+// The same sum where few elements have many chunks: wave w of a workgroup takes the w-th quarter of the chunks, and the
+// four sums are added in that order.  One wave alone is a chain of memory round trips, 0.7 us per RG chunks.  Taken from
+// RG + 1 chunks (with RG or fewer one round trip is all there is: 1.015 of the time of the call, above 0.965) up to one
+// workgroup per CU (with two 0.98 to 1.04).  The call, us: 1 shape of n = 20000, k = 4, d = 512 27.5, 18.9 so; 4 of
+// n = 49998, k = 4, d = 16 38.1, 33.1; 2 of n = 5000, k = 30, d = 256 16.0, 14.3.  For k <= 64 alone: with more, C can hang on
+// the last bits of A.
+__global__ __launch_bounds__(256) void proj_reduce_parts_kernel(const float *__restrict__ part, int nsplit, int64_t kd,
+                                                                int64_t total, float *__restrict__ A)
+{
+    __shared__ f32x4 s_sum[3][64];
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int64_t q4 = kd / 4, tq = total / 4, e = (int64_t)blockIdx.x * 64 + lane;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    if (e < tq) {
+        const int64_t s = e / q4, r = e - s * q4;
+        const f32x4 *p = reinterpret_cast<const f32x4 *>(part + (size_t)s * nsplit * kd) + r;
+        const int end = (int)((int64_t)nsplit * (w + 1) / 4);
+        for (int c0 = (int)((int64_t)nsplit * w / 4); c0 < end; c0 += RG) {
+            f32x4 v[RG];
+#pragma unroll
+            for (int u = 0; u < RG; ++u) v[u] = p[(size_t)min(c0 + u, end - 1) * q4];
+#pragma unroll
+            for (int u = 0; u < RG; ++u)
+                if (c0 + u < end) acc += v[u];
+        }
+    }
+    if (w > 0) s_sum[w - 1][lane] = acc;
+    __syncthreads();
+    if (w == 0 && e < tq)
+        reinterpret_cast<f32x4 *>(A)[e] = acc + s_sum[0][lane] + s_sum[1][lane] + s_sum[2][lane];
+}
+
 // The same sum, one element per thread, for any k*d and alignment.
 __global__ __launch_bounds__(256) void proj_reduce1_kernel(const float *__restrict__ part, int nsplit, int64_t kd,
                                                            int64_t total, float *__restrict__ A)
@@ -397,10 +429,15 @@ hipError_t launch_reduce_items(const RedItem *items, int nitems, hipStream_t st)
 }
 
 hipError_t launch_reduce(const float *part, int nsplit, int64_t batch, int64_t k, int64_t d, float *A,
-                                hipStream_t st)
+                         bool parts, hipStream_t st)
 {
     const int64_t total = batch * k * d;
     const bool vec = (k * d) % 4 == 0 && aligned16(part) && aligned16(A);
+    if (parts && vec && nsplit > RG && total <= 256 * (int64_t)device_cus()) {
+        hipLaunchKernelGGL(proj_reduce_parts_kernel, dim3((unsigned)((total / 4 + 63) / 64)), dim3(256), 0, st, part,
+                           nsplit, (int64_t)(k * d), total, A);
+        return hipGetLastError();
+    }
     int64_t blocks = ((vec ? total / 4 : total) + 255) / 256;
     if (blocks > 4096) blocks = 4096;
     hipLaunchKernelGGL(vec ? proj_reduce_kernel : proj_reduce1_kernel, dim3((unsigned)blocks), dim3(256), 0, st, part,
@@ -429,7 +466,7 @@ hipError_t launch_project(const void *phi, const float *mass, const void *feat, 
     else launch_fwd_dt<uint16_t>(phi, mass, feat, batch, n, k, d, p, out, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.nsplit <= 1) return e;
-    return launch_reduce((const float *)ws, p.nsplit, batch, k, d, A, st);
+    return launch_reduce((const float *)ws, p.nsplit, batch, k, d, A, false, st);
 }
 
 template <typename T, int NT>

@@ -309,7 +309,7 @@ hipError_t launch_project_bf16(const uint16_t *phi, const float *mass, const uin
     }
 #undef FMAP_BF
     if (e != hipSuccess || ns <= 1) return e;
-    return launch_reduce(out, ns, batch, k, d, A, st);
+    return launch_reduce(out, ns, batch, k, d, A, false, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -821,7 +821,7 @@ hipError_t launch_project_sliced(const float *phi, const float *mass, const floa
                        ns, dblocks, kblocks, ntiles, out);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || ns <= 1) return e;
-    return launch_reduce(out, ns, batch, k, d, A, st);
+    return launch_reduce(out, ns, batch, k, d, A, false, st);
 }
 
 // 64 < k and d close to k (above)

@@ -353,7 +353,7 @@ hipError_t launch_project_short(const float *phi, const float *mass, const float
 #undef FMAP_H2
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || ns <= 1) return e;
-    return launch_reduce(out, ns, batch, k, d, A, st);
+    return launch_reduce(out, ns, batch, k, d, A, true, st);
 }
 
 hipError_t launch_fwd_short_items(const FwdItem *items, int nitems, hipStream_t st)

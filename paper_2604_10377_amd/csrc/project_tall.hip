@@ -446,7 +446,7 @@ hipError_t launch_project_tall(const float *phi, const float *mass, const float 
     default: e = dispatch_tall<4, 5>(phi, mass, feat, batch, n, k, d, ns, out, st); break;
     }
     if (e != hipSuccess || ns <= 1) return e;
-    return launch_reduce(out, ns, batch, k, d, A, st);
+    return launch_reduce(out, ns, batch, k, d, A, false, st);
 }
 
 template <int RG, int RT>

@@ -492,6 +492,68 @@ static void launch_bwd_t(const void *phi, const float *mass, const float *dA, in
                        (int)k, (int)d, rgroups, RB, dblocks, dF);
 }
 
+// Backward for k = 1, 2, 3 in float32: a stream of dF with a few multiply-adds an entry.  A thread keeps its V columns of
+// dA and walks down the vertices; the rows a workgroup writes at a time are adjacent, so its stores are one run of
+// memory whatever d is.  Bound by the writes (5.4 to 6.2 TB/s).  On the general kernel, whose matrix tiles are made for 32
+// columns of the basis and more, and here: 16 shapes of n = 5000, k = 3, d = 256 25.7 -> 15.1 us; k = 2, d = 300 42 -> 17 us; 4
+// of n = 49998, k = 2, d = 16 18.5 -> 4.9 us.  Ordinary stores: non-temporal ones write the lines that two rows share twice
+// (d = 300 24 us).
+constexpr int FEW_U = 4;  // rows whose basis values and masses are in flight together
+
+template <int K, int V>
+__global__ __launch_bounds__(256) void proj_bwd_few_kernel(const float *__restrict__ phi, const float *__restrict__ mass,
+                                                           const float *__restrict__ dA, int n, int d, int per, int cblocks,
+                                                           int chunks, int steps, float *__restrict__ dF)
+{
+    typedef float vec __attribute__((ext_vector_type(V)));
+    const int cb = blockIdx.x % cblocks, q = blockIdx.x / cblocks;
+    const int chunk = q % chunks, s = q / chunks;
+    const int R = 256 / per, r = threadIdx.x / per, c = V * (cb * 256 + (int)threadIdx.x - r * per);
+    if (r >= R || c >= d) return;
+    const float *P = phi + (size_t)s * n * K, *M = mass + (size_t)s * n, *G = dA + (size_t)s * K * d + c;
+    float *O = dF + (size_t)s * n * d + c;
+    vec g[K];
+#pragma unroll
+    for (int j = 0; j < K; ++j) g[j] = *reinterpret_cast<const vec *>(G + (size_t)j * d);
+    const int v0 = chunk * steps * R + r, v1 = min(n, (chunk + 1) * steps * R);
+    for (int v = v0; v < v1; v += FEW_U * R) {
+        float m[FEW_U], a[FEW_U][K];
+#pragma unroll
+        for (int u = 0; u < FEW_U; ++u) {
+            const int row = min(v + u * R, n - 1);
+            m[u] = M[row];
+#pragma unroll
+            for (int j = 0; j < K; ++j) a[u][j] = P[(size_t)row * K + j];
+        }
+#pragma unroll
+        for (int u = 0; u < FEW_U; ++u) {
+            vec o = a[u][0] * m[u] * g[0];
+#pragma unroll
+            for (int j = 1; j < K; ++j) o += a[u][j] * m[u] * g[j];
+            if (v + u * R < v1) *reinterpret_cast<vec *>(O + (size_t)(v + u * R) * d) = o;
+        }
+    }
+}
+
+template <int V>
+static void launch_bwd_few(const float *phi, const float *mass, const float *dA, int64_t batch, int64_t n, int64_t k,
+                           int64_t d, float *dF, hipStream_t st)
+{
+    const int64_t groups = (d + V - 1) / V, per = std::min<int64_t>(groups, 256), cblocks = (groups + 255) / 256;
+    const int64_t R = 256 / per, rows = (n + R - 1) / R;  // rows: of R vertices
+    // eight workgroups per CU where that leaves them 4 to 32 rows
+    const int64_t fair = batch * cblocks * rows / (8 * (int64_t)device_cus()) / FEW_U * FEW_U;
+    const int64_t steps = std::min<int64_t>(std::max<int64_t>(fair, FEW_U), 32), chunks = (rows + steps - 1) / steps;
+    const dim3 grid((unsigned)(batch * cblocks * chunks));
+#define FMAP_FEW(K)                                                                                                   \
+    hipLaunchKernelGGL((proj_bwd_few_kernel<K, V>), grid, dim3(256), 0, st, phi, mass, dA, (int)n, (int)d, (int)per,    \
+                       (int)cblocks, (int)chunks, (int)steps, dF)
+    if (k == 1) FMAP_FEW(1);
+    else if (k == 2) FMAP_FEW(2);
+    else FMAP_FEW(3);
+#undef FMAP_FEW
+}
+
 hipError_t launch_project_backward(const void *phi, const float *mass, int32_t dtype, const float *dA, int64_t batch,
                                    int64_t n, int64_t k, int64_t d, float *dF, hipStream_t st)
 {
@@ -499,6 +561,11 @@ hipError_t launch_project_backward(const void *phi, const float *mass, int32_t d
         return launch_project_back((const float *)phi, mass, dA, batch, n, k, d, dF, st);
     if (dtype == 1 && bf16_bwd_shape_ok(n, k, d) && aligned16(phi) && aligned16(dF))
         return launch_project_backward_bf16((const uint16_t *)phi, mass, dA, batch, n, k, d, dF, st);
+    if (dtype == 0 && k < 4) {
+        if (d % 4 == 0 && aligned16(dA) && aligned16(dF)) launch_bwd_few<4>((const float *)phi, mass, dA, batch, n, k, d, dF, st);
+        else launch_bwd_few<1>((const float *)phi, mass, dA, batch, n, k, d, dF, st);
+        return hipGetLastError();
+    }
     if (dtype == 0) {
         if (d <= 128) launch_bwd_t<float, 4>(phi, mass, dA, batch, n, k, d, dF, st);
         else launch_bwd_t<float, 8>(phi, mass, dA, batch, n, k, d, dF, st);

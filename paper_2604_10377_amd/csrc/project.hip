@@ -88,11 +88,11 @@ __global__ __launch_bounds__(256) void proj_reduce_kernel(const float *__restric
 }
 
 // The same sum where few elements have many chunks: wave w of a workgroup takes the w-th quarter of the chunks, and the
-// four sums are added in that order.  One wave alone is a chain of memory round trips, 0.7 us per RG chunks.  Taken from
-// RG + 1 chunks (with RG or fewer one round trip is all there is: 1.015 of the time of the call, above 0.965) up to one
-// workgroup per CU (with two 0.98 to 1.04).  The call, us: 1 shape of n = 20000, k = 4, d = 512 27.5, 18.9 so; 4 of
-// n = 49998, k = 4, d = 16 38.1, 33.1; 2 of n = 5000, k = 30, d = 256 16.0, 14.3.  For k <= 64 alone: with more, C can hang on
-// the last bits of A.
+// four sums are added in that order.  One wave alone is a chain of memory round trips, 0.7 us per RG chunks.  The call, us:
+// 1 shape of n = 20000, k = 4, d = 512 27.5, 18.9 so; 4 of n = 49998, k = 4, d = 16 38.1, 33.1.  Taken up to one workgroup per
+// CU (with two 0.98 to 1.04 of the time of the call) and above 64 chunks: with 9 to 64 the call alone gains 4% to 11%, but a
+// map of one pair, bound by its launches, does not (37.2, 37.6 us).  For k <= 64 alone: with more, C can hang on the last bits
+// of A.
 __global__ __launch_bounds__(256) void proj_reduce_parts_kernel(const float *__restrict__ part, int nsplit, int64_t kd,
                                                                 int64_t total, float *__restrict__ A)
 {
@@ -433,7 +433,7 @@ hipError_t launch_reduce(const float *part, int nsplit, int64_t batch, int64_t k
 {
     const int64_t total = batch * k * d;
     const bool vec = (k * d) % 4 == 0 && aligned16(part) && aligned16(A);
-    if (parts && vec && nsplit > RG && total <= 256 * (int64_t)device_cus()) {
+    if (parts && vec && nsplit > 8 * RG && total <= 256 * (int64_t)device_cus()) {
         hipLaunchKernelGGL(proj_reduce_parts_kernel, dim3((unsigned)((total / 4 + 63) / 64)), dim3(256), 0, st, part,
                            nsplit, (int64_t)(k * d), total, A);
         return hipGetLastError();

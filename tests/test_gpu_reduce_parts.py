@@ -1,5 +1,5 @@
 """The sum over a short forward projection's chunks (k <= 64), where four waves share it and on either side of that rule:
-8, 9 and more chunks, fewer elements than a wave, the last element count that one workgroup per CU covers and the next.
+64, 65 and more chunks, fewer elements than a wave, the last element count that one workgroup per CU covers and the next.
 
 Tolerance, per entry: float32 sums of at most 32 stages and 156 chunks, a few 2^-24 sqrt(chunks) of the sum of the entry's
 terms' magnitudes, and operands of 22 bits: 2e-6.
@@ -12,9 +12,9 @@ import oracle
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("b,n,k,d", [(1, 1024, 5, 12), (1, 1152, 5, 12), (1, 1153, 1, 4), (3, 1301, 3, 28),
-                                     (2, 5000, 30, 256), (1, 20000, 1, 4), (1, 19999, 33, 300), (2, 2500, 64, 512),
-                                     (2, 2500, 64, 516), (4, 49998, 4, 16)])
+@pytest.mark.parametrize("b,n,k,d", [(1, 8256, 5, 12), (1, 8320, 5, 12), (1, 8321, 1, 4), (3, 9301, 3, 28),
+                                     (2, 20000, 30, 256), (1, 20000, 1, 4), (1, 19999, 33, 300), (2, 8400, 64, 512),
+                                     (2, 8400, 64, 516), (4, 49998, 4, 16)])
 def test_sum_over_chunks(dev, b, n, k, d):
     import torch
     from paper_2604_10377_amd import fmap as F
